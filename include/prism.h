@@ -50,7 +50,7 @@ extern "C" {
 #define PRISM_E_WORKSPACE    -5   /* workspace pointer NULL or smaller than required */
 
 /* ---- arithmetic of the beam contraction (probe synthesis) -------------- */
-#define PRISM_FP32           0    /* FP32 products, FP32 accumulation                   */
+#define PRISM_FP32           0    /* FP32 accuracy: 3 BF16 parts, 6 MFMA products, FP32 accumulation */
 #define PRISM_SPLIT_BF16X3   1    /* hi*hi + hi*lo + lo*hi BF16 MFMA, FP32 accumulation */
 #define PRISM_BF16           2    /* hi*hi BF16 MFMA, FP32 accumulation (error reported) */
 
@@ -447,7 +447,7 @@ int prism_detector_default_bins(const prism_grid* grid, double E0, double dalpha
 #define PRISM_K_WINDOW         6   /* window FFT, |Psi|^2, detector sums */
 #define PRISM_K_POTENTIAL      7   /* projected potential */
 #define PRISM_K_BIN_REDUCE     8   /* multislice detector sums */
-#define PRISM_K_SPLIT          9   /* S-matrix to split-BF16 records (MFMA precisions) */
+#define PRISM_K_SPLIT          9   /* none: the contraction splits the S-matrix itself */
 #define PRISM_K_FIRST         10   /* first slice of an S-matrix build (plane waves from the row spectrum) */
 #define PRISM_TIMING_CLASSES  11
 

@@ -456,9 +456,8 @@ int batch_of(const prism_smatrix_desc* d) {
     return (d->beam_batch > 0 && d->beam_batch < d->n_beams) ? d->beam_batch : d->n_beams;
 }
 
-// Workspace of one probe-synthesis job: coefficients (complex64, or the
-// split layout of the MFMA contraction, whichever is larger), windows and
-// (for windows above 128 pixels) intensities.
+// Workspace of one probe-synthesis job: the contraction's C operand, windows
+// and (for windows above 128 pixels) intensities.
 struct SynthJobDev {
     void* C;
     float2* win;
@@ -467,15 +466,15 @@ struct SynthJobDev {
 SynthJobDev synth_job_carve(const prism_smatrix_desc* d, const prism_probe_plan* plan, Carve& c) {
     const size_t P = (size_t)std::max<int64_t>(plan->n_probes, 1);
     SynthJobDev j;
-    j.C = c.take<char>(split_c_bytes((int64_t)P, d->n_beams));
+    j.C = c.take<char>(c_operand_bytes((int64_t)P, d->n_beams));
     j.win = c.take<float2>(P * d->m_win * d->m_win);
     j.inten = d->m_win > 128 ? c.take<float>(P * d->m_win * d->m_win) : nullptr;
     return j;
 }
-// The MFMA contraction reads S as split records, converted once per distinct
-// S-matrix of a call (nothing is reserved when it splits S itself).
-void* split_s_carve(const prism_smatrix_desc* d, Carve& c) {
-    return contract_reads_split_s() ? c.take<char>(split_s_bytes(d->ns, d->n_beams)) : nullptr;
+// Part of every workspace per distinct S-matrix of a call: the size of the
+// S-matrix with its beams padded to whole K steps.
+char* s_scratch_carve(const prism_smatrix_desc* d, int n_beams, Carve& c) {
+    return c.take<char>((size_t)d->ns * d->ns * ksteps_of(n_beams) * KSTEP * sizeof(float2));
 }
 
 // Consistency of a descriptor filled by prism_smatrix_plan (without recounting
@@ -969,7 +968,7 @@ static int probe_plan_make(const prism_smatrix_desc* d, const double* probe_xy, 
     p.plan_bytes = c.off + 256;
     Carve w(nullptr);
     synth_job_carve(d, &p, w);
-    split_s_carve(d, w);
+    s_scratch_carve(d, d->n_beams, w);
     p.ws_bytes = w.off + 256;
     *plan = p;
     memo_store(d, dalpha, n_bins, C1, C3, dmap, std::move(h), maxpt);
@@ -1070,43 +1069,20 @@ static int synth_validate(const prism_probe_job* jobs, int n_jobs, int precision
         synth_job_carve(jb.desc, jb.plan, c);
     }
     for (int k = 0; k < n_jobs; ++k)
-        if (first_with_same_s(jobs, k) == k) split_s_carve(jobs[k].desc, c);
+        if (first_with_same_s(jobs, k) == k) s_scratch_carve(jobs[k].desc, jobs[k].desc->n_beams, c);
     *need = c.off + 256;
     return PRISM_OK;
 }
 
 // Probe synthesis for several (S-matrix, probe plan) jobs on one stream:
-// coefficients per job, split S per distinct S-matrix (MFMA precisions), one
-// contraction launch for all jobs, one window launch per window side.
+// coefficients per job, one contraction launch for all jobs, one window launch
+// per window side.
 static int synth_run(const prism_probe_job* jobs, int n_jobs, int precision, void* ws, hipStream_t st) {
     std::vector<ContractArgs> ca;
     std::vector<std::vector<WindowArgs>> wa(10);   // by log2(m)
-    const bool split = precision != PRISM_FP32;
-    const bool split_s = split && contract_reads_split_s();
     Carve c(ws);
     std::vector<SynthJobDev> jd(n_jobs);
     for (int k = 0; k < n_jobs; ++k) jd[k] = synth_job_carve(jobs[k].desc, jobs[k].plan, c);
-    std::vector<const void*> s_op(n_jobs, nullptr);
-    for (int k = 0; k < n_jobs; ++k) {
-        const int j = first_with_same_s(jobs, k);
-        if (j < k) {
-            s_op[k] = s_op[j];
-            continue;
-        }
-        void* ss = split_s_carve(jobs[k].desc, c);
-        s_op[k] = split_s ? ss : jobs[k].S;
-        // the split copy serves every job on this S-matrix: convert it when
-        // any of them has probes (the first may have none)
-        bool used = false;
-        for (int i = k; i < n_jobs && !used; ++i)
-            used = jobs[i].plan->n_probes > 0 && first_with_same_s(jobs, i) == k;
-        if (split_s && used) {
-            const prism_smatrix_desc* d = jobs[k].desc;
-            HIP_TRY(timed(PRISM_K_SPLIT, st, [&] {
-                return launch_split_s(precision, static_cast<const float2*>(jobs[k].S), ss, d->n_beams, d->ns, st);
-            }));
-        }
-    }
     for (int k = 0; k < n_jobs; ++k) {
         const prism_probe_job& jb = jobs[k];
         const prism_smatrix_desc* d = jb.desc;
@@ -1127,10 +1103,9 @@ static int synth_run(const prism_probe_job* jobs, int n_jobs, int precision, voi
         const double inv_L = 1.0 / d->grid.cell[0];
         const float amp = (float)(1.0 / std::sqrt((double)B));
         HIP_TRY(timed(PRISM_K_COEFFICIENTS, st, [&] {
-            return split ? launch_coefficients_split(precision, jd[k].C, xy, beams, aberr, P, B, inv_L, amp, st)
-                         : launch_coefficients(static_cast<float2*>(jd[k].C), xy, beams, aberr, P, B, inv_L, amp, st);
+            return launch_coefficients(precision, jd[k].C, xy, beams, aberr, P, B, inv_L, amp, st);
         }));
-        ca.push_back(ContractArgs{jd[k].C, s_op[k], jd[k].win, tstart, tprobes, torigin, corner, plan->n_tiles,
+        ca.push_back(ContractArgs{jd[k].C, static_cast<const float2*>(jb.S), jd[k].win, tstart, tprobes, torigin, corner, plan->n_tiles,
                                   plan->max_per_tile, B, d->ns, M});
         int lg = 0;
         while ((1 << lg) < M) ++lg;
@@ -1580,21 +1555,21 @@ int prism_build_smatrix_streaming(const prism_smatrix_desc* d, const float* V_ho
 // --------------------------------------------------- streaming synthesis --
 struct StreamSynthDev {
     float2* Sst[2];
-    void *C, *Ssplit;
+    void* C;
     float2* win;
     float* inten;
 };
 
 // Beam-chunked synthesis layout: two chunk slots when S is streamed from
-// host memory (none when S is device-resident), the coefficients and split S
-// of one chunk, the windows of all probes.
+// host memory (none when S is device-resident), the coefficients of one
+// chunk, the windows of all probes.
 static void stream_synth_carve(Carve& c, const prism_smatrix_desc* d, const prism_probe_plan* plan, int chunk,
                                bool slots, StreamSynthDev& m) {
     const size_t P = (size_t)std::max<int64_t>(plan->n_probes, 1), M = d->m_win;
     m.Sst[0] = slots ? c.take<float2>((size_t)chunk * d->ns * d->ns) : nullptr;
     m.Sst[1] = slots ? c.take<float2>((size_t)chunk * d->ns * d->ns) : nullptr;
-    m.C = c.take<char>(split_c_bytes((int64_t)P, chunk));
-    m.Ssplit = contract_reads_split_s() ? c.take<char>(split_s_bytes(d->ns, chunk)) : nullptr;
+    m.C = c.take<char>(c_operand_bytes((int64_t)P, chunk));
+    s_scratch_carve(d, chunk, c);
     m.win = c.take<float2>(P * M * M);
     m.inten = M > 128 ? c.take<float>(P * M * M) : nullptr;
 }
@@ -1646,7 +1621,6 @@ static int synth_chunked(const prism_smatrix_desc* d, const void* S, const prism
     auto aberr = (plan->C1 != 0.0 || plan->C3 != 0.0) ? reinterpret_cast<const float2*>(pb + plan->off[8]) : nullptr;
     auto torigin = reinterpret_cast<const int2*>(pb + plan->off[9]);
     const float amp = (float)(1.0 / std::sqrt((double)B));
-    const bool split = precision != PRISM_FP32;
     const double inv_L = 1.0 / d->grid.cell[0];
     const float2* Sb = static_cast<const float2*>(S);
     Ring2 r;
@@ -1668,16 +1642,10 @@ static int synth_chunked(const prism_smatrix_desc* d, const void* S, const prism
             chunk = m.Sst[k];
         }
         const float2* ab = aberr ? aberr + c0 : nullptr;
-        const void* s_op = chunk;
-        if (split && contract_reads_split_s()) {
-            HIP_TRY(timed(PRISM_K_SPLIT, st, [&] { return launch_split_s(precision, chunk, m.Ssplit, nb, d->ns, st); }));
-            s_op = m.Ssplit;
-        }
         HIP_TRY(timed(PRISM_K_COEFFICIENTS, st, [&] {
-            return split ? launch_coefficients_split(precision, m.C, xy, beams + c0, ab, P, nb, inv_L, amp, st)
-                         : launch_coefficients(static_cast<float2*>(m.C), xy, beams + c0, ab, P, nb, inv_L, amp, st);
+            return launch_coefficients(precision, m.C, xy, beams + c0, ab, P, nb, inv_L, amp, st);
         }));
-        ContractArgs ca{m.C, s_op, m.win, tstart, tprobes, torigin, corner, plan->n_tiles, plan->max_per_tile, nb,
+        ContractArgs ca{m.C, chunk, m.win, tstart, tprobes, torigin, corner, plan->n_tiles, plan->max_per_tile, nb,
                         d->ns, M, ci > 0 ? 1 : 0};
         HIP_TRY(timed(PRISM_K_CONTRACT, st, [&] { return launch_contract_batch(precision, &ca, 1, st); }));
         // a streamed slot is free again once its chunk has been read

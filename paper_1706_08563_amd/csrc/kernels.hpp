@@ -59,40 +59,23 @@ hipError_t launch_potential(float* V, int n, int n_slices, double L, const PotAt
                             const int* slice_start, const PotSpecies* species, float rc_max, hipStream_t st);
 
 // ---- probe synthesis ----------------------------------------------------------
-// C[p][b] = amp * exp(-2 pi i (kx_b x_p + ky_b y_p) / L) (FP64 argument, range
-// reduced), times aberr[b] when aberr is not null.
-hipError_t launch_coefficients(float2* C, const double2* xy, const int2* beams, const float2* aberr, int n_probes,
-                               int n_beams, double inv_L, float amp, hipStream_t st);
-
-// Operand records of the MFMA contraction.  A K step is 16 beams; a record
-// holds, for one (pixel or probe, K step), NP parts (hi, lo) x (re, im) x two
-// halves of 8 beams as bf16: NP * 64 bytes, beams past n_beams zero.
-//   split S:  [K step][pixel y ns + x][record]   (pixel-major)
-//   split C:  [probe][K step][record]
+// A K step of the contraction is 16 beams.
 constexpr int KSTEP = 16;
 inline int ksteps_of(int n_beams) { return (n_beams + KSTEP - 1) / KSTEP; }
-// Bytes reserved for either split layout (the split-BF16 size, the larger).
-inline size_t split_s_bytes(int ns, int n_beams) { return (size_t)ns * ns * ksteps_of(n_beams) * 128; }
-inline size_t split_c_bytes(int64_t n_probes, int n_beams) { return (size_t)n_probes * ksteps_of(n_beams) * 128; }
-// True when the MFMA contraction reads S as split records (launch_split_s
-// first); false when it splits the FP32 S-matrix itself.
-bool contract_reads_split_s();
-// S [n_beams][ns][ns] complex64 -> split S (precision PRISM_SPLIT_BF16X3 or PRISM_BF16).
-hipError_t launch_split_s(int precision, const float2* S, void* Ssplit, int n_beams, int ns, hipStream_t st);
-// Coefficients as launch_coefficients, written as split C (precision
-// PRISM_SPLIT_BF16X3 or PRISM_BF16).
-hipError_t launch_coefficients_split(int precision, void* Csplit, const double2* xy, const int2* beams,
-                                     const float2* aberr, int n_probes, int n_beams, double inv_L, float amp,
-                                     hipStream_t st);
+// Bytes of the C operand, one record of up to 128 bytes per (probe, K step).
+inline size_t c_operand_bytes(int64_t n_probes, int n_beams) { return (size_t)n_probes * ksteps_of(n_beams) * 128; }
+// Coefficients amp * exp(-2 pi i (kx_b x_p + ky_b y_p) / L) (FP64 argument, range
+// reduced), times aberr[b] when aberr is not null, as the C operand of `precision`.
+hipError_t launch_coefficients(int precision, void* C, const double2* xy, const int2* beams, const float2* aberr,
+                               int n_probes, int n_beams, double inv_L, float amp, hipStream_t st);
 
 // Windowed contraction of one probe set: win[p][v][u] = sum_b C[p][b] S[b][pix]
 // over the plan's work tiles (16 x 16 pixels from tile_origin, periodic).
-// C and S are complex64 ([n_probes][n_beams], [n_beams][ns][ns]) for FP32;
-// for the MFMA precisions C is split C, and S is split S when
-// contract_reads_split_s() (else complex64).
+// C is the precision's operand (launch_coefficients), S complex64
+// [n_beams][ns][ns].
 struct ContractArgs {
     const void* C;
-    const void* S;
+    const float2* S;
     float2* win;
     const int* tile_start;
     const int* tile_probes;
@@ -101,7 +84,7 @@ struct ContractArgs {
     int n_tiles, max_per_tile, n_beams, ns, m;
     int accumulate = 0;       // add to the windows (partial sums over beam chunks)
 };
-// Probes per workgroup of the MFMA contraction (the plan's work-tile cost unit).
+// Probes per workgroup of the contraction (the plan's work-tile cost unit).
 int contract_probe_chunk();
 // All jobs in as few launches as possible (one per 24 jobs).
 hipError_t launch_contract_batch(int precision, const ContractArgs* jobs, int n_jobs, hipStream_t st);

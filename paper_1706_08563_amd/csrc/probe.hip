@@ -7,6 +7,9 @@
 #include "fft.hpp"
 #include "kernels.hpp"
 
+#include <algorithm>
+#include <type_traits>
+
 namespace prism {
 
 constexpr int WG = 256;
@@ -23,28 +26,6 @@ __device__ __forceinline__ float2 coefficient(double2 r, int2 k, const float2* _
     float2 v = make_float2(amp * c, amp * s);
     if (aberr) v = cmul(v, aberr[b]);
     return v;
-}
-
-__global__ __launch_bounds__(WG) void k_coefficients(float2* __restrict__ C, const double2* __restrict__ xy,
-                                                     const int2* __restrict__ beams,
-                                                     const float2* __restrict__ aberr, int n_probes, int n_beams,
-                                                     double inv_L, float amp) {
-    int64_t total = (int64_t)n_probes * n_beams;
-    for (int64_t i = (int64_t)blockIdx.x * WG + threadIdx.x; i < total; i += (int64_t)gridDim.x * WG) {
-        int p = (int)(i / n_beams), b = (int)(i % n_beams);
-        C[i] = coefficient(xy[p], beams[b], aberr, b, inv_L, amp);
-    }
-}
-
-hipError_t launch_coefficients(float2* C, const double2* xy, const int2* beams, const float2* aberr, int n_probes,
-                               int n_beams, double inv_L, float amp, hipStream_t st) {
-    int64_t total = (int64_t)n_probes * n_beams;
-    int64_t blocks = (total + WG - 1) / WG;
-    if (blocks > 65536) blocks = 65536;
-    if (blocks < 1) blocks = 1;
-    hipLaunchKernelGGL(k_coefficients, dim3((unsigned)blocks), dim3(WG), 0, st, C, xy, beams, aberr, n_probes,
-                       n_beams, inv_L, amp);
-    return hipGetLastError();
 }
 
 // --------------------------------------------------- windowed contraction --
@@ -64,17 +45,17 @@ constexpr int TILE = 16;
 
 // Work of one (request's) probe synthesis inside a batched contraction launch.
 struct ContractJob {
-    const void* C;            // coefficients: complex64 [n_probes][n_beams] (FP32) or split C
-    const void* S;            // S-matrix: complex64 [n_beams][ns][ns] (FP32) or split S
+    const void* C;            // coefficients (k_coefficients)
+    const float2* S;          // S-matrix: complex64 [n_beams][ns][ns]
     float2* win;              // [n_probes][m][m]
     const int* tile_start;    // [n_tiles + 1]
     const int* tile_probes;
     const int2* tile_origin;  // [n_tiles] first pixel (x, y) of each work tile
     const int2* corner;       // window corner per probe
     int n_beams, ns, m;
-    int ksteps;               // K steps of 16 beams (split layouts)
+    int ksteps;               // K steps of 16 beams
     int accumulate;           // 1: add to the windows' contents (beam chunks of one sum)
-    int chunks;               // workgroups per tile (probe chunks)
+    int chunks;               // workgroups per tile
     int n_tiles;
     int block0;               // first logical workgroup of this job
 };
@@ -107,120 +88,55 @@ __device__ __forceinline__ bool locate(const ContractBatch& b, ContractJob& job,
     return true;
 }
 
-namespace fp32c {
-constexpr int PC = 32;   // probes per workgroup
-constexpr int KB = 32;   // beams per LDS chunk
-}
-
-__global__ __launch_bounds__(WG) void k_contract_fp32(ContractBatch batch) {
-    using namespace fp32c;
-    __shared__ float2 cs[KB][PC];
-    __shared__ int pidx[PC];
-    int tile, chunk;
-    ContractJob job;
-    if (!locate(batch, job, tile, chunk)) return;
-    const float2* __restrict__ C = static_cast<const float2*>(job.C);
-    const float2* __restrict__ S = static_cast<const float2*>(job.S);
-    float2* __restrict__ win = job.win;
-    const int* __restrict__ tile_probes = job.tile_probes;
-    const int2* __restrict__ corner = job.corner;
-    const int n_beams = job.n_beams, ns = job.ns, m = job.m;
-    const int t0 = job.tile_start[tile], t1 = job.tile_start[tile + 1];
-    const int pc0 = t0 + chunk * PC;
-    if (pc0 >= t1) return;
-    const int np = min(PC, t1 - pc0);
-    const int2 org = job.tile_origin[tile];
-    const int tid = threadIdx.x;
-    const int px = (org.x + tid % TILE) & (ns - 1);
-    const int py = (org.y + tid / TILE) & (ns - 1);
-    if (tid < PC) pidx[tid] = tid < np ? tile_probes[pc0 + tid] : -1;
-    __syncthreads();
-
-    float2 acc[PC];
-#pragma unroll
-    for (int p = 0; p < PC; ++p) acc[p] = make_float2(0.f, 0.f);
-    const size_t plane = (size_t)ns * ns;
-    const float2* Sp = S + (size_t)py * ns + px;
-
-    for (int b0 = 0; b0 < n_beams; b0 += KB) {
-        for (int e = tid; e < KB * PC; e += WG) {
-            int p = e / KB, kk = e % KB;
-            float2 v = make_float2(0.f, 0.f);
-            if (p < np && b0 + kk < n_beams) v = C[(size_t)pidx[p] * n_beams + b0 + kk];
-            cs[kk][p] = v;
-        }
-        __syncthreads();
-        const int kb = min(KB, n_beams - b0);
-        float2 s[KB];
-#pragma unroll
-        for (int kk = 0; kk < KB; ++kk) s[kk] = kk < kb ? Sp[(size_t)(b0 + kk) * plane] : make_float2(0.f, 0.f);
-#pragma unroll
-        for (int kk = 0; kk < KB; ++kk) {
-#pragma unroll
-            for (int p = 0; p < PC; ++p) {
-                float2 c = cs[kk][p];
-                acc[p].x += c.x * s[kk].x - c.y * s[kk].y;
-                acc[p].y += c.x * s[kk].y + c.y * s[kk].x;
-            }
-        }
-        __syncthreads();
-    }
-#pragma unroll
-    for (int p = 0; p < PC; ++p) {
-        if (p < np) {
-            int q = pidx[p];
-            int2 c0 = corner[q];
-            int v = (py - c0.y) & (ns - 1);
-            int u = (px - c0.x) & (ns - 1);
-            if (v < m && u < m) {
-                float2* w = win + (size_t)q * m * m + (size_t)v * m + u;
-                float2 r = acc[p];
-                if (job.accumulate) r = cadd(*w, r);
-                *w = r;
-            }
-        }
-    }
-}
-
-// ----------------------------------------------- MFMA (BF16) contraction --
-// The complex product is carried by real BF16 MFMA (v_mfma_f32_16x16x32_bf16)
-// through the block identity, with K running over 16 beams twice:
-//   Re = [Cr | -Ci] . [Sr ; Si]        Im = [Ci | Cr] . [Sr ; Si]
-// Split mode: every FP32 operand x = hi + lo with hi = bf16(x), lo = bf16(x - hi),
-// and each product is hi*hi + hi*lo + lo*hi accumulated in FP32 (the lo*lo
-// term, ~2^-16 relative, is dropped).  Plain mode keeps hi*hi only.
+// The complex product is carried by real BF16 MFMA (v_mfma_f32_32x32x16_bf16,
+// FP32 accumulators) over K = 8 beams x (re, im), interleaved: with operand
+// words (re | im << 16),
+//   Re = (Cr, -Ci) . (Sr, Si)        Im = (Ci, Cr) . (Sr, Si)
+// so both need one S operand, and the two C operands are a sign flip and a
+// half-word rotation of the stored word.
 //
-// Operands are staged per K step (16 beams) as records: NP parts (hi, lo) x
-// (re, im) x two halves of 8 beams as bf16, one record per pixel or probe.
-// Both operands are converted once per call, before the contraction, into
-// records in global memory: C per (probe, K step), S per (K step, pixel) in
-// pixel-major order, so that a work tile at any phase reads each of its 16
-// rows of records as one contiguous 2 KB run.  A workgroup copies a K step's
-// records into LDS (S chunks permuted by tile pixel, see rec_key) and feeds
-// the MFMAs while the next step's loads are in flight.  (The alternative
-// PRISM_CONTRACT_PRESPLIT = 0 reads S in its FP32 layout and splits it on the
-// fly: no converted copy, but every phase tile converting its pixels again.)
-// With W wavefronts (4 or 8), wave w owns tile rows (16/W)w .. (16/W)(w+1)-1
-// (16-pixel MFMA column blocks) and all W 16-probe row blocks: 16 W probes
-// per workgroup.
-#ifndef PRISM_CONTRACT_PRESPLIT
-#define PRISM_CONTRACT_PRESPLIT 1   // 1: S as pixel-major split records; 0: FP32 S split on the fly
-#endif
-#ifndef PRISM_CONTRACT_WAVES
-#define PRISM_CONTRACT_WAVES 4   // wavefronts per contraction workgroup (4: 64 probes, 8: 128 probes)
-#endif
+// An FP32 operand is a sum of NP BF16 parts, each the rounding of what the
+// parts before it leave (the differences are exact):
+//   NP = 3 (FP32)   all 24 bits; products hh, hm, mh, mm, hl, lh.  What is
+//                   left out (ml, lm, ll) is at most 2^-25 of the product,
+//                   below the rounding of an FP32 product.
+//   NP = 2 (split)  16 bits; hh, hl, lh (lo lo, ~2^-16 relative, left out).
+//   NP = 1 (BF16)   hh.
+//
+// A workgroup is one work tile (FP32: half of one) x PC = 64 probes: a wave
+// owns CB 32-pixel column blocks, 2 CB tile rows, and all probes (two 32-row
+// blocks).  A lane's S operand of a step of 8 beams is 4 beams of one pixel,
+// which it loads itself (no other wave needs them: nothing goes through LDS)
+// two steps ahead and converts in registers.  C of 16 beams x 64 probes is
+// shared through a double-buffered LDS tile [part][4-beam group][probe], one
+// barrier per 16 beams.
+//
+// Bound: MFMA power.  16,384 probes x 1245 beams x 128^2 windows in split
+// BF16 take 7.0 ms: 1.15 PFLOP/s of MFMA work at the 1.5 GHz the clock drops
+// to, the rate of a large library BF16 product on the same card (1.18).
+// Before: S converted to BF16 records by a pass of its own (1.06 ms, and as
+// much memory again as S) and both operands staged through LDS, 6.8 + 1.06
+// ms; with few probes per pixel the pass was as long as the contraction (441
+// probes of 256^2 windows: 1.16 + 1.07 -> 1.02 ms).  FP32 products on the
+// VALU: 2025 probes x 1245 beams x 128^2, 7.1 -> 2.0 ms with six BF16 products.
 namespace mfmac {
-constexpr int WAVES = PRISM_CONTRACT_WAVES;
-constexpr int NT = 64 * WAVES;        // threads per workgroup
-constexpr int PB = 16 / WAVES;        // tile rows (16-pixel MFMA column blocks) per wave
-constexpr int QB = 16 / PB;           // 16-probe row blocks
-constexpr int PC = 16 * QB;           // probes per workgroup
-constexpr int SH = NT / 256;          // threads per tile pixel in the S staging
-constexpr int HPT = 2 / SH;           // 8-beam halves of a K step converted per thread
+constexpr int NT = 256;               // threads per workgroup
+constexpr int PC = 64;                // probes per workgroup
+constexpr int RB = PC / 32;           // 32-probe row blocks
+constexpr int SUB = 8;                // beams per MFMA step, half a K step
+// 32-pixel column blocks (pairs of tile rows) per wave.  FP32 takes one, and
+// two workgroups per tile, so that the registers of the other hold the sum
+// of the last FLUSH K steps apart from the running total: an FP32 sum of
+// 1245 beams, 6 products each, is otherwise rounded 936 times at the size of
+// the total (2025 probes of 1245 beams: error against 64 bits 1.4e-7 on the
+// VALU, 1.7e-7 without the split total, 9e-8 with it).
+template <int NP> constexpr int CBS = NP == 3 ? 1 : 2;
+template <int NP> constexpr int SPLITS = 2 / CBS<NP>;   // workgroups per (tile, probe chunk)
+template <int NP> constexpr int FLUSH = NP == 3 ? 2 : 1 << 30;
 }
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
-typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 
@@ -229,158 +145,97 @@ __device__ __forceinline__ unsigned int pack_bf16(float a, float b) {
     bf16x2 h = {(__bf16)a, (__bf16)b};
     return __builtin_bit_cast(unsigned int, h);
 }
-// x = hi + lo + O(2^-16 |x|): hi = bf16(x), lo = bf16(x - hi), for a pair.
-__device__ __forceinline__ void split_pair(float a, float b, unsigned int& hi, unsigned int& lo) {
-    hi = pack_bf16(a, b);
-    const float ra = __uint_as_float(hi << 16), rb = __uint_as_float(hi & 0xffff0000u);
-    lo = pack_bf16(a - ra, b - rb);
-}
 __device__ __forceinline__ bf16x8 as_bf16x8(u32x4 v) { return __builtin_bit_cast(bf16x8, v); }
 
-// Record chunk c (= part * 4 + reim * 2 + half) of row r sits at chunk
-// position c ^ key(r): 8 consecutive rows then touch 8 distinct 16-byte bank
-// groups (records of 128 bytes: key = r & 7; of 64 bytes: two rows share a
-// 128-byte line and key = (r >> 1) & 3).
+// The NP parts of one complex value, as words (re | im << 16).
 template <int NP>
-__device__ __forceinline__ int rec_key(int r) { return NP == 2 ? (r & 7) : ((r >> 1) & 3); }
-
-// Records of 8 complex values v[0..7] (beams half*8 + 0..7): writes chunks
-// (reim, half) of each part into ch[part * 4 + reim * 2 + half].
-template <int NP>
-__device__ __forceinline__ void make_chunks(const float2 (&v)[8], int half, u32x4 (&ch)[NP * 4]) {
+__device__ __forceinline__ void split_parts(float re, float im, unsigned int (&w)[NP]) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        unsigned int rh, rl, ih, il;
-        if constexpr (NP == 2) {
-            split_pair(v[2 * i].x, v[2 * i + 1].x, rh, rl);
-            split_pair(v[2 * i].y, v[2 * i + 1].y, ih, il);
-            ch[4 + half][i] = rl;
-            ch[6 + half][i] = il;
-        } else {
-            rh = pack_bf16(v[2 * i].x, v[2 * i + 1].x);
-            ih = pack_bf16(v[2 * i].y, v[2 * i + 1].y);
-        }
-        ch[half][i] = rh;
-        ch[2 + half][i] = ih;
+    for (int part = 0; part < NP; ++part) {
+        w[part] = pack_bf16(re, im);
+        re -= __uint_as_float(w[part] << 16);
+        im -= __uint_as_float(w[part] & 0xffff0000u);
     }
 }
 
-// The record chunks of one 8-beam half of a pixel's K step, written to the
-// pixel's LDS record (chunk c at position c ^ key).
-template <int NP, int HALF>
-__device__ __forceinline__ void stage_s_half(const float2 (&v)[8], u32x4* rec, int key) {
-    u32x4 ch[NP * 4];
-    make_chunks<NP>(v, HALF, ch);
-#pragma unroll
-    for (int part = 0; part < NP; ++part)
-#pragma unroll
-        for (int reim = 0; reim < 2; ++reim) {
-            const int c = part * 4 + reim * 2 + HALF;
-            rec[c ^ key] = ch[c];
-        }
-}
-
-// Split S, pixel-major: out[(k plane + pixel) NCH + c] holds chunk c of the
-// record of K step k at pixel = y ns + x (chunks in order).  Thread = (K step,
-// pixel); consecutive threads read consecutive pixels of each beam plane and
-// write consecutive records.
+// C operands, thread = (probe, group of 4 beams): split records
+// [probe][K step][part][4-beam group] for NP = 1, 2, and the FP32 values
+// [probe][K step][16 beams] (the same bytes as NP = 2) for NP = 3, which the
+// contraction splits as it stages them.  Beams past the last are zero.
 template <int NP>
-__global__ __launch_bounds__(WG) void k_split_s(const float2* __restrict__ S, u32x4* __restrict__ out, int n_beams,
-                                                int plane, int K) {
-    constexpr int NCH = NP * 4;
-    const int64_t i = (int64_t)blockIdx.x * WG + threadIdx.x;
-    if (i >= (int64_t)K * plane) return;
-    const int k = (int)(i / plane), pix = (int)(i % plane);
-    const float2* src = S + pix;
-    float2 v[2][8];
-#pragma unroll
-    for (int h = 0; h < 2; ++h)
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const int b = k * KSTEP + h * 8 + j;
-            v[h][j] = b < n_beams ? src[(size_t)b * plane] : make_float2(0.f, 0.f);
-        }
-    u32x4 ch[NCH];
-    make_chunks<NP>(v[0], 0, ch);
-    make_chunks<NP>(v[1], 1, ch);
-    u32x4* rec = out + i * NCH;
-#pragma unroll
-    for (int c = 0; c < NCH; ++c) rec[c] = ch[c];
-}
-
-hipError_t launch_split_s(int precision, const float2* S, void* Ssplit, int n_beams, int ns, hipStream_t st) {
-    const int K = ksteps_of(n_beams), plane = ns * ns;
-    const int64_t blocks = ((int64_t)K * plane + WG - 1) / WG;
-    if (precision == 1)
-        hipLaunchKernelGGL(k_split_s<2>, dim3((unsigned)blocks), dim3(WG), 0, st, S, static_cast<u32x4*>(Ssplit), n_beams,
-                           plane, K);
-    else
-        hipLaunchKernelGGL(k_split_s<1>, dim3((unsigned)blocks), dim3(WG), 0, st, S, static_cast<u32x4*>(Ssplit), n_beams,
-                           plane, K);
-    return hipGetLastError();
-}
-
-// Split C: thread = (probe, K step, half of 8 beams); records unpermuted.
-template <int NP>
-__global__ __launch_bounds__(WG) void k_coefficients_split(u32x4* __restrict__ Cs, const double2* __restrict__ xy,
-                                                           const int2* __restrict__ beams,
-                                                           const float2* __restrict__ aberr, int n_probes,
-                                                           int n_beams, int K, double inv_L, float amp) {
-    constexpr int NCH = NP * 4;
-    const int64_t total = (int64_t)n_probes * K * 2;
+__global__ __launch_bounds__(WG) void k_coefficients(u32x4* __restrict__ C, const double2* __restrict__ xy,
+                                                     const int2* __restrict__ beams,
+                                                     const float2* __restrict__ aberr, int n_probes, int n_beams,
+                                                     int K, double inv_L, float amp) {
+    const int64_t total = (int64_t)n_probes * K * 4;
     for (int64_t i = (int64_t)blockIdx.x * WG + threadIdx.x; i < total; i += (int64_t)gridDim.x * WG) {
-        const int p = (int)(i / (2 * K)), r = (int)(i % (2 * K)), k = r >> 1, half = r & 1;
+        const int p = (int)(i / (4 * K)), r = (int)(i % (4 * K)), k = r >> 2, g = r & 3;
         const double2 xyp = xy[p];
-        float2 v[8];
+        float2 v[4];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const int b = k * KSTEP + half * 8 + j;
+        for (int j = 0; j < 4; ++j) {
+            const int b = k * KSTEP + g * 4 + j;
             v[j] = b < n_beams ? coefficient(xyp, beams[b], aberr, b, inv_L, amp) : make_float2(0.f, 0.f);
         }
-        u32x4 ch[NCH];
-        make_chunks<NP>(v, half, ch);
-        u32x4* rec = Cs + ((size_t)p * K + k) * NCH;
+        if constexpr (NP == 3) {
+            float4* dst = reinterpret_cast<float4*>(C) + i * 2;
+            dst[0] = make_float4(v[0].x, v[0].y, v[1].x, v[1].y);
+            dst[1] = make_float4(v[2].x, v[2].y, v[3].x, v[3].y);
+        } else {
+            u32x4 ch[NP];
 #pragma unroll
-        for (int part = 0; part < NP; ++part) {
-            rec[part * 4 + half] = ch[part * 4 + half];
-            rec[part * 4 + 2 + half] = ch[part * 4 + 2 + half];
+            for (int j = 0; j < 4; ++j) {
+                unsigned int w[NP];
+                split_parts<NP>(v[j].x, v[j].y, w);
+#pragma unroll
+                for (int part = 0; part < NP; ++part) ch[part][j] = w[part];
+            }
+            u32x4* rec = C + ((size_t)p * K + k) * NP * 4;
+#pragma unroll
+            for (int part = 0; part < NP; ++part) rec[part * 4 + g] = ch[part];
         }
     }
 }
 
-hipError_t launch_coefficients_split(int precision, void* Csplit, const double2* xy, const int2* beams,
-                                     const float2* aberr, int n_probes, int n_beams, double inv_L, float amp,
-                                     hipStream_t st) {
+hipError_t launch_coefficients(int precision, void* C, const double2* xy, const int2* beams, const float2* aberr,
+                               int n_probes, int n_beams, double inv_L, float amp, hipStream_t st) {
     const int K = ksteps_of(n_beams);
-    int64_t total = (int64_t)n_probes * K * 2;
+    const int64_t total = (int64_t)n_probes * K * 4;
     int64_t blocks = (total + WG - 1) / WG;
     if (blocks > 65536) blocks = 65536;
     if (blocks < 1) blocks = 1;
-    u32x4* Cs = static_cast<u32x4*>(Csplit);
-    if (precision == 1)
-        hipLaunchKernelGGL(k_coefficients_split<2>, dim3((unsigned)blocks), dim3(WG), 0, st, Cs, xy, beams, aberr,
-                           n_probes, n_beams, K, inv_L, amp);
+    u32x4* Cw = static_cast<u32x4*>(C);
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(WG), 0, st, Cw, xy, beams, aberr, n_probes, n_beams, K,
+                           inv_L, amp);
+    };
+    if (precision == 0)
+        launch(k_coefficients<3>);
+    else if (precision == 1)
+        launch(k_coefficients<2>);
     else
-        hipLaunchKernelGGL(k_coefficients_split<1>, dim3((unsigned)blocks), dim3(WG), 0, st, Cs, xy, beams, aberr,
-                           n_probes, n_beams, K, inv_L, amp);
+        launch(k_coefficients<1>);
     return hipGetLastError();
 }
 
 template <int NP>
-__global__ __launch_bounds__(mfmac::NT) __attribute__((amdgpu_waves_per_eu(2))) void k_contract_mfma(ContractBatch batch) {
+__global__ __launch_bounds__(mfmac::NT) __attribute__((amdgpu_waves_per_eu(2))) void k_contract(ContractBatch batch) {
     using namespace mfmac;
-    constexpr int NCH = NP * 4;                 // 16-byte chunks per record
-    constexpr int CPT = PC * NCH / NT;          // C chunks staged per thread
-    __shared__ u32x4 Ss[256 * NCH];             // one K step of the tile (pixel records, chunks permuted)
-    __shared__ u32x4 Cl[PC * NCH];              // one K step of the probe chunk (records permuted)
+    constexpr int CB = CBS<NP>;
+    constexpr int NCH = NP * 4;                   // 16-byte chunks per record
+    // probe stride of an LDS chunk row: odd (or = 2 mod 8 when 4 lanes write
+    // one probe) so that 8 lanes of a staging store hit distinct bank groups
+    constexpr int LP = NP == 3 ? PC + 2 : PC + 1;
+    __shared__ u32x4 Cl[2][NCH * LP];
     __shared__ int pidx[PC];
+    __shared__ int2 pcorner[PC];
 
     int tile, chunk;
     ContractJob job;
     if (!locate(batch, job, tile, chunk)) return;
+    const int row0 = 8 * CB * (chunk % SPLITS<NP>);   // first tile row of this workgroup
+    chunk /= SPLITS<NP>;
     float2* __restrict__ win = job.win;
-    const int* __restrict__ tile_probes = job.tile_probes;
-    const int2* __restrict__ corner = job.corner;
     const int ns = job.ns, m = job.m, K = job.ksteps, n_beams = job.n_beams;
     const int t0 = job.tile_start[tile], t1 = job.tile_start[tile + 1];
     const int pc0 = t0 + chunk * PC;
@@ -388,171 +243,204 @@ __global__ __launch_bounds__(mfmac::NT) __attribute__((amdgpu_waves_per_eu(2))) 
     const int np = min(PC, t1 - pc0);
     const int2 org = job.tile_origin[tile];
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    if (tid < PC) pidx[tid] = tid < np ? tile_probes[pc0 + tid] : -1;
-
-    f32x4 accr[QB][PB], acci[QB][PB];
-#pragma unroll
-    for (int a = 0; a < QB; ++a)
-#pragma unroll
-        for (int b = 0; b < PB; ++b) {
-            accr[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
-            acci[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
-        }
-    const size_t plane = (size_t)ns * ns;
-#if PRISM_CONTRACT_PRESPLIT
-    // S staging: chunks q = tid + j NT of the step's 256 x NCH chunks, i.e.
-    // chunk sc of tile pixels sp0 + j PPJ, read by raw buffer loads from a
-    // scalar resource at the K step's records (byte offsets per chunk kept in
-    // registers; rows wrap periodically)
-    constexpr int SPT = 256 * NCH / NT, PPJ = NT / NCH;
-    const int sc = tid % NCH, sp0 = tid / NCH;
-    const int sx = (org.x + sp0 % TILE) & (ns - 1);
-    const int skey = rec_key<NP>(sp0);          // the same for every j: PPJ is a multiple of 8
-    int voff[SPT];
-#pragma unroll
-    for (int j = 0; j < SPT; ++j) {
-        const int sy = (org.y + (sp0 + j * PPJ) / TILE) & (ns - 1);
-        voff[j] = ((sy * ns + sx) * NCH + sc) * (int)sizeof(u32x4);
+    const int col = lane & 31, half = lane >> 5;
+    if (tid < PC) {
+        const int q = tid < np ? job.tile_probes[pc0 + tid] : -1;
+        pidx[tid] = q;
+        pcorner[tid] = q >= 0 ? job.corner[q] : make_int2(0, 0);
     }
-#else
-    // S staging: tile pixel sp, 8-beam halves sh0 .. sh0 + HPT - 1 of each K
-    // step, read by raw buffer loads: a scalar resource at the K step's first
-    // beam plane, the pixel's byte offset in a plane (one register) and the
-    // beam's plane offset as a scalar, so the 16 loads of a step cost no
-    // address registers
-    // (sh0 is uniform over a wavefront: 0 with 4 wavefronts)
-    const int sp = tid & 255, sh0 = SH == 1 ? 0 : __builtin_amdgcn_readfirstlane((tid >> 8) * HPT);
-    const int sy = (org.y + sp / TILE) & (ns - 1), sx = (org.x + sp % TILE) & (ns - 1);
-    const int pix_off = (sy * ns + sx) * (int)sizeof(float2);
-    const int plane_bytes = (int)(plane * sizeof(float2));
-    const int skey = rec_key<NP>(sp);
-#endif
     __syncthreads();
-    // C staging: chunk q = tid * CPT + j of the step's PC x NCH chunks
-    const int crow = (tid * CPT) / NCH, cc0 = (tid * CPT) % NCH;
-    const int cq = pidx[crow];
-    const u32x4* __restrict__ Cg = static_cast<const u32x4*>(job.C) + (size_t)(cq < 0 ? 0 : cq) * K * NCH + cc0;
-    const int ckey = rec_key<NP>(crow);
-    const u32x4 zero = u32x4{0u, 0u, 0u, 0u};
 
-    u32x4 creg[CPT];
-#if PRISM_CONTRACT_PRESPLIT
-    u32x4 sreg[SPT];
-    auto load_s = [&](int k) {
-        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<u32x4*>(static_cast<const u32x4*>(job.S) + (size_t)k * plane * NCH), (short)0, 0x7fffffff,
-            0x00020000);
+    f32x16 accr[RB][CB], acci[RB][CB];
 #pragma unroll
-        for (int j = 0; j < SPT; ++j)
-            sreg[j] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, voff[j], 0, 0));
-    };
-    auto stage_s = [&]() {
+    for (int a = 0; a < RB; ++a)
 #pragma unroll
-        for (int j = 0; j < SPT; ++j) Ss[(sp0 + j * PPJ) * NCH + (sc ^ skey)] = sreg[j];
-    };
-#else
-    float2 sv[HPT][8];
-    auto load_s = [&](int k) {
-        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<float2*>(static_cast<const float2*>(job.S) + (size_t)k * KSTEP * plane), (short)0, 0x7fffffff,
-            0x00020000);
-        const bool full = k * KSTEP + KSTEP <= n_beams;   // every beam of the step exists (uniform)
+        for (int b = 0; b < CB; ++b)
 #pragma unroll
-        for (int h = 0; h < HPT; ++h)
+            for (int r = 0; r < 16; ++r) accr[a][b][r] = acci[a][b][r] = 0.f;
+    f32x16 totr[RB][CB], toti[RB][CB];            // running totals (NP = 3)
+    if constexpr (NP == 3) {
 #pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const int jb = (SH == 1 ? h : sh0) * 8 + j;
-                sv[h][j] = full || k * KSTEP + jb < n_beams
-                               ? __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(rs, pix_off, jb * plane_bytes, 0))
-                               : make_float2(0.f, 0.f);
+        for (int a = 0; a < RB; ++a)
+#pragma unroll
+            for (int b = 0; b < CB; ++b) {
+                totr[a][b] = accr[a][b];
+                toti[a][b] = acci[a][b];
             }
+    }
+
+    // S operand of this lane: pixel (py, px) of column block cb; byte offsets
+    // from the start of the step, read by buffer loads from a scalar resource
+    // that ends with the last beam, so that beams past it read as zero and
+    // the loop holds no branch around a load (each would end in a wait for
+    // all loads in flight)
+    const size_t plane = (size_t)ns * ns;
+    const int plane_bytes = (int)(plane * sizeof(float2));
+    int voff[CB][4];
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb) {
+        const int py = (org.y + row0 + 2 * (CB * wave + cb) + (col >> 4)) & (ns - 1), px = (org.x + (col & 15)) & (ns - 1);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) voff[cb][j] = (py * ns + px) * (int)sizeof(float2) + (4 * half + j) * plane_bytes;
+    }
+    float2 raw[2][CB][4];
+    auto load_s = [&](int k, int h) {
+        const int b0 = min(k * KSTEP + h * SUB, n_beams);
+        const int64_t left = (int64_t)(n_beams - b0) * plane_bytes;
+        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<float2*>(job.S + (size_t)b0 * plane), (short)0,
+            (int)min(left, (int64_t)0x7fffffff), 0x00020000);
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                raw[h][cb][j] = __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(rs, voff[cb][j], 0, 0));
     };
-    // record chunks of the staged halves (the half index must be a
-    // compile-time constant: it selects registers)
-    auto stage_s = [&]() {
-        if constexpr (SH == 1) {
-            stage_s_half<NP, 0>(sv[0], Ss + sp * NCH, skey);
-            stage_s_half<NP, 1>(sv[HPT - 1], Ss + sp * NCH, skey);
-        } else if (sh0 == 0) {
-            stage_s_half<NP, 0>(sv[0], Ss + sp * NCH, skey);
+    // C staging.  NP <= 2: chunk (tid + j NT) of the K step's PC records;
+    // NP = 3: the 4 beams (tid % 4) of probe tid / 4, split when stored.
+    // Rows past np read probe 0's record; they are not stored.
+    constexpr int CW = NP == 3 ? 2 : NP, NCP = NP == 3 ? 1 : NP;
+    u32x4 creg[CW];
+    const u32x4* cptr[NCP];
+#pragma unroll
+    for (int j = 0; j < NCP; ++j) {
+        const int q = max(pidx[NP == 3 ? tid / 4 : (tid + j * NT) / NCH], 0);
+        const int off = NP == 3 ? (tid % 4) * 2 : (tid + j * NT) % NCH;
+        cptr[j] = static_cast<const u32x4*>(job.C) + (size_t)q * K * (NP == 3 ? 8 : NCH) + off;
+    }
+    auto load_c = [&](int k) {
+        const size_t at = (size_t)min(k, K - 1) * (NP == 3 ? 8 : NCH);
+#pragma unroll
+        for (int j = 0; j < CW; ++j) creg[j] = NP == 3 ? cptr[0][at + j] : cptr[NP == 3 ? 0 : j][at];
+    };
+    auto stage_c = [&](u32x4* dst) {
+        if constexpr (NP == 3) {
+            u32x4 ch[3];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                unsigned int w[3];
+                split_parts<3>(__uint_as_float(creg[j / 2][(j % 2) * 2]), __uint_as_float(creg[j / 2][(j % 2) * 2 + 1]), w);
+#pragma unroll
+                for (int part = 0; part < 3; ++part) ch[part][j] = w[part];
+            }
+#pragma unroll
+            for (int part = 0; part < 3; ++part) dst[(part * 4 + tid % 4) * LP + tid / 4] = ch[part];
         } else {
-            stage_s_half<NP, 1>(sv[0], Ss + sp * NCH, skey);
+#pragma unroll
+            for (int j = 0; j < CW; ++j) dst[((tid + j * NT) % NCH) * LP + (tid + j * NT) / NCH] = creg[j];
         }
     };
-#endif
-    load_s(0);
+    // B operands of the two steps of a K step: step s + 1 is converted while
+    // the products of step s run
+    u32x4 B[2][NP][CB];
+    auto convert_s = [&](int h) {
 #pragma unroll
-    for (int j = 0; j < CPT; ++j) creg[j] = cq >= 0 ? Cg[j] : zero;
-
-    const int col = lane & 15, g = lane >> 4;   // MFMA operand lane roles
-    const u32x4 sgn = u32x4{0x80008000u, 0x80008000u, 0x80008000u, 0x80008000u};
-    for (int k = 0; k < K; ++k) {
-        stage_s();
+        for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
-        for (int j = 0; j < CPT; ++j) Cl[crow * NCH + ((cc0 + j) ^ ckey)] = creg[j];
-        __syncthreads();
-        if (k + 1 < K) {
-            load_s(k + 1);
+            for (int j = 0; j < 4; ++j) {
+                unsigned int w[NP];
+                split_parts<NP>(raw[h][cb][j].x, raw[h][cb][j].y, w);
 #pragma unroll
-            for (int j = 0; j < CPT; ++j) creg[j] = cq >= 0 ? Cg[(size_t)(k + 1) * NCH + j] : zero;
-        }
-        // B operand of lane group g: chunk part*4 + g (re beams 0-7, 8-15, im beams 0-7, 8-15)
-        u32x4 Bop[NP][PB];
-#pragma unroll
-        for (int pb = 0; pb < PB; ++pb) {
-            const int pix = (PB * wave + pb) * TILE + col;
-            const int key = rec_key<NP>(pix);
-#pragma unroll
-            for (int part = 0; part < NP; ++part) Bop[part][pb] = Ss[pix * NCH + ((part * 4 + g) ^ key)];
-        }
-#pragma unroll
-        for (int qb = 0; qb < QB; ++qb) {
-            const int row = 16 * qb + col;
-            const int key = rec_key<NP>(row);
-            // A_r = [Cr | -Ci]: chunk part*4 + g, negated for g >= 2; A_i = [Ci | Cr]: chunk part*4 + (g ^ 2)
-            u32x4 Ar[NP], Ai[NP];
-#pragma unroll
-            for (int part = 0; part < NP; ++part) {
-                Ar[part] = Cl[row * NCH + ((part * 4 + g) ^ key)];
-                if (g >= 2) Ar[part] ^= sgn;
-                Ai[part] = Cl[row * NCH + ((part * 4 + (g ^ 2)) ^ key)];
+                for (int part = 0; part < NP; ++part) B[h][part][cb][j] = w[part];
             }
+    };
+    load_c(0);
+    load_s(0, 0);
+    load_s(0, 1);
+    stage_c(Cl[0]);
+    __syncthreads();
+    convert_s(0);
+    load_s(1, 0);
+
+    const bool two = np > 32;                     // the second row block holds probes
+    for (int k0 = 0; k0 < K; k0 += FLUSH<NP>) {
+        const int k1 = min(k0 + FLUSH<NP>, K);
+        for (int k = k0; k < k1; ++k) {
+            const u32x4* Ck = Cl[k & 1];
+            load_c(k + 1);
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int pb = 0; pb < PB; ++pb) {
-                accr[qb][pb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(Ar[0]), as_bf16x8(Bop[0][pb]),
-                                                                      accr[qb][pb], 0, 0, 0);
-                acci[qb][pb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(Ai[0]), as_bf16x8(Bop[0][pb]),
-                                                                      acci[qb][pb], 0, 0, 0);
-                if constexpr (NP == 2) {
-                    accr[qb][pb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(Ar[0]), as_bf16x8(Bop[1][pb]),
-                                                                          accr[qb][pb], 0, 0, 0);
-                    acci[qb][pb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(Ai[0]), as_bf16x8(Bop[1][pb]),
-                                                                          acci[qb][pb], 0, 0, 0);
-                    accr[qb][pb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(Ar[1]), as_bf16x8(Bop[0][pb]),
-                                                                          accr[qb][pb], 0, 0, 0);
-                    acci[qb][pb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(Ai[1]), as_bf16x8(Bop[0][pb]),
-                                                                          acci[qb][pb], 0, 0, 0);
+            for (int h = 0; h < 2; ++h) {
+                convert_s(1 - h);
+#pragma unroll
+                for (int rb = 0; rb < RB; ++rb) {
+                    if (rb > 0 && !two) break;
+                    u32x4 A[NP];
+#pragma unroll
+                    for (int part = 0; part < NP; ++part) A[part] = Ck[(part * 4 + 2 * h + half) * LP + 32 * rb + col];
+                    auto product = [&](f32x16 (&acc)[CB], int pa, int pb) {
+#pragma unroll
+                        for (int cb = 0; cb < CB; ++cb)
+                            acc[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(A[pa]), as_bf16x8(B[h][pb][cb]),
+                                                                              acc[cb], 0, 0, 0);
+                    };
+                    auto products = [&](f32x16 (&acc)[CB]) {
+                        if constexpr (NP == 3) {
+                            product(acc, 2, 0);
+                            product(acc, 0, 2);
+                            product(acc, 1, 1);
+                        }
+                        if constexpr (NP >= 2) {
+                            product(acc, 1, 0);
+                            product(acc, 0, 1);
+                        }
+                        product(acc, 0, 0);
+                    };
+#pragma unroll
+                    for (int part = 0; part < NP; ++part) A[part] ^= 0x80000000u;             // (Cr, -Ci)
+                    products(accr[rb]);
+#pragma unroll
+                    for (int part = 0; part < NP; ++part) {                                   // (Ci, Cr)
+                        A[part] ^= 0x80000000u;
+                        A[part] = (A[part] >> 16) | (A[part] << 16);
+                    }
+                    products(acci[rb]);
+                    if (rb == 0) {
+                        // the loads reuse the registers that the conversion
+                        // frees: it ends here (not sunk to where its results
+                        // are used), and the loads are not moved down
+#pragma unroll
+                        for (int part = 0; part < NP; ++part)
+#pragma unroll
+                            for (int cb = 0; cb < CB; ++cb) asm volatile("" : "+v"(B[1 - h][part][cb]));
+                        __builtin_amdgcn_sched_barrier(0);
+                        load_s(h == 0 ? k + 1 : k + 2, 1 - h);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
                 }
             }
+            stage_c(Cl[(k + 1) & 1]);
+            __syncthreads();
         }
-        __syncthreads();
+        if constexpr (NP == 3) {
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+                for (int cb = 0; cb < CB; ++cb) {
+                    totr[rb][cb] += accr[rb][cb];
+                    toti[rb][cb] += acci[rb][cb];
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) accr[rb][cb][r] = acci[rb][cb][r] = 0.f;
+                }
+        }
     }
-    // ---- epilogue: D row = probe 16 qb + 4 g + r, column = pixel
+    // ---- epilogue: D register r = probe row (r & 3) + 8 (r >> 2) + 4 half, column = pixel
 #pragma unroll
-    for (int qb = 0; qb < QB; ++qb)
+    for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int q = pidx[16 * qb + 4 * g + r];
+        for (int r = 0; r < 16; ++r) {
+            const int row = 32 * rb + (r & 3) + 8 * (r >> 2) + 4 * half;
+            const int q = pidx[row];
             if (q < 0) continue;
-            const int2 c0 = corner[q];
+            const int2 c0 = pcorner[row];
 #pragma unroll
-            for (int pb = 0; pb < PB; ++pb) {
-                const int py = (org.y + PB * wave + pb) & (ns - 1), px = (org.x + col) & (ns - 1);
+            for (int cb = 0; cb < CB; ++cb) {
+                const int py = org.y + row0 + 2 * (CB * wave + cb) + (col >> 4), px = org.x + (col & 15);
                 const int v = (py - c0.y) & (ns - 1);
                 const int u = (px - c0.x) & (ns - 1);
                 if (v < m && u < m) {
                     float2* w = win + (size_t)q * m * m + (size_t)v * m + u;
-                    float2 res = make_float2(accr[qb][pb][r], acci[qb][pb][r]);
+                    float2 res = NP == 3 ? make_float2(totr[rb][cb][r], toti[rb][cb][r]) : make_float2(accr[rb][cb][r], acci[rb][cb][r]);
                     if (job.accumulate) res = cadd(*w, res);
                     *w = res;
                 }
@@ -561,10 +449,8 @@ __global__ __launch_bounds__(mfmac::NT) __attribute__((amdgpu_waves_per_eu(2))) 
 }
 
 int contract_probe_chunk() { return mfmac::PC; }
-bool contract_reads_split_s() { return PRISM_CONTRACT_PRESPLIT != 0; }
 
 hipError_t launch_contract_batch(int precision, const ContractArgs* jobs, int n_jobs, hipStream_t st) {
-    const int pc = precision == 0 ? fp32c::PC : mfmac::PC;
     for (int j0 = 0; j0 < n_jobs; j0 += MAX_JOBS) {
         ContractBatch b{};
         b.n_jobs = n_jobs - j0 < MAX_JOBS ? n_jobs - j0 : MAX_JOBS;
@@ -584,8 +470,8 @@ hipError_t launch_contract_batch(int precision, const ContractArgs* jobs, int n_
             job.m = a.m;
             job.ksteps = ksteps_of(a.n_beams);
             job.accumulate = a.accumulate;
-            job.chunks = (a.max_per_tile + pc - 1) / pc;
-            if (job.chunks < 1) job.chunks = 1;
+            job.chunks = std::max(1, (a.max_per_tile + mfmac::PC - 1) / mfmac::PC) *
+                         (precision == 0 ? mfmac::SPLITS<3> : mfmac::SPLITS<2>);
             job.n_tiles = a.n_tiles;
             job.block0 = blocks;
             blocks += job.chunks * job.n_tiles;
@@ -594,12 +480,13 @@ hipError_t launch_contract_batch(int precision, const ContractArgs* jobs, int n_
         b.per_xcd = (blocks + 7) / 8;
         if (blocks == 0) continue;
         dim3 grid((unsigned)(8 * b.per_xcd));
+        auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(mfmac::NT), 0, st, b); };
         if (precision == 0)
-            hipLaunchKernelGGL(k_contract_fp32, grid, dim3(WG), 0, st, b);
+            launch(k_contract<3>);
         else if (precision == 1)
-            hipLaunchKernelGGL(k_contract_mfma<2>, grid, dim3(mfmac::NT), 0, st, b);
+            launch(k_contract<2>);
         else
-            hipLaunchKernelGGL(k_contract_mfma<1>, grid, dim3(mfmac::NT), 0, st, b);
+            launch(k_contract<1>);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
