@@ -704,14 +704,23 @@ constexpr int kMaxBuildStreams = 4;
 #ifndef PRISM_FORK_STAGE
 #define PRISM_FORK_STAGE 1
 #endif
-// 0: by grid size.  Four streams up to n = 1024 (1245 beams at 1024^2 on 1,
-// 2, 3 and 4 streams: 262.4, 253.9, 251.0 and 249.5 ms per build), one above
-// (1245 beams at 2048^2: 1.419, 1.410, 1.418 and 1.426 s, no gain beyond the
-// spread between runs).
+// 0: by size.  One stream above n = 1024 (1245 beams at 2048^2 on 1, 2, 3 and
+// 4: 1.419, 1.410, 1.418 and 1.426 s per build, no gain beyond the spread
+// between runs).  Up to 1024^2, by the pixels of a beam batch (beams x n^2),
+// as each further stream costs two launches per slice and shorter kernels, in
+// us per build on 1, 2 and 4 streams:
+//   21 beams at 256^2 (1.4 M)    339    455    765
+//   69 beams at 256^2 (4.5 M)    308    310    472
+//   69 beams at 512^2 (18 M)    1502   1374   1807
+//   305 beams at 256^2 (20 M)   1566   1408   1765
+//   1245 beams at 512^2 (326 M) 23359 22753  23269
+//   1245 beams at 1024^2 (1.3 G) 262.4, 253.9 and 249.5 ms
 std::atomic<int> g_build_streams{0};
-int build_streams_for(int n) {
+int build_streams_for(int n, int beams) {
     const int s = g_build_streams.load();
-    return s > 0 ? s : (n <= 1024 ? 4 : 1);
+    if (s > 0) return s;
+    const int64_t pixels = (int64_t)beams * n * n;
+    return n > 1024 || pixels < (int64_t)8 << 20 ? 1 : (pixels < (int64_t)700 << 20 ? 2 : 4);
 }
 std::mutex g_partner_mu;
 std::map<hipStream_t, std::vector<hipStream_t>> g_partner;
@@ -810,7 +819,7 @@ static int build_range(const prism_smatrix_desc* d, const float* V, void* S, int
         HIP_TRY(timed(PRISM_K_FINAL, q, [&] { return launch_smatrix_final(n, Wq, Sq, pd.tw_half, cnt, q); }));
         return PRISM_OK;
     };
-    int P = std::min(build_streams_for(n), NB);
+    int P = std::min(build_streams_for(n, NB), NB);
     hipStream_t q[kMaxBuildStreams] = {st};
     if (P > 1) {
         int got = 0;

@@ -22,6 +22,8 @@
 #include "fft.hpp"
 #include "kernels.hpp"
 
+#include <type_traits>
+
 namespace prism {
 
 constexpr int WG = 256;      // 4 wavefronts
@@ -54,7 +56,7 @@ constexpr int WG = 256;      // 4 wavefronts
 #define PRISM_PASSB_DEPTH 1      // columns prefetched ahead in registers (1 or 2)
 #endif
 #ifndef PRISM_PASSB_COLS
-#define PRISM_PASSB_COLS 8       // adjacent columns per transform group in pass B (pipelined loads)
+#define PRISM_PASSB_COLS 8       // most adjacent columns per transform group in pass B (pipelined loads)
 #endif
 
 // Non-temporal wave-buffer traffic, measured at n = 1024 (1245 beams): in the
@@ -103,7 +105,7 @@ __device__ __forceinline__ void wave_store(float4* p, float4 v) {
     else *p = v;
 }
 
-// Columns per pass-B transform group: pipelined when the column count allows.
+// Most columns per pass-B transform group: pipelined when the column count allows.
 template <int N, int MODE>
 struct PassBCols {
     static constexpr int CPB = 4 * (64 / Fft<N / 2>::LPT);
@@ -423,15 +425,9 @@ hipError_t launch_first_from_spectrum(int n, float2* W, const float2* R, const P
 template <int N>
 constexpr int pass_b_lds() { return (PRISM_PASSB_ILP ? 2 : 1) * 4 * (64 / Fft<N / 2>::LPT) * Fft<N / 2>::LDS; }
 
-// Workgroups of a column-pass launch over n_items items.
-template <int N, int MODE>
-constexpr int pass_b_blocks_per_item() {
-    constexpr int CPB = 4 * (64 / Fft<N / 2>::LPT) * PassBCols<N, MODE>::value;
-    return (N / 2 + CPB - 1) / CPB;
-}
-
-// One column-pass workgroup: logical block blk of a launch over n_items items.
-template <int N, int MODE>
+// One column-pass workgroup: logical block blk of a launch over n_items items,
+// NC adjacent columns per transform group.
+template <int N, int MODE, int NC>
 __device__ __forceinline__ void pass_b_block(float2* __restrict__ W, const PropTables& tb,
                                              const float2* __restrict__ aux, float* __restrict__ inten,
                                              const int* __restrict__ ky_max, const double2* __restrict__ probe_xy,
@@ -439,7 +435,6 @@ __device__ __forceinline__ void pass_b_block(float2* __restrict__ W, const PropT
     using F = Fft<N / 2>;
     constexpr int L = N / 2, E = F::E, LPT = F::LPT, G = 64 / LPT, CPB = 4 * G;
     constexpr int NB = PRISM_PASSB_ILP ? 2 : 1;
-    constexpr int NC = PassBCols<N, MODE>::value;   // adjacent columns per transform group
     float2* const xch = smem;
 
     const int item = blk % n_items;
@@ -569,12 +564,12 @@ __device__ __forceinline__ void pass_b_block(float2* __restrict__ W, const PropT
     }
 }
 
-template <int N, int MODE>
+template <int N, int MODE, int NC>
 __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(PRISM_PASSB_WPE))) void k_pass_b(
     float2* __restrict__ W, PropTables tb, const float2* __restrict__ aux, float* __restrict__ inten,
     const int* __restrict__ ky_max, const double2* __restrict__ probe_xy, double inv_L, float amp, int n_items) {
     __shared__ float2 smem[pass_b_lds<N>()];
-    pass_b_block<N, MODE>(W, tb, aux, inten, ky_max, probe_xy, inv_L, amp, n_items, blockIdx.x, smem);
+    pass_b_block<N, MODE, NC>(W, tb, aux, inten, ky_max, probe_xy, inv_L, amp, n_items, blockIdx.x, smem);
 }
 
 // Tile-staged column pass for interior and last slices (used from n = 2048,
@@ -690,7 +685,7 @@ __global__ __launch_bounds__(WG) void k_pass_b_tile(float2* __restrict__ W, Prop
 template <int N, int MODE>
 static hipError_t pass_b_nm(float2* W, const PropTables& tb, const float2* aux, float* inten, const int* ky_max,
                             const double2* xy, double inv_L, float amp, int n_items, hipStream_t st) {
-    constexpr int L = N / 2, LPT = Fft<L>::LPT, CPB = 4 * (64 / LPT) * PassBCols<N, MODE>::value;
+    constexpr int L = N / 2, LPT = Fft<L>::LPT, GROUPS = 4 * (64 / LPT), NC = PassBCols<N, MODE>::value;
     if constexpr (MODE != PASSB_INIT && PassBTile<N>::ok) {
         constexpr int TC = PassBTile<N>::TC;
         static_assert(L % TC == 0, "columns must split into whole tiles");
@@ -698,9 +693,26 @@ static hipError_t pass_b_nm(float2* W, const PropTables& tb, const float2* aux, 
         hipLaunchKernelGGL((k_pass_b_tile<N, MODE>), grid, dim3(WG), 0, st, W, tb, inten, n_items);
         return hipGetLastError();
     }
-    dim3 grid((unsigned)((size_t)n_items * ((L + CPB - 1) / CPB)));
-    hipLaunchKernelGGL((k_pass_b<N, MODE>), grid, dim3(WG), 0, st, W, tb, aux, inten, ky_max, xy, inv_L, amp,
-                       n_items);
+    auto launch = [&](auto nc) {
+        constexpr int CPB = GROUPS * decltype(nc)::value;
+        dim3 grid((unsigned)((size_t)n_items * ((L + CPB - 1) / CPB)));
+        hipLaunchKernelGGL((k_pass_b<N, MODE, decltype(nc)::value>), grid, dim3(WG), 0, st, W, tb, aux, inten, ky_max,
+                           xy, inv_L, amp, n_items);
+    };
+    // The most columns per group that leave two workgroups per CU: a group
+    // works its columns off one after the other, so in a small launch fewer
+    // CUs each take longer.  One slice of 69 beams at 256^2: 26 us with 8
+    // columns (17-69 workgroups), 6 us with 1; 152 beams at 512^2 (608
+    // workgroups) 5.64 ms per 20-slice build with 8, 5.78 ms with 4.
+    if constexpr (NC > 1) {
+        const int64_t one = (int64_t)n_items * (L / GROUPS);   // workgroups at one column per group
+        if (one >= 512 * NC) launch(std::integral_constant<int, NC>{});
+        else if (NC > 4 && one >= 512 * 4) launch(std::integral_constant<int, 4>{});
+        else if (NC > 2 && one >= 512 * 2) launch(std::integral_constant<int, 2>{});
+        else launch(std::integral_constant<int, 1>{});
+    } else {
+        launch(std::integral_constant<int, 1>{});
+    }
     return hipGetLastError();
 }
 
