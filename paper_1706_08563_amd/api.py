@@ -83,10 +83,15 @@ def prism_project_potential(pos, species_idx, species, grid: prism_grid, device=
     torch = _torch()
     pos = np.ascontiguousarray(pos, dtype=np.float64)
     n_atoms = len(pos)
-    atoms = (prism_atom * max(n_atoms, 1))()
-    for i in range(n_atoms):
-        atoms[i].x, atoms[i].y, atoms[i].z = float(pos[i, 0]), float(pos[i, 1]), float(pos[i, 2])
-        atoms[i].species = int(species_idx[i])
+    # prism_atom records: x, y, z, and species beside a zero pad in the last 8 bytes
+    rec = np.zeros((max(n_atoms, 1), 4), dtype=np.float64)
+    if n_atoms:
+        rec[:, :3] = pos[:, :3]
+        if not (isinstance(species_idx, np.ndarray) and species_idx.dtype.kind in "iu" and species_idx.ndim == 1
+                and len(species_idx) >= n_atoms):
+            species_idx = np.array([int(species_idx[i]) for i in range(n_atoms)])
+        rec.view(np.int32)[:, 6] = species_idx[:n_atoms]
+    atoms = rec.ctypes.data_as(ctypes.POINTER(prism_atom))
     sp = (prism_species * len(species))()
     for i, s in enumerate(species):
         sp[i].n_gauss = len(s.amp)

@@ -12,6 +12,7 @@
 #include <algorithm>
 #include <atomic>
 #include <map>
+#include <memory>
 #include <mutex>
 #include <cmath>
 #include <cstdarg>
@@ -218,12 +219,13 @@ void stage(std::vector<char>& blob, const void* dev_base, const T* dev_ptr, cons
     if (!v.empty()) std::memcpy(blob.data() + off, v.data(), v.size() * sizeof(T));
 }
 
-int upload(void* dev, const std::vector<char>& blob, hipStream_t st) {
-    if (blob.empty()) return PRISM_OK;
-    HIP_TRY(hipMemcpyAsync(dev, blob.data(), blob.size(), hipMemcpyHostToDevice, st));
+int upload(void* dev, const void* host, size_t bytes, hipStream_t st) {
+    if (!bytes) return PRISM_OK;
+    HIP_TRY(hipMemcpyAsync(dev, host, bytes, hipMemcpyHostToDevice, st));
     HIP_TRY(hipStreamSynchronize(st));
     return PRISM_OK;
 }
+int upload(void* dev, const std::vector<char>& blob, hipStream_t st) { return upload(dev, blob.data(), blob.size(), st); }
 
 int check_grid(const prism_grid* g) {
     if (!g) return fail(PRISM_E_INVAL, "grid is NULL");
@@ -565,11 +567,12 @@ int prism_detector_default_bins(const prism_grid* grid, double E0, double dalpha
 }
 
 // ------------------------------------------------------------ potential --
+constexpr int kMaxCells = 8192;   // (slice, cell) lists of the potential
 int prism_project_potential_workspace(int64_t n_atoms, size_t* bytes) {
     if (!bytes || n_atoms < 0) return fail(PRISM_E_INVAL, "invalid argument");
     Carve c(nullptr);
     c.take<PotAtom>((size_t)std::max<int64_t>(n_atoms, 1));
-    c.take<int>(8193);
+    c.take<int>(kMaxCells + 1);
     c.take<PotSpecies>(256);
     *bytes = c.off + 256;
     return PRISM_OK;
@@ -581,7 +584,7 @@ int prism_project_potential(const prism_atom* atoms, int64_t n_atoms, const pris
     if (rc) return rc;
     if (!V || (n_atoms > 0 && !atoms) || !species || n_species <= 0 || n_species > 256 || n_atoms < 0)
         return fail(PRISM_E_INVAL, "potential: invalid argument");
-    if (grid->n_slices > 8192) return fail(PRISM_E_UNSUPPORTED, "potential: more than 8192 slices");
+    if (grid->n_slices > kMaxCells) return fail(PRISM_E_UNSUPPORTED, "potential: more than 8192 slices");
     size_t need = 0;
     prism_project_potential_workspace(n_atoms, &need);
     if (!ws || ws_bytes < need) return fail(PRISM_E_WORKSPACE, "potential: workspace %zu < %zu bytes", ws_bytes, need);
@@ -589,6 +592,7 @@ int prism_project_potential(const prism_atom* atoms, int64_t n_atoms, const pris
     const int S = grid->n_slices;
     std::vector<PotSpecies> sp(n_species);
     float rc_max = 0.f;
+    int max_gauss = 1;
     for (int i = 0; i < n_species; ++i) {
         const prism_species& s = species[i];
         if (s.n_gauss < 1 || s.n_gauss > 4) return fail(PRISM_E_INVAL, "species %d: n_gauss must be 1..4", i);
@@ -603,45 +607,53 @@ int prism_project_potential(const prism_atom* atoms, int64_t n_atoms, const pris
         double rcut = 6.0 * wmax;
         if (!(2.0 * rcut < L)) return fail(PRISM_E_INVAL, "species %d: cutoff 6*max(width) must be below L/2", i);
         p.n_gauss = s.n_gauss;
+        max_gauss = std::max(max_gauss, p.n_gauss);
         p.rc = (float)rcut;
         p.rc2 = (float)(rcut * rcut);
         rc_max = std::max(rc_max, p.rc);
         sp[i] = p;
     }
-    // atoms sorted (stably) by slice
-    std::vector<int> slice_of(n_atoms);
-    std::vector<int> start(S + 1, 0);
+    // atoms sorted (stably) by slice and cell: as many cells per axis as the
+    // lists allow, but none much smaller than a tile's reach
+    const int nc = std::max(1, std::min({(int)std::sqrt((double)(kMaxCells / S)), (int)(L / std::max(rc_max, 1.f)), 64}));
+    auto wrapped = [&](double x) {
+        if (x >= 0 && x < L) return x;
+        x = std::fmod(x, L);
+        return x < 0 ? x + L : x;
+    };
+    auto cell = [&](double x) { return std::min(nc - 1, (int)(x * nc / L)); };
+    std::vector<int> key(n_atoms), start((size_t)S * nc * nc + 1, 0);
     for (int64_t a = 0; a < n_atoms; ++a) {
         const prism_atom& at = atoms[a];
         if (at.species < 0 || at.species >= n_species) return fail(PRISM_E_INVAL, "atom %lld: bad species", (long long)a);
         if (!std::isfinite(at.x) || !std::isfinite(at.y) || !std::isfinite(at.z))
             return fail(PRISM_E_INVAL, "atom %lld: non-finite position", (long long)a);
-        double s = std::floor(at.z / grid->dz);
-        int si = s < 0 ? 0 : (s > S - 1 ? S - 1 : (int)s);
-        slice_of[a] = si;
-        start[si + 1]++;
+        const double s = std::floor(at.z / grid->dz);
+        const int si = s < 0 ? 0 : (s > S - 1 ? S - 1 : (int)s);
+        key[a] = (si * nc + cell(wrapped(at.y))) * nc + cell(wrapped(at.x));
+        start[key[a] + 1]++;
     }
-    for (int s = 0; s < S; ++s) start[s + 1] += start[s];
-    std::vector<PotAtom> sorted(std::max<int64_t>(n_atoms, 1));
-    std::vector<int> fill(start.begin(), start.end() - 1);
-    for (int64_t a = 0; a < n_atoms; ++a) {
-        double x = std::fmod(atoms[a].x, L), y = std::fmod(atoms[a].y, L);
-        if (x < 0) x += L;
-        if (y < 0) y += L;
-        sorted[fill[slice_of[a]]++] = PotAtom{x, y, slice_of[a], atoms[a].species};
-    }
+    for (size_t k = 1; k < start.size(); ++k) start[k] += start[k - 1];
     Carve c(ws);
-    PotAtom* d_atoms = c.take<PotAtom>(sorted.size());
-    int* d_start = c.take<int>(8193);
+    PotAtom* d_atoms = c.take<PotAtom>(std::max<int64_t>(n_atoms, 1));
+    int* d_start = c.take<int>(kMaxCells + 1);
     PotSpecies* d_sp = c.take<PotSpecies>(256);
-    std::vector<char> blob;
-    stage(blob, ws, d_atoms, sorted);
-    stage(blob, ws, d_start, start);
-    stage(blob, ws, d_sp, sp);
+    // one buffer laid out as the workspace, written in place
+    const size_t bytes = reinterpret_cast<char*>(d_sp + n_species) - static_cast<char*>(ws);
+    std::unique_ptr<char[]> blob(new (std::nothrow) char[bytes]);
+    if (!blob) return fail(PRISM_E_NOMEM, "potential: %zu bytes of host memory", bytes);
+    auto host = [&](const void* dev) { return blob.get() + (static_cast<const char*>(dev) - static_cast<char*>(ws)); };
+    std::memcpy(host(d_start), start.data(), start.size() * sizeof(int));
+    std::memcpy(host(d_sp), sp.data(), sp.size() * sizeof(PotSpecies));
+    PotAtom* sorted = reinterpret_cast<PotAtom*>(host(d_atoms));
+    for (int64_t a = 0; a < n_atoms; ++a)
+        sorted[start[key[a]]++] = PotAtom{wrapped(atoms[a].x), wrapped(atoms[a].y), atoms[a].species, 0};
     hipStream_t st = as_stream(stream);
-    rc = upload(ws, blob, st);
+    rc = upload(ws, blob.get(), bytes, st);
     if (rc) return rc;
-    HIP_TRY(timed(PRISM_K_POTENTIAL, st, [&] { return launch_potential(V, grid->n, S, L, d_atoms, d_start, d_sp, rc_max, st); }));
+    HIP_TRY(timed(PRISM_K_POTENTIAL, st, [&] {
+        return launch_potential(V, grid->n, S, L, nc, d_atoms, d_start, d_sp, max_gauss, rc_max, st);
+    }));
     return PRISM_OK;
 }
 

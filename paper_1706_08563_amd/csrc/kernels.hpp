@@ -53,10 +53,14 @@ hipError_t launch_smatrix_final(int n, const float2* half, float2* S, const floa
                                 hipStream_t st);
 
 // ---- projected potential --------------------------------------------------
-struct PotAtom { double x, y; int32_t slice, species; };
+// Atoms sorted by (slice, cell of a cells x cells grid over the wrapped
+// positions, row-major); cell_start[(slice cells + cy) cells + cx] is a cell's
+// first atom, with one more entry for the end.
+struct PotAtom { double x, y; int32_t species, pad; };
 struct PotSpecies { float amp_n[4]; float inv2w2[4]; float rc2; int n_gauss; float rc; int pad; };
-hipError_t launch_potential(float* V, int n, int n_slices, double L, const PotAtom* atoms,
-                            const int* slice_start, const PotSpecies* species, float rc_max, hipStream_t st);
+hipError_t launch_potential(float* V, int n, int n_slices, double L, int cells, const PotAtom* atoms,
+                            const int* cell_start, const PotSpecies* species, int max_gauss, float rc_max,
+                            hipStream_t st);
 
 // ---- probe synthesis ----------------------------------------------------------
 // A K step of the contraction is 16 beams.
