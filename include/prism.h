@@ -120,7 +120,7 @@ typedef struct prism_probe_plan {
     size_t plan_bytes;       /* device bytes of the plan tables */
     size_t ws_bytes;         /* workspace of prism_probe_outputs for all probes at once */
     double C1, C3;           /* aberrations the plan was made with */
-    size_t off[10];          /* internal: offsets of the tables inside the plan buffer */
+    size_t off[10];          /* internal: offsets and sizes of the tables inside the plan buffer */
 } prism_probe_plan;
 
 /* ---- grid ---------------------------------------------------------------- */

@@ -249,7 +249,35 @@ struct ProbeHost {
     std::vector<float2> tw_m;
     std::vector<int2> beams;
     std::vector<float2> aberr;      // per beam, empty when there are no aberrations
+    // two-stage sum, empty when the probes share too few x positions
+    std::vector<double2> col_xy;    // (x, 0) of each scan column, by window corner
+    std::vector<int> col_corner, col_start, entry_corner, entry_probe;
+    int max_cols = 0, max_probes = 0, tile_width = 0;
 };
+
+// Beams of each ky of beam_list, and the K steps of 16 beams they make.
+struct BeamRows {
+    std::vector<int4> rows;         // first beam, beams, first K step, ky
+    std::vector<int4> steps;        // first beam, beams, ky row, last of its ky
+    int most = 0;                   // most beams of one ky
+};
+BeamRows beam_rows(double L, double lam, double alpha_max, int f) {
+    BeamRows r;
+    int ky = 0, b0 = 0;
+    while (angle_of(lam, 0, ky + f, L) <= alpha_max) ky += f;
+    for (ky = -ky; angle_of(lam, 0, ky, L) <= alpha_max; ky += f) {
+        int kx = 0;
+        while (angle_of(lam, kx + f, ky, L) <= alpha_max) kx += f;
+        const int nb = 2 * (kx / f) + 1;
+        const int row = (int)r.rows.size();
+        r.rows.push_back(make_int4(b0, nb, (int)r.steps.size(), ky));
+        for (int k = 0; k < nb; k += KSTEP)
+            r.steps.push_back(make_int4(b0 + k, std::min(KSTEP, nb - k), row, k + KSTEP >= nb));
+        r.most = std::max(r.most, nb);
+        b0 += nb;
+    }
+    return r;
+}
 
 // Detector tables: pixel indices grouped by bin (bins[i] in [-1, n_bins),
 // -1 = no bin), ascending pixel index inside a bin; start[b] .. start[b+1]
@@ -337,6 +365,85 @@ static uint32_t morton(uint32_t ty, uint32_t tx) {
     uint32_t r = 0;
     for (int b = 0; b < 16; ++b) r |= ((tx >> b) & 1u) << (2 * b) | ((ty >> b) & 1u) << (2 * b + 1);
     return r;
+}
+
+// Most of the sorted corners in any cyclic run of `len` pixels (an upper
+// bound on the windows over a tile).
+static int most_in_run(const int* c, int n, int len, int ns) {
+    if (len >= ns) return n;
+    int most = 0;
+    for (int a = 0, b = 0; a < n; ++a) {            // corners c[a] .. c[b - 1] (cyclic) within len
+        b = std::max(b, a);
+        while (b < a + n && ((c[b % n] - c[a]) & (ns - 1)) < len && (b < n || c[b % n] < c[a])) ++b;
+        most = std::max(most, b - a);
+    }
+    return most;
+}
+
+// The probes grouped by their x ("scan columns"): columns sorted by window
+// corner, each one's probes by corner, when there are at least MIN_PER_COLUMN
+// probes per column.
+constexpr int MIN_PER_COLUMN = 8;
+static void scan_columns(const double* xy, int64_t n_probes, int ns, int M, ProbeHost& h) {
+    const int64_t most = n_probes / MIN_PER_COLUMN;
+    if (most < 1) return;
+    size_t size = 64;
+    while ((int64_t)size < 4 * most) size *= 2;
+    std::vector<int> slot(size, -1), column(n_probes), head;   // open addressing on the bits of x
+    for (int64_t p = 0; p < n_probes; ++p) {
+        uint64_t bits;
+        std::memcpy(&bits, &xy[2 * p], sizeof bits);
+        size_t at = (size_t)((bits * 0x9E3779B97F4A7C15ull) >> 20) & (size - 1);
+        while (slot[at] >= 0 && std::memcmp(&xy[2 * head[slot[at]]], &bits, sizeof bits) != 0) at = (at + 1) & (size - 1);
+        if (slot[at] < 0) {
+            if ((int64_t)head.size() == most) return;
+            slot[at] = (int)head.size();
+            head.push_back((int)p);
+        }
+        column[p] = slot[at];
+    }
+    const int G = (int)head.size();
+    std::vector<int> order(G), rank(G);
+    for (int g = 0; g < G; ++g) order[g] = g;
+    std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return h.corner[head[a]].x < h.corner[head[b]].x; });
+    h.col_xy.resize(G);
+    h.col_corner.resize(G);
+    for (int g = 0; g < G; ++g) {
+        rank[order[g]] = g;
+        h.col_xy[g] = make_double2(xy[2 * head[order[g]]], 0.0);
+        h.col_corner[g] = h.corner[head[order[g]]].x;
+    }
+    // probes by corner y (counting sort), then into their columns in that order
+    std::vector<int> by_y(ns + 1, 0), probe(n_probes);
+    for (int64_t p = 0; p < n_probes; ++p) by_y[h.corner[p].y + 1]++;
+    for (int y = 0; y < ns; ++y) by_y[y + 1] += by_y[y];
+    for (int64_t p = 0; p < n_probes; ++p) probe[by_y[h.corner[p].y]++] = (int)p;
+    h.col_start.assign(G + 1, 0);
+    for (int64_t p = 0; p < n_probes; ++p) h.col_start[rank[column[p]] + 1]++;
+    for (int g = 0; g < G; ++g) h.col_start[g + 1] += h.col_start[g];
+    h.entry_corner.resize(n_probes);
+    h.entry_probe.resize(n_probes);
+    std::vector<int> fill(h.col_start.begin(), h.col_start.end() - 1);
+    for (int64_t i = 0; i < n_probes; ++i) {
+        const int e = fill[rank[column[probe[i]]]]++;
+        h.entry_probe[e] = probe[i];
+        h.entry_corner[e] = h.corner[probe[i]].y;
+    }
+    // the 128-pixel tile of the sum over kx: the fewest 32-column row blocks
+    // (products), then the widest (its rows of T are the longest runs to write)
+    int blocks = 0;
+    for (int w = 16; w <= std::min(128, ns); w *= 2) {
+        const int cols = most_in_run(h.col_corner.data(), G, M + w - 1, ns), nb = (cols + 31) / 32;
+        if (blocks && nb > blocks) break;
+        blocks = nb;
+        h.max_cols = cols;
+        h.tile_width = w;
+    }
+    h.max_probes = 0;
+    for (int g = 0; g < G; ++g)
+        h.max_probes = std::max(h.max_probes, most_in_run(h.entry_corner.data() + h.col_start[g],
+                                                          h.col_start[g + 1] - h.col_start[g],
+                                                          M + 128 / std::min(M, 128) - 1, ns));
 }
 
 int probe_host(const prism_smatrix_desc* d, const double* xy, int64_t n_probes, double dalpha, int n_bins,
@@ -442,6 +549,7 @@ int probe_host(const prism_smatrix_desc* d, const double* xy, int64_t n_probes, 
     } else {
         fill_phases(0, nph);
     }
+    scan_columns(xy, n_probes, ns, M, h);
     bin_tables(d->lambda, L / d->f, d->alpha_aa, dalpha, n_bins, M, dmap, h.perm, h.bin_start);
     h.tw_m = twiddle_table(M);
     h.beams = beam_list(n, L, d->lambda, d->alpha_max, d->f);
@@ -477,6 +585,40 @@ SynthJobDev synth_job_carve(const prism_smatrix_desc* d, const prism_probe_plan*
 // S-matrix with its beams padded to whole K steps.
 char* s_scratch_carve(const prism_smatrix_desc* d, int n_beams, Carve& c) {
     return c.take<char>((size_t)d->ns * d->ns * ksteps_of(n_beams) * KSTEP * sizeof(float2));
+}
+
+// Tables of the two-stage sum inside the plan buffer, after the others.  The
+// plan's off[0] (the positions start the buffer) holds the counts the launches
+// need: scan columns (0: none), log2 of the tile width, max_cols and max_probes
+// in 28, 4, 16 and 16 bits.
+struct ColumnTables {
+    int n_cols, tile_width, max_cols, max_probes;
+    size_t col_xy, col_corner, col_start, entry_corner, entry_probe, rows, steps, end;
+};
+uint64_t pack_columns(const ProbeHost& h) {
+    const uint64_t g = h.col_xy.size();
+    if (g == 0 || g >= 1u << 28 || h.max_cols > 0xffff || h.max_probes > 0xffff) return 0;
+    return g | (uint64_t)__builtin_ctz(h.tile_width) << 28 | (uint64_t)h.max_cols << 32 | (uint64_t)h.max_probes << 48;
+}
+ColumnTables column_tables(const prism_probe_plan* plan, size_t n_rows, size_t n_steps) {
+    ColumnTables t{};
+    const uint64_t packed = plan->off[0];
+    t.n_cols = (int)(packed & 0xfffffffu);
+    t.tile_width = 1 << (packed >> 28 & 15);
+    t.max_cols = (int)(packed >> 32 & 0xffff);
+    t.max_probes = (int)(packed >> 48);
+    Carve c(nullptr);
+    c.off = plan->off[9] + std::max<size_t>(plan->n_tiles, 1) * sizeof(int2);
+    const size_t G = t.n_cols, P = (size_t)plan->n_probes;
+    t.col_xy = (size_t)c.take<double2>(G);
+    t.col_corner = (size_t)c.take<int>(G);
+    t.col_start = (size_t)c.take<int>(G + 1);
+    t.entry_corner = (size_t)c.take<int>(P);
+    t.entry_probe = (size_t)c.take<int>(P);
+    t.rows = (size_t)c.take<int4>(n_rows);
+    t.steps = (size_t)c.take<int4>(n_steps);
+    t.end = c.off;
+    return t;
 }
 
 // Consistency of a descriptor filled by prism_smatrix_plan (without recounting
@@ -976,7 +1118,8 @@ static int probe_plan_make(const prism_smatrix_desc* d, const double* probe_xy, 
     p.C3 = C3;
     Carve c(nullptr);
     const size_t P = (size_t)std::max<int64_t>(n_probes, 1);
-    p.off[0] = (size_t)c.take<double2>(P);
+    c.take<double2>(P);                              // positions, at offset 0
+    p.off[0] = (size_t)pack_columns(h);
     p.off[1] = (size_t)c.take<int2>(P);
     p.off[2] = (size_t)c.take<int>(h.tile_start.size());
     p.off[3] = (size_t)c.take<int>(std::max<size_t>(h.tile_probes.size(), 1));
@@ -986,6 +1129,10 @@ static int probe_plan_make(const prism_smatrix_desc* d, const double* probe_xy, 
     p.off[7] = (size_t)c.take<int2>(h.beams.size());
     p.off[8] = h.aberr.empty() ? 0 : (size_t)c.take<float2>(h.aberr.size());
     p.off[9] = (size_t)c.take<int2>(std::max<size_t>(h.tile_origin.size(), 1));
+    if (p.off[0]) {
+        const BeamRows br = beam_rows(d->grid.cell[0], d->lambda, d->alpha_max, d->f);
+        c.off = column_tables(&p, br.rows.size(), br.steps.size()).end;
+    }
     p.plan_bytes = c.off + 256;
     Carve w(nullptr);
     synth_job_carve(d, &p, w);
@@ -1035,13 +1182,13 @@ static int probe_plan_put(const prism_smatrix_desc* d, const double* probe_xy, c
     const ProbeHost& h = *hp;
     // every size the kernels and the workspace depend on must be the plan's
     if ((int64_t)h.tile_probes.size() != plan->n_entries || (int)h.perm.size() != plan->n_binned ||
-        maxpt != plan->max_per_tile || (int64_t)h.tile_start.size() - 1 != plan->n_tiles)
+        maxpt != plan->max_per_tile || (int64_t)h.tile_start.size() - 1 != plan->n_tiles || pack_columns(h) != plan->off[0])
         return fail(PRISM_E_INVAL, "probe plan upload: plan does not match these probes");
     std::vector<char> blob(plan->plan_bytes, 0);
     auto put = [&](size_t off, const void* src, size_t bytes) {
         if (bytes) std::memcpy(blob.data() + off, src, bytes);
     };
-    put(plan->off[0], h.xy.data(), h.xy.size() * sizeof(double2));
+    put(0, h.xy.data(), h.xy.size() * sizeof(double2));
     put(plan->off[1], h.corner.data(), h.corner.size() * sizeof(int2));
     put(plan->off[2], h.tile_start.data(), h.tile_start.size() * sizeof(int));
     put(plan->off[3], h.tile_probes.data(), h.tile_probes.size() * sizeof(int));
@@ -1051,6 +1198,17 @@ static int probe_plan_put(const prism_smatrix_desc* d, const double* probe_xy, c
     put(plan->off[7], h.beams.data(), h.beams.size() * sizeof(int2));
     if (!h.aberr.empty()) put(plan->off[8], h.aberr.data(), h.aberr.size() * sizeof(float2));
     put(plan->off[9], h.tile_origin.data(), h.tile_origin.size() * sizeof(int2));
+    if (plan->off[0]) {
+        const BeamRows br = beam_rows(d->grid.cell[0], d->lambda, d->alpha_max, d->f);
+        const ColumnTables t = column_tables(plan, br.rows.size(), br.steps.size());
+        put(t.col_xy, h.col_xy.data(), h.col_xy.size() * sizeof(double2));
+        put(t.col_corner, h.col_corner.data(), h.col_corner.size() * sizeof(int));
+        put(t.col_start, h.col_start.data(), h.col_start.size() * sizeof(int));
+        put(t.entry_corner, h.entry_corner.data(), h.entry_corner.size() * sizeof(int));
+        put(t.entry_probe, h.entry_probe.data(), h.entry_probe.size() * sizeof(int));
+        put(t.rows, br.rows.data(), br.rows.size() * sizeof(int4));
+        put(t.steps, br.steps.data(), br.steps.size() * sizeof(int4));
+    }
     return upload(plan_dev, blob, as_stream(stream));
 }
 
@@ -1095,6 +1253,59 @@ static int synth_validate(const prism_probe_job* jobs, int n_jobs, int precision
     return PRISM_OK;
 }
 
+inline size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
+
+// The two-stage sum's arguments for a job, when it takes that route.
+static bool two_stage_args(const prism_smatrix_desc* d, const prism_probe_plan* plan, const char* pb, int precision,
+                           TwoStageArgs& t) {
+    if (!plan->off[0] || precision == PRISM_BF16) return false;
+    const BeamRows br = beam_rows(d->grid.cell[0], d->lambda, d->alpha_max, d->f);
+    if (br.rows.back().x + br.rows.back().y != d->n_beams) return false;
+    const ColumnTables c = column_tables(plan, br.rows.size(), br.steps.size());
+    t = TwoStageArgs{};
+    t.n_cols = c.n_cols;
+    t.tile_width = c.tile_width;
+    t.max_cols = c.max_cols;
+    t.max_probes = c.max_probes;
+    t.col_steps = (int)br.steps.size();
+    t.n_rows = (int)br.rows.size();
+    t.max_row_beams = br.most;
+    t.n_probes = (int)plan->n_probes;
+    t.ns = d->ns;
+    t.m = d->m_win;
+    // both operands within the C operand's part of the workspace, a column
+    // of T within the S-matrix's
+    Carve s(nullptr);
+    s_scratch_carve(d, d->n_beams, s);
+    t.T_bytes = s.off;
+    if (align256(two_stage_cx_bytes(t.n_cols, t.col_steps)) + two_stage_cy_bytes(t.n_probes, t.n_rows) >
+            c_operand_bytes(t.n_probes, d->n_beams) ||
+        two_stage_column_bytes(t.n_rows, t.ns, t.m) > t.T_bytes)
+        return false;
+    // Time of the one-stage sum by its products, at what it reaches, against
+    // that of the two stages by their memory traffic (S read, T written and
+    // read) and two more launches.  Measured calls, one and two stages (FP32;
+    // split BF16), in us:
+    //   256 probes, 69 beams, 64^2 windows at 256^2      47, 61
+    //   400 probes, 305 beams, 64^2 windows at 512^2     84, 130;   62, 122
+    //   144 probes, 1245 beams, 128^2 windows at 512^2   253, 274;  161, 255
+    //   900 probes, 1245 beams, 128^2 windows at 1024^2  1502, 1067;  917, 1005
+    //   16,384 probes, 305 beams, 64^2 windows at 256^2  1669, 778;  1050, 770
+    //   16,384 probes, 1245 beams, 128^2 at 1024^2       (split) 8100, 3650
+    const double s_bytes = (double)d->smatrix_bytes, t_bytes = (double)t.n_cols * two_stage_column_bytes(t.n_rows, t.ns, t.m);
+    const double one = (double)plan->n_entries * 256 * 8 * d->n_beams / (precision == PRISM_FP32 ? 130e12 : 230e12);
+    const double two = 20e-6 + (s_bytes + 2 * t_bytes) / 4e12;
+    if (one < 1.15 * two) return false;
+    t.col_xy = reinterpret_cast<const double2*>(pb + c.col_xy);
+    t.col_corner = reinterpret_cast<const int*>(pb + c.col_corner);
+    t.col_start = reinterpret_cast<const int*>(pb + c.col_start);
+    t.entry_corner = reinterpret_cast<const int*>(pb + c.entry_corner);
+    t.entry_probe = reinterpret_cast<const int*>(pb + c.entry_probe);
+    t.rows = reinterpret_cast<const int4*>(pb + c.rows);
+    t.steps = reinterpret_cast<const int4*>(pb + c.steps);
+    return true;
+}
+
 // Probe synthesis for several (S-matrix, probe plan) jobs on one stream:
 // coefficients per job, one contraction launch for all jobs, one window launch
 // per window side.
@@ -1104,6 +1315,12 @@ static int synth_run(const prism_probe_job* jobs, int n_jobs, int precision, voi
     Carve c(ws);
     std::vector<SynthJobDev> jd(n_jobs);
     for (int k = 0; k < n_jobs; ++k) jd[k] = synth_job_carve(jobs[k].desc, jobs[k].plan, c);
+    std::vector<float2*> scratch(n_jobs);
+    for (int k = 0; k < n_jobs; ++k) {
+        const int j = first_with_same_s(jobs, k);
+        scratch[k] = j < k ? scratch[j]
+                           : reinterpret_cast<float2*>(s_scratch_carve(jobs[k].desc, jobs[k].desc->n_beams, c));
+    }
     for (int k = 0; k < n_jobs; ++k) {
         const prism_probe_job& jb = jobs[k];
         const prism_smatrix_desc* d = jb.desc;
@@ -1111,7 +1328,7 @@ static int synth_run(const prism_probe_job* jobs, int n_jobs, int precision, voi
         const char* pb = static_cast<const char*>(jb.plan_dev);
         const int P = (int)plan->n_probes, B = d->n_beams, M = d->m_win;
         if (P == 0) continue;
-        auto xy = reinterpret_cast<const double2*>(pb + plan->off[0]);
+        auto xy = reinterpret_cast<const double2*>(pb);
         auto corner = reinterpret_cast<const int2*>(pb + plan->off[1]);
         auto tstart = reinterpret_cast<const int*>(pb + plan->off[2]);
         auto tprobes = reinterpret_cast<const int*>(pb + plan->off[3]);
@@ -1123,15 +1340,36 @@ static int synth_run(const prism_probe_job* jobs, int n_jobs, int precision, voi
         auto torigin = reinterpret_cast<const int2*>(pb + plan->off[9]);
         const double inv_L = 1.0 / d->grid.cell[0];
         const float amp = (float)(1.0 / std::sqrt((double)B));
+        int lg = 0;
+        while ((1 << lg) < M) ++lg;
+        wa[lg].push_back(WindowArgs{jd[k].win, jd[k].inten, jb.out, jb.diffraction, perm, bstart, tw_m, P,
+                                    plan->n_bins, jb.out_scale, jb.accumulate});
+        TwoStageArgs ts;
+        if (two_stage_args(d, plan, pb, precision, ts)) {
+            ts.S = static_cast<const float2*>(jb.S);
+            ts.T = scratch[k];
+            ts.win = jd[k].win;
+            ts.cx = jd[k].C;
+            ts.cy = static_cast<char*>(jd[k].C) + align256(two_stage_cx_bytes(ts.n_cols, ts.col_steps));
+            ts.beams = beams;
+            ts.aberr = aberr;
+            ts.xy = xy;
+            ts.inv_L = inv_L;
+            ts.amp = amp;
+            HIP_TRY(timed(PRISM_K_COEFFICIENTS, st, [&] { return launch_two_stage_operands(ts, st); }));
+            const int step = two_stage_columns(ts);
+            for (int q = 0; q < ts.n_cols; q += step) {
+                const int n = std::min(step, ts.n_cols - q);
+                HIP_TRY(timed(PRISM_K_CONTRACT, st, [&] { return launch_sum_kx(precision, ts, q, n, st); }));
+                HIP_TRY(timed(PRISM_K_CONTRACT, st, [&] { return launch_sum_ky(ts, q, n, st); }));
+            }
+            continue;
+        }
         HIP_TRY(timed(PRISM_K_COEFFICIENTS, st, [&] {
             return launch_coefficients(precision, jd[k].C, xy, beams, aberr, P, B, inv_L, amp, st);
         }));
         ca.push_back(ContractArgs{jd[k].C, static_cast<const float2*>(jb.S), jd[k].win, tstart, tprobes, torigin, corner, plan->n_tiles,
                                   plan->max_per_tile, B, d->ns, M});
-        int lg = 0;
-        while ((1 << lg) < M) ++lg;
-        wa[lg].push_back(WindowArgs{jd[k].win, jd[k].inten, jb.out, jb.diffraction, perm, bstart, tw_m, P,
-                                    plan->n_bins, jb.out_scale, jb.accumulate});
     }
     if (!ca.empty())
         HIP_TRY(timed(PRISM_K_CONTRACT, st, [&] { return launch_contract_batch(precision, ca.data(), (int)ca.size(), st); }));
@@ -1631,7 +1869,7 @@ static int synth_chunked(const prism_smatrix_desc* d, const void* S, const prism
     const char* pb = static_cast<const char*>(plan_dev);
     const int P = (int)plan->n_probes, B = d->n_beams, M = d->m_win;
     const size_t layer = (size_t)d->ns * d->ns;
-    auto xy = reinterpret_cast<const double2*>(pb + plan->off[0]);
+    auto xy = reinterpret_cast<const double2*>(pb);
     auto corner = reinterpret_cast<const int2*>(pb + plan->off[1]);
     auto tstart = reinterpret_cast<const int*>(pb + plan->off[2]);
     auto tprobes = reinterpret_cast<const int*>(pb + plan->off[3]);

@@ -93,6 +93,38 @@ int contract_probe_chunk();
 // All jobs in as few launches as possible (one per 24 jobs).
 hipError_t launch_contract_batch(int precision, const ContractArgs* jobs, int n_jobs, hipStream_t st);
 
+// The same windows by sums over kx, per distinct x of the probes ("scan
+// column"), then over ky (PRISM_FP32 and PRISM_SPLIT_BF16X3).
+struct TwoStageArgs {
+    const float2* S;
+    float2* T;                 // scratch of T_bytes, at least one column's
+    size_t T_bytes;
+    float2* win;
+    void *cx, *cy;             // C operands, two_stage_cx_bytes and two_stage_cy_bytes
+    const double2 *col_xy, *xy;   // (x, 0) of each column; probe positions
+    const int2* beams;
+    const float2* aberr;
+    const int4* steps;         // per K step of a column (beams of one ky): first beam, beams, ky row, last of its ky
+    const int4* rows;          // per ky: first beam, beams, first K step, ky
+    const int *col_corner, *col_start, *entry_corner, *entry_probe;   // see struct TwoStage
+    int n_cols, col_steps, n_probes, n_rows, ns, m;
+    int max_row_beams;         // most beams of one ky
+    int tile_width;            // of the first sum's 128-pixel tiles
+    int max_cols, max_probes;  // most columns over tile_width pixels; most probes of a column over the
+                               // rows of 128 window pixels
+    double inv_L;
+    float amp;
+};
+size_t two_stage_cx_bytes(int n_cols, int col_steps);
+size_t two_stage_cy_bytes(int64_t n_probes, int n_rows);
+size_t two_stage_column_bytes(int n_rows, int ns, int m);
+hipError_t launch_two_stage_operands(const TwoStageArgs& t, hipStream_t st);
+// Scan columns per pair of launches (whose T fits), and the two sums for
+// columns q0 .. q0 + n - 1.
+int two_stage_columns(const TwoStageArgs& t);
+hipError_t launch_sum_kx(int precision, const TwoStageArgs& t, int q0, int n, hipStream_t st);
+hipError_t launch_sum_ky(const TwoStageArgs& t, int q0, int n, hipStream_t st);
+
 // out[p][bin] = sum over the bin's pixels of |FFT_m(win[p])|^2 / m^4.  For
 // m > 128 the window is transformed in place and `inten` ([p][m*m] floats)
 // holds the intensities; for m <= 128 both stay untouched.

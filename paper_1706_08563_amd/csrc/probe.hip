@@ -158,10 +158,32 @@ __device__ __forceinline__ void split_parts(float re, float im, unsigned int (&w
     }
 }
 
-// C operands, thread = (probe, group of 4 beams): split records
-// [probe][K step][part][4-beam group] for NP = 1, 2, and the FP32 values
-// [probe][K step][16 beams] (the same bytes as NP = 2) for NP = 3, which the
-// contraction splits as it stages them.  Beams past the last are zero.
+// C operands, thread = (row, group of 4 beams): split records
+// [row][K step][part][4-beam group] for NP = 1, 2, and the FP32 values
+// [row][K step][16 beams] (the same bytes as NP = 2) for NP = 3, which the
+// contraction splits as it stages them.  Beams past the last are zero.  A row
+// is a probe, or a scan column of the two-stage sum.
+template <int NP> constexpr int REC = NP == 3 ? 8 : NP * 4;   // 16-byte words per record
+template <int NP>
+__device__ __forceinline__ void store_operand(u32x4* rec, int g, const float2 (&v)[4]) {
+    if constexpr (NP == 3) {
+        float4* dst = reinterpret_cast<float4*>(rec) + 2 * g;
+        dst[0] = make_float4(v[0].x, v[0].y, v[1].x, v[1].y);
+        dst[1] = make_float4(v[2].x, v[2].y, v[3].x, v[3].y);
+    } else {
+        u32x4 ch[NP];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            unsigned int w[NP];
+            split_parts<NP>(v[j].x, v[j].y, w);
+#pragma unroll
+            for (int part = 0; part < NP; ++part) ch[part][j] = w[part];
+        }
+#pragma unroll
+        for (int part = 0; part < NP; ++part) rec[part * 4 + g] = ch[part];
+    }
+}
+
 template <int NP>
 __global__ __launch_bounds__(WG) void k_coefficients(u32x4* __restrict__ C, const double2* __restrict__ xy,
                                                      const int2* __restrict__ beams,
@@ -177,23 +199,7 @@ __global__ __launch_bounds__(WG) void k_coefficients(u32x4* __restrict__ C, cons
             const int b = k * KSTEP + g * 4 + j;
             v[j] = b < n_beams ? coefficient(xyp, beams[b], aberr, b, inv_L, amp) : make_float2(0.f, 0.f);
         }
-        if constexpr (NP == 3) {
-            float4* dst = reinterpret_cast<float4*>(C) + i * 2;
-            dst[0] = make_float4(v[0].x, v[0].y, v[1].x, v[1].y);
-            dst[1] = make_float4(v[2].x, v[2].y, v[3].x, v[3].y);
-        } else {
-            u32x4 ch[NP];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                unsigned int w[NP];
-                split_parts<NP>(v[j].x, v[j].y, w);
-#pragma unroll
-                for (int part = 0; part < NP; ++part) ch[part][j] = w[part];
-            }
-            u32x4* rec = C + ((size_t)p * K + k) * NP * 4;
-#pragma unroll
-            for (int part = 0; part < NP; ++part) rec[part * 4 + g] = ch[part];
-        }
+        store_operand<NP>(C + (i >> 2) * REC<NP>, g, v);
     }
 }
 
@@ -218,103 +224,92 @@ hipError_t launch_coefficients(int precision, void* C, const double2* xy, const 
     return hipGetLastError();
 }
 
-template <int NP>
-__global__ __launch_bounds__(mfmac::NT) __attribute__((amdgpu_waves_per_eu(2))) void k_contract(ContractBatch batch) {
-    using namespace mfmac;
-    constexpr int CB = CBS<NP>;
-    constexpr int NCH = NP * 4;                   // 16-byte chunks per record
-    // probe stride of an LDS chunk row: odd (or = 2 mod 8 when 4 lanes write
-    // one probe) so that 8 lanes of a staging store hit distinct bank groups
-    constexpr int LP = NP == 3 ? PC + 2 : PC + 1;
-    __shared__ u32x4 Cl[2][NCH * LP];
-    __shared__ int pidx[PC];
-    __shared__ int2 pcorner[PC];
+// LDS of a contraction workgroup, C operand in NA parts.
+template <int NA>
+struct ContractLds {
+    static constexpr int NCH = NA * 4;            // 16-byte chunks of a K step's operand row
+    // row stride of a chunk: odd (or = 2 mod 8 when 4 lanes write one row) so
+    // that 8 lanes of a staging store hit distinct bank groups
+    static constexpr int LP = NA == 3 ? mfmac::PC + 2 : mfmac::PC + 1;
+    u32x4 C[2][NCH * LP];
+    int idx[mfmac::PC];                           // C operand of each row, or -1
+    int2 at[mfmac::PC];                           // window corner of each row
+};
+// Row (MFMA row: probe or scan column) of D register r of row block rb.
+__device__ __forceinline__ int sum_row(int rb, int r, int half) { return 32 * rb + (r & 3) + 8 * (r >> 2) + 4 * half; }
 
-    int tile, chunk;
-    ContractJob job;
-    if (!locate(batch, job, tile, chunk)) return;
-    const int row0 = 8 * CB * (chunk % SPLITS<NP>);   // first tile row of this workgroup
-    chunk /= SPLITS<NP>;
-    float2* __restrict__ win = job.win;
-    const int ns = job.ns, m = job.m, K = job.ksteps, n_beams = job.n_beams;
-    const int t0 = job.tile_start[tile], t1 = job.tile_start[tile + 1];
-    const int pc0 = t0 + chunk * PC;
-    if (pc0 >= t1) return;
-    const int np = min(PC, t1 - pc0);
-    const int2 org = job.tile_origin[tile];
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const int col = lane & 31, half = lane >> 5;
-    if (tid < PC) {
-        const int q = tid < np ? job.tile_probes[pc0 + tid] : -1;
-        pidx[tid] = q;
-        pcorner[tid] = q >= 0 ? job.corner[q] : make_int2(0, 0);
-    }
-    __syncthreads();
-
-    f32x16 accr[RB][CB], acci[RB][CB];
-#pragma unroll
-    for (int a = 0; a < RB; ++a)
-#pragma unroll
-        for (int b = 0; b < CB; ++b)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) accr[a][b][r] = acci[a][b][r] = 0.f;
-    f32x16 totr[RB][CB], toti[RB][CB];            // running totals (NP = 3)
-    if constexpr (NP == 3) {
-#pragma unroll
-        for (int a = 0; a < RB; ++a)
-#pragma unroll
-            for (int b = 0; b < CB; ++b) {
-                totr[a][b] = accr[a][b];
-                toti[a][b] = acci[a][b];
-            }
-    }
-
-    // S operand of this lane: pixel (py, px) of column block cb; byte offsets
-    // from the start of the step, read by buffer loads from a scalar resource
-    // that ends with the last beam, so that beams past it read as zero and
-    // the loop holds no branch around a load (each would end in a wait for
-    // all loads in flight)
-    const size_t plane = (size_t)ns * ns;
-    const int plane_bytes = (int)(plane * sizeof(float2));
+// Registers and steps of the pipelined product of C (NA parts, through LDS)
+// and S (NB parts, CB 32-pixel column blocks of the wave).
+template <int NA, int NB, int CB>
+struct BeamPipe {
+    static constexpr int NCH = NA * 4, LP = ContractLds<NA>::LP, NT = mfmac::NT;
+    static constexpr int CW = NA == 3 ? 2 : NA, NCP = NA == 3 ? 1 : NA;
     int voff[CB][4];
+    float2 raw[2][CB][4];                         // S of the two halves of a K step, in flight
+    u32x4 B[2][NB][CB];                           // the same converted
+    u32x4 creg[CW];
+    const u32x4* cptr[NCP];
+
+    // S operand of this lane: pixel pix[cb] of column block cb, beams 4 half
+    // .. 4 half + 3 of a step; byte offsets from the start of the step.
+    // C staging.  NA <= 2: chunk (tid + j NT) of a K step's PC records;
+    // NA = 3: the 4 beams (tid % 4) of row tid / 4, split when stored.
+    // Rows without an operand (idx < 0) read operand 0; nothing of them is stored.
+    __device__ __forceinline__ void init(const ContractLds<NA>& lds, const int (&pix)[CB], int plane_bytes,
+                                         const u32x4* C, int stride) {
+        const int tid = threadIdx.x, half = (tid & 63) >> 5;
 #pragma unroll
-    for (int cb = 0; cb < CB; ++cb) {
-        const int py = (org.y + row0 + 2 * (CB * wave + cb) + (col >> 4)) & (ns - 1), px = (org.x + (col & 15)) & (ns - 1);
+        for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) voff[cb][j] = (py * ns + px) * (int)sizeof(float2) + (4 * half + j) * plane_bytes;
+            for (int j = 0; j < 4; ++j) voff[cb][j] = pix[cb] * (int)sizeof(float2) + (4 * half + j) * plane_bytes;
+#pragma unroll
+        for (int j = 0; j < NCP; ++j) {
+            const int q = max(lds.idx[NA == 3 ? tid / 4 : (tid + j * NT) / NCH], 0);
+            const int off = NA == 3 ? (tid % 4) * 2 : (tid + j * NT) % NCH;
+            cptr[j] = C + (size_t)q * stride * REC<NA> + off;
+        }
     }
-    float2 raw[2][CB][4];
-    auto load_s = [&](int k, int h) {
-        const int b0 = min(k * KSTEP + h * SUB, n_beams);
-        const int64_t left = (int64_t)(n_beams - b0) * plane_bytes;
+    // Buffer loads from a scalar resource that ends with the last beam (left
+    // bytes from the start of the step), so that beams past it read as zero
+    // and the loop holds no branch around a load (each would end in a wait
+    // for all loads in flight).
+    __device__ __forceinline__ void load_s(int h, const float2* S, int64_t left) {
         const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<float2*>(job.S + (size_t)b0 * plane), (short)0,
-            (int)min(left, (int64_t)0x7fffffff), 0x00020000);
+            const_cast<float2*>(S), (short)0, (int)max((int64_t)0, min(left, (int64_t)0x7fffffff)), 0x00020000);
 #pragma unroll
         for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
             for (int j = 0; j < 4; ++j)
                 raw[h][cb][j] = __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(rs, voff[cb][j], 0, 0));
-    };
-    // C staging.  NP <= 2: chunk (tid + j NT) of the K step's PC records;
-    // NP = 3: the 4 beams (tid % 4) of probe tid / 4, split when stored.
-    // Rows past np read probe 0's record; they are not stored.
-    constexpr int CW = NP == 3 ? 2 : NP, NCP = NP == 3 ? 1 : NP;
-    u32x4 creg[CW];
-    const u32x4* cptr[NCP];
-#pragma unroll
-    for (int j = 0; j < NCP; ++j) {
-        const int q = max(pidx[NP == 3 ? tid / 4 : (tid + j * NT) / NCH], 0);
-        const int off = NP == 3 ? (tid % 4) * 2 : (tid + j * NT) % NCH;
-        cptr[j] = static_cast<const u32x4*>(job.C) + (size_t)q * K * (NP == 3 ? 8 : NCH) + off;
     }
-    auto load_c = [&](int k) {
-        const size_t at = (size_t)min(k, K - 1) * (NP == 3 ? 8 : NCH);
+    __device__ __forceinline__ void convert_s(int h) {
 #pragma unroll
-        for (int j = 0; j < CW; ++j) creg[j] = NP == 3 ? cptr[0][at + j] : cptr[NP == 3 ? 0 : j][at];
-    };
-    auto stage_c = [&](u32x4* dst) {
-        if constexpr (NP == 3) {
+        for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                unsigned int w[NB];
+                split_parts<NB>(raw[h][cb][j].x, raw[h][cb][j].y, w);
+#pragma unroll
+                for (int part = 0; part < NB; ++part) B[h][part][cb][j] = w[part];
+            }
+    }
+    // Ends the conversion of half h here (not sunk to where its results are
+    // used): the loads that follow reuse its registers and are not moved down.
+    __device__ __forceinline__ void pin(int h) {
+#pragma unroll
+        for (int part = 0; part < NB; ++part)
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb) asm volatile("" : "+v"(B[h][part][cb]));
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    __device__ __forceinline__ void load_c(int step) {
+        const size_t at = (size_t)step * REC<NA>;
+#pragma unroll
+        for (int j = 0; j < CW; ++j) creg[j] = NA == 3 ? cptr[0][at + j] : cptr[NA == 3 ? 0 : j][at];
+    }
+    __device__ __forceinline__ void stage_c(u32x4* dst) const {
+        const int tid = threadIdx.x;
+        if constexpr (NA == 3) {
             u32x4 ch[3];
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
@@ -329,118 +324,175 @@ __global__ __launch_bounds__(mfmac::NT) __attribute__((amdgpu_waves_per_eu(2))) 
 #pragma unroll
             for (int j = 0; j < CW; ++j) dst[((tid + j * NT) % NCH) * LP + (tid + j * NT) / NCH] = creg[j];
         }
-    };
-    // B operands of the two steps of a K step: step s + 1 is converted while
-    // the products of step s run
-    u32x4 B[2][NP][CB];
-    auto convert_s = [&](int h) {
+    }
+    // Products of half h of the K step staged in Ck with row block rb.
+    __device__ __forceinline__ void products(const u32x4* Ck, int h, int rb, f32x16 (&accr)[CB], f32x16 (&acci)[CB]) const {
+        const int lane = threadIdx.x & 63, col = lane & 31, half = lane >> 5;
+        u32x4 A[NA];
+#pragma unroll
+        for (int part = 0; part < NA; ++part) A[part] = Ck[(part * 4 + 2 * h + half) * LP + 32 * rb + col];
+        auto product = [&](f32x16 (&acc)[CB], int pa, int pb) {
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb)
+                acc[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(A[pa]), as_bf16x8(B[h][pb][cb]), acc[cb], 0, 0, 0);
+        };
+        auto all = [&](f32x16 (&acc)[CB]) {
+            if constexpr (NA == 3) product(acc, 2, 0);
+            if constexpr (NB == 3) {
+                product(acc, 0, 2);
+                product(acc, 1, 1);
+            }
+            if constexpr (NA >= 2) product(acc, 1, 0);
+            if constexpr (NB >= 2) product(acc, 0, 1);
+            product(acc, 0, 0);
+        };
+#pragma unroll
+        for (int part = 0; part < NA; ++part) A[part] ^= 0x80000000u;             // (Cr, -Ci)
+        all(accr);
+#pragma unroll
+        for (int part = 0; part < NA; ++part) {                                   // (Ci, Cr)
+            A[part] ^= 0x80000000u;
+            A[part] = (A[part] >> 16) | (A[part] << 16);
+        }
+        all(acci);
+    }
+};
+template <int RB, int CB>
+__device__ __forceinline__ void clear(f32x16 (&a)[RB][CB]) {
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
         for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                unsigned int w[NP];
-                split_parts<NP>(raw[h][cb][j].x, raw[h][cb][j].y, w);
-#pragma unroll
-                for (int part = 0; part < NP; ++part) B[h][part][cb][j] = w[part];
-            }
+            for (int r = 0; r < 16; ++r) a[rb][cb][r] = 0.f;
+}
+template <int CB>
+struct Sums {
+    f32x16 r[mfmac::RB][CB], i[mfmac::RB][CB];
+};
+
+// sum[row][pixel] = sum over the n_beams planes of S (plane elements apart)
+// of C[lds.idx[row]][beam] S[beam][pix]: one lane's pixels are pix[cb]; C rows
+// are `stride` records apart; `two`: the second row block holds rows; every
+// FLUSH K steps are summed by themselves.  Called by all threads of the
+// workgroup, lds.idx written and synchronised.
+template <int NP, int CB, int FLUSH>
+__device__ __forceinline__ void sum_beams(ContractLds<NP>& lds, const float2* __restrict__ S, size_t plane, int n_beams,
+                                          const int (&pix)[CB], const u32x4* __restrict__ C, int stride, bool two,
+                                          Sums<CB>& sum) {
+    using namespace mfmac;
+    const int K = (n_beams + KSTEP - 1) / KSTEP, plane_bytes = (int)(plane * sizeof(float2));
+    constexpr bool PARTS = FLUSH < 1 << 30;
+    f32x16 accr[RB][CB], acci[RB][CB];
+    clear(accr);
+    clear(acci);
+    if constexpr (PARTS) {
+        clear(sum.r);
+        clear(sum.i);
+    }
+    BeamPipe<NP, NP, CB> pipe;
+    pipe.init(lds, pix, plane_bytes, C, stride);
+    auto load_s = [&](int k, int h) {
+        const int b0 = min(k * KSTEP + h * SUB, n_beams);
+        pipe.load_s(h, S + (size_t)b0 * plane, (int64_t)(n_beams - b0) * plane_bytes);
     };
-    load_c(0);
+    pipe.load_c(0);
     load_s(0, 0);
     load_s(0, 1);
-    stage_c(Cl[0]);
+    pipe.stage_c(lds.C[0]);
     __syncthreads();
-    convert_s(0);
+    // step s + 1 is converted while the products of step s run
+    pipe.convert_s(0);
     load_s(1, 0);
-
-    const bool two = np > 32;                     // the second row block holds probes
-    for (int k0 = 0; k0 < K; k0 += FLUSH<NP>) {
-        const int k1 = min(k0 + FLUSH<NP>, K);
+    for (int k0 = 0; k0 < K; k0 += FLUSH) {
+        const int k1 = min(k0 + FLUSH, K);
         for (int k = k0; k < k1; ++k) {
-            const u32x4* Ck = Cl[k & 1];
-            load_c(k + 1);
+            pipe.load_c(min(k + 1, K - 1));
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
-                convert_s(1 - h);
-#pragma unroll
-                for (int rb = 0; rb < RB; ++rb) {
-                    if (rb > 0 && !two) break;
-                    u32x4 A[NP];
-#pragma unroll
-                    for (int part = 0; part < NP; ++part) A[part] = Ck[(part * 4 + 2 * h + half) * LP + 32 * rb + col];
-                    auto product = [&](f32x16 (&acc)[CB], int pa, int pb) {
-#pragma unroll
-                        for (int cb = 0; cb < CB; ++cb)
-                            acc[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(A[pa]), as_bf16x8(B[h][pb][cb]),
-                                                                              acc[cb], 0, 0, 0);
-                    };
-                    auto products = [&](f32x16 (&acc)[CB]) {
-                        if constexpr (NP == 3) {
-                            product(acc, 2, 0);
-                            product(acc, 0, 2);
-                            product(acc, 1, 1);
-                        }
-                        if constexpr (NP >= 2) {
-                            product(acc, 1, 0);
-                            product(acc, 0, 1);
-                        }
-                        product(acc, 0, 0);
-                    };
-#pragma unroll
-                    for (int part = 0; part < NP; ++part) A[part] ^= 0x80000000u;             // (Cr, -Ci)
-                    products(accr[rb]);
-#pragma unroll
-                    for (int part = 0; part < NP; ++part) {                                   // (Ci, Cr)
-                        A[part] ^= 0x80000000u;
-                        A[part] = (A[part] >> 16) | (A[part] << 16);
-                    }
-                    products(acci[rb]);
-                    if (rb == 0) {
-                        // the loads reuse the registers that the conversion
-                        // frees: it ends here (not sunk to where its results
-                        // are used), and the loads are not moved down
-#pragma unroll
-                        for (int part = 0; part < NP; ++part)
-#pragma unroll
-                            for (int cb = 0; cb < CB; ++cb) asm volatile("" : "+v"(B[1 - h][part][cb]));
-                        __builtin_amdgcn_sched_barrier(0);
-                        load_s(h == 0 ? k + 1 : k + 2, 1 - h);
-                        __builtin_amdgcn_sched_barrier(0);
-                    }
-                }
+                pipe.convert_s(1 - h);
+                pipe.products(lds.C[k & 1], h, 0, accr[0], acci[0]);
+                pipe.pin(1 - h);
+                load_s(h == 0 ? k + 1 : k + 2, 1 - h);
+                __builtin_amdgcn_sched_barrier(0);
+                if (two) pipe.products(lds.C[k & 1], h, 1, accr[1], acci[1]);
             }
-            stage_c(Cl[(k + 1) & 1]);
+            pipe.stage_c(lds.C[(k + 1) & 1]);
             __syncthreads();
         }
-        if constexpr (NP == 3) {
+        if constexpr (PARTS) {
 #pragma unroll
             for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
                 for (int cb = 0; cb < CB; ++cb) {
-                    totr[rb][cb] += accr[rb][cb];
-                    toti[rb][cb] += acci[rb][cb];
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) accr[rb][cb][r] = acci[rb][cb][r] = 0.f;
+                    sum.r[rb][cb] += accr[rb][cb];
+                    sum.i[rb][cb] += acci[rb][cb];
                 }
+            clear(accr);
+            clear(acci);
         }
     }
-    // ---- epilogue: D register r = probe row (r & 3) + 8 (r >> 2) + 4 half, column = pixel
+    if constexpr (!PARTS) {
+#pragma unroll
+        for (int a = 0; a < RB; ++a)
+#pragma unroll
+            for (int b = 0; b < CB; ++b) {
+                sum.r[a][b] = accr[a][b];
+                sum.i[a][b] = acci[a][b];
+            }
+    }
+}
+
+template <int NP>
+__global__ __launch_bounds__(mfmac::NT) __attribute__((amdgpu_waves_per_eu(2))) void k_contract(ContractBatch batch) {
+    using namespace mfmac;
+    constexpr int CB = CBS<NP>;
+    __shared__ ContractLds<NP> lds;
+    int tile, chunk;
+    ContractJob job;
+    if (!locate(batch, job, tile, chunk)) return;
+    const int row0 = 8 * CB * (chunk % SPLITS<NP>);   // first tile row of this workgroup
+    chunk /= SPLITS<NP>;
+    float2* __restrict__ win = job.win;
+    const int ns = job.ns, m = job.m;
+    const int t0 = job.tile_start[tile], t1 = job.tile_start[tile + 1];
+    const int pc0 = t0 + chunk * PC;
+    if (pc0 >= t1) return;
+    const int np = min(PC, t1 - pc0);
+    const int2 org = job.tile_origin[tile];
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const int col = lane & 31, half = lane >> 5;
+    if (tid < PC) {
+        const int q = tid < np ? job.tile_probes[pc0 + tid] : -1;
+        lds.idx[tid] = q;
+        lds.at[tid] = q >= 0 ? job.corner[q] : make_int2(0, 0);
+    }
+    __syncthreads();
+    int px = (org.x + (col & 15)) & (ns - 1), py[CB], pix[CB];
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb) {
+        py[cb] = (org.y + row0 + 2 * (CB * wave + cb) + (col >> 4)) & (ns - 1);
+        pix[cb] = py[cb] * ns + px;
+    }
+    Sums<CB> sum;
+    sum_beams<NP, CB, FLUSH<NP>>(lds, job.S, (size_t)ns * ns, job.n_beams, pix, static_cast<const u32x4*>(job.C),
+                                 job.ksteps, np > 32, sum);
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-            const int row = 32 * rb + (r & 3) + 8 * (r >> 2) + 4 * half;
-            const int q = pidx[row];
+            const int row = sum_row(rb, r, half);
+            const int q = lds.idx[row];
             if (q < 0) continue;
-            const int2 c0 = pcorner[row];
+            const int2 c0 = lds.at[row];
 #pragma unroll
             for (int cb = 0; cb < CB; ++cb) {
-                const int py = org.y + row0 + 2 * (CB * wave + cb) + (col >> 4), px = org.x + (col & 15);
-                const int v = (py - c0.y) & (ns - 1);
+                const int v = (py[cb] - c0.y) & (ns - 1);
                 const int u = (px - c0.x) & (ns - 1);
                 if (v < m && u < m) {
                     float2* w = win + (size_t)q * m * m + (size_t)v * m + u;
-                    float2 res = NP == 3 ? make_float2(totr[rb][cb][r], toti[rb][cb][r]) : make_float2(accr[rb][cb][r], acci[rb][cb][r]);
+                    float2 res = make_float2(sum.r[rb][cb][r], sum.i[rb][cb][r]);
                     if (job.accumulate) res = cadd(*w, res);
                     *w = res;
                 }
@@ -491,6 +543,286 @@ hipError_t launch_contract_batch(int precision, const ContractArgs* jobs, int n_
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
+}
+
+// --------------------------------------------------------- two-stage sum --
+// A coefficient is a product of one phase per axis, and the probes of a scan
+// share few x positions, so the beam sum splits into
+//   T[x][ky][pixel] = sum_kx c_b(x) S_b[pixel]      (aberrations, amplitude)
+//   win[probe][pixel] = sum_ky e^{-2 pi i ky y / L} T[x][ky][pixel]
+// with (for 16,384 probes of 1245 beams) a sixteenth of the products.  T is
+// kept for the columns of the windows at x only: [ky][S-grid row][x][window
+// column] (x next to the window column, so that a tile's writes for all its x
+// spread over the memory channels).  Scan columns are sorted by window corner, and the probes of each
+// by corner too, so those whose windows cover a tile are one cyclic run.
+//
+// Bound: HBM traffic (S read, T written and read, windows written) and the
+// latency of its short sums.  16,384 probes of 1245 beams, 128^2 windows at
+// 1024^2, split BF16: 7.0 ms in one stage, 1.2 + 1.1 ms in two (9.9 GB, 4.3
+// TB/s), with the products of the second stage in FP32 accuracy: the error
+// against 64 bits falls from 7e-7 to 2.4e-7.  With T by [x][ky][row][column]
+// and 16-pixel tiles the first stage took 1.9 ms.
+struct TwoStage {
+    const float2* S;
+    float2* T;                // [n_rows][ns][columns of this launch][m]
+    float2* win;              // [n_probes][m][m]
+    const u32x4* cx;          // C operand of the launch's columns over their K steps
+    const u32x4* cy;          // C operand of the probes over ky
+    const int4* rows;         // per ky: first beam, beams, first K step, ky
+    const int4* steps;        // per K step: first beam, beams, ky row, last of its ky
+    const int* col_corner;    // window corner x of the launch's columns, ascending
+    const int* col_start;     // first entry of each of the launch's columns, and the end
+    const int* entry_corner;  // window corner y, ascending within a column
+    const int* entry_probe;
+    int n_cols, n_rows, col_steps, ns, m;
+    int tile_width;           // of the first stage's 128-pixel tiles
+    int row_groups;           // workgroups that share a tile's ky rows
+    int chunks;               // workgroups per 64 scan columns / probes
+    int n_blocks, per_xcd;
+};
+
+// The sorted corners c[0 .. n) whose windows of side m (cyclic on ns) cover
+// any of `span` pixels from `from`: the cyclic run first, count.
+__device__ __forceinline__ void cover_run(const int* __restrict__ c, int n, int from, int span, int m, int ns, int& first,
+                                          int& count) {
+    const int lane = threadIdx.x & 63, a = (from - (m - 1)) & (ns - 1), len = min(m + span - 1, ns);
+    int below = 0, in = 0;
+    for (int base = 0; base < n; base += 64) {
+        const bool have = base + lane < n;
+        const int v = have ? c[base + lane] : 0;
+        below += __popcll(__ballot(have && v < a));
+        in += __popcll(__ballot(have && ((v - a) & (ns - 1)) < len));
+    }
+    first = below == n ? 0 : below;
+    count = in;
+}
+
+// T of 128 pixels (tile_width x 128 / tile_width rows), 64 scan columns and a
+// run of ky.  The K steps of the run are one pipeline: the sum of a ky is
+// stored while the loads of the next are in flight.  The C operand keeps all
+// its parts also when S has two (NB): a column's operand is the same for every
+// ky, and its rounding would add up over them (1.5 times the error of the
+// one-stage sum).
+constexpr int MAX_STEPS = 256;   // K steps of one workgroup
+template <int NB>
+__global__ __launch_bounds__(mfmac::NT) __attribute__((amdgpu_waves_per_eu(2))) void k_sum_kx(TwoStage a) {
+    using namespace mfmac;
+    __shared__ ContractLds<3> lds;
+    __shared__ int4 step[MAX_STEPS];              // first beam, beams, ky row, last of its ky
+    int l = (blockIdx.x & 7) * a.per_xcd + (blockIdx.x >> 3);
+    if (l >= a.n_blocks) return;
+    const int rg = l % a.row_groups;
+    l /= a.row_groups;
+    const int chunk = l % a.chunks;
+    l /= a.chunks;
+    const int ns = a.ns, m = a.m, tw = a.tile_width, nt = ns / tw;
+    const int ox = l % nt * tw, oy = l / nt * (128 / tw);
+    int first, count;
+    cover_run(a.col_corner, a.n_cols, ox, tw, m, ns, first, count);
+    const int np = min(PC, count - chunk * PC);
+    if (np <= 0) return;
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, col = lane & 31, half = lane >> 5;
+    const int r0 = rg * a.n_rows / a.row_groups, r1 = (rg + 1) * a.n_rows / a.row_groups;
+    const int t0 = a.rows[r0].z, n_steps = (r1 < a.n_rows ? a.rows[r1].z : a.col_steps) - t0;
+    for (int t = tid; t < n_steps; t += NT) step[t] = a.steps[t0 + t];
+    if (tid < PC) {
+        const int q = tid < np ? (first + chunk * PC + tid) % a.n_cols : -1;
+        lds.idx[tid] = q;
+        lds.at[tid] = make_int2(q >= 0 ? a.col_corner[q] : 0, 0);
+    }
+    __syncthreads();
+    const int at = wave * 32 + col, px = ox + at % tw, py = oy + at / tw;
+    const int pix[1] = {py * ns + px};
+    const size_t plane = (size_t)ns * ns;
+    const int plane_bytes = (int)(plane * sizeof(float2));
+    BeamPipe<3, NB, 1> pipe;
+    pipe.init(lds, pix, plane_bytes, a.cx + (size_t)t0 * REC<3>, a.col_steps);
+    auto load_s = [&](int t, int h) {
+        const int4 s = step[min(t, n_steps - 1)];
+        const int b0 = __builtin_amdgcn_readfirstlane(s.x) + h * SUB, nb = __builtin_amdgcn_readfirstlane(s.y) - h * SUB;
+        pipe.load_s(h, a.S + (size_t)b0 * plane, (int64_t)nb * plane_bytes);
+    };
+    f32x16 accr[RB][1], acci[RB][1];
+    clear(accr);
+    clear(acci);
+    pipe.load_c(0);
+    load_s(0, 0);
+    load_s(0, 1);
+    pipe.stage_c(lds.C[0]);
+    __syncthreads();
+    pipe.convert_s(0);
+    load_s(1, 0);
+    const bool two = np > 32;
+    for (int t = 0; t < n_steps; ++t) {
+        pipe.load_c(min(t + 1, n_steps - 1));
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            pipe.convert_s(1 - h);
+            pipe.products(lds.C[t & 1], h, 0, accr[0], acci[0]);
+            pipe.pin(1 - h);
+            load_s(h == 0 ? t + 1 : t + 2, 1 - h);
+            __builtin_amdgcn_sched_barrier(0);
+            if (two) pipe.products(lds.C[t & 1], h, 1, accr[1], acci[1]);
+        }
+        pipe.stage_c(lds.C[(t + 1) & 1]);
+        const int4 s = step[t];
+        if (__builtin_amdgcn_readfirstlane(s.w)) {
+            const int k = __builtin_amdgcn_readfirstlane(s.z);
+            float2* out = a.T + ((size_t)k * ns + py) * a.n_cols * m;
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    if (sum_row(rb, r, 0) >= np) continue;        // no rows left here (uniform)
+                    const int row = sum_row(rb, r, half), q = lds.idx[row];
+                    const int u = (px - lds.at[row].x) & (ns - 1);
+                    if (q >= 0 && u < m) out[(size_t)q * m + u] = make_float2(accr[rb][0][r], acci[rb][0][r]);
+                }
+            clear(accr);
+            clear(acci);
+        }
+        __syncthreads();
+    }
+}
+
+// Windows of up to 64 probes of one scan column on 128 pixels of T (1, 2, 4 or
+// 8 rows of the S grid).  T is FP32, and so are these products.
+__global__ __launch_bounds__(mfmac::NT) __attribute__((amdgpu_waves_per_eu(3))) void k_sum_ky(TwoStage a) {
+    using namespace mfmac;
+    __shared__ ContractLds<3> lds;
+    int l = (blockIdx.x & 7) * a.per_xcd + (blockIdx.x >> 3);
+    if (l >= a.n_blocks) return;
+    const int ns = a.ns, m = a.m, w = min(m, 128), R = 128 / w, nu = m / w;
+    const int chunk = l % a.chunks;
+    l /= a.chunks;
+    const int ut = l % nu;
+    l /= nu;
+    const int y0 = l % (ns / R) * R, q = l / (ns / R);
+    const int e0 = a.col_start[q], n = a.col_start[q + 1] - e0;
+    int first, count;
+    cover_run(a.entry_corner + e0, n, y0, R, m, ns, first, count);
+    const int np = min(PC, count - chunk * PC);
+    if (np <= 0) return;
+    const int tid = threadIdx.x, lane = tid & 63, col = lane & 31, half = lane >> 5;
+    if (tid < PC) {
+        const int e = e0 + (first + chunk * PC + tid) % n;
+        lds.idx[tid] = tid < np ? a.entry_probe[e] : -1;
+        lds.at[tid] = make_int2(0, tid < np ? a.entry_corner[e] : 0);
+    }
+    __syncthreads();
+    const int at = (tid >> 6) * 32 + col, py = y0 + at / w, u = ut * 128 + at % w;
+    const int pix[1] = {(at / w) * a.n_cols * m + u};
+    Sums<1> sum;
+    sum_beams<3, 1, 1 << 30>(lds, a.T + ((size_t)y0 * a.n_cols + q) * m, (size_t)ns * a.n_cols * m, a.n_rows, pix, a.cy,
+                 (a.n_rows + KSTEP - 1) / KSTEP, np > 32, sum);
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const int row = sum_row(rb, r, half), p = lds.idx[row];
+            const int v = (py - lds.at[row].y) & (ns - 1);
+            if (p >= 0 && v < m)
+                a.win[(size_t)p * m * m + (size_t)v * m + u] = make_float2(sum.r[rb][0][r], sum.i[rb][0][r]);
+        }
+}
+
+// C operands of both stages, FP32.  Columns: coefficients at (x, 0) over the K
+// steps; probes: e^{-2 pi i ky y / L} over ky.
+__global__ __launch_bounds__(WG) void k_two_stage_operands(u32x4* __restrict__ cx, u32x4* __restrict__ cy,
+                                                           const double2* __restrict__ col_xy,
+                                                           const double2* __restrict__ xy, const int2* __restrict__ beams,
+                                                           const float2* __restrict__ aberr,
+                                                           const int4* __restrict__ steps,
+                                                           const int4* __restrict__ rows, int n_cols, int col_steps,
+                                                           int n_probes, int n_rows, double inv_L, float amp) {
+    const int K2 = (n_rows + KSTEP - 1) / KSTEP;
+    const int64_t nx = (int64_t)n_cols * col_steps * 4, total = nx + (int64_t)n_probes * K2 * 4;
+    for (int64_t i = (int64_t)blockIdx.x * WG + threadIdx.x; i < total; i += (int64_t)gridDim.x * WG) {
+        float2 v[4];
+        if (i < nx) {
+            const int q = (int)((i >> 2) / col_steps), k = (int)((i >> 2) % col_steps), g = (int)(i & 3);
+            const int4 step = steps[k];
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                v[j] = g * 4 + j < step.y ? coefficient(col_xy[q], beams[step.x + g * 4 + j], aberr, step.x + g * 4 + j, inv_L, amp)
+                                          : make_float2(0.f, 0.f);
+            store_operand<3>(cx + (i >> 2) * REC<3>, g, v);
+        } else {
+            const int64_t o = i - nx;
+            const int p = (int)((o >> 2) / K2), k = (int)((o >> 2) % K2), g = (int)(o & 3);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int r = k * KSTEP + g * 4 + j;
+                v[j] = r < n_rows ? coefficient(xy[p], make_int2(0, rows[r].w), nullptr, 0, inv_L, 1.f) : make_float2(0.f, 0.f);
+            }
+            store_operand<3>(cy + (o >> 2) * REC<3>, g, v);
+        }
+    }
+}
+
+hipError_t launch_two_stage_operands(const TwoStageArgs& t, hipStream_t st) {
+    const int K2 = ksteps_of(t.n_rows);
+    const int64_t total = ((int64_t)t.n_cols * t.col_steps + (int64_t)t.n_probes * K2) * 4;
+    const int64_t blocks = std::min<int64_t>((total + WG - 1) / WG, 65536);
+    hipLaunchKernelGGL(k_two_stage_operands, dim3((unsigned)blocks), dim3(WG), 0, st, static_cast<u32x4*>(t.cx),
+                       static_cast<u32x4*>(t.cy), t.col_xy, t.xy, t.beams, t.aberr, t.steps, t.rows, t.n_cols,
+                       t.col_steps, t.n_probes, t.n_rows, t.inv_L, t.amp);
+    return hipGetLastError();
+}
+
+size_t two_stage_cx_bytes(int n_cols, int col_steps) { return (size_t)n_cols * col_steps * 16 * REC<3>; }
+size_t two_stage_cy_bytes(int64_t n_probes, int n_rows) { return (size_t)n_probes * ksteps_of(n_rows) * 16 * REC<3>; }
+size_t two_stage_column_bytes(int n_rows, int ns, int m) { return (size_t)n_rows * ns * m * sizeof(float2); }
+
+int two_stage_columns(const TwoStageArgs& t) {
+    const size_t fit = t.T_bytes / two_stage_column_bytes(t.n_rows, t.ns, t.m);
+    return (int)std::max<size_t>(1, std::min<size_t>(fit, t.n_cols));
+}
+
+static TwoStage two_stage_launch(const TwoStageArgs& t, int q0, int n) {
+    TwoStage a{};
+    a.S = t.S;
+    a.T = t.T;
+    a.win = t.win;
+    a.cx = static_cast<const u32x4*>(t.cx) + (size_t)q0 * t.col_steps * REC<3>;
+    a.cy = static_cast<const u32x4*>(t.cy);
+    a.rows = t.rows;
+    a.steps = t.steps;
+    a.col_corner = t.col_corner + q0;
+    a.col_start = t.col_start + q0;
+    a.entry_corner = t.entry_corner;
+    a.entry_probe = t.entry_probe;
+    a.n_cols = n;
+    a.n_rows = t.n_rows;
+    a.col_steps = t.col_steps;
+    a.ns = t.ns;
+    a.m = t.m;
+    a.tile_width = t.tile_width;
+    return a;
+}
+static hipError_t start_two_stage(void (*kernel)(TwoStage), TwoStage& a, int64_t blocks, hipStream_t st) {
+    if (blocks > 0x7ffffff0) return hipErrorInvalidValue;
+    a.n_blocks = (int)blocks;
+    a.per_xcd = (a.n_blocks + 7) / 8;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(8 * a.per_xcd)), dim3(mfmac::NT), 0, st, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_sum_kx(int precision, const TwoStageArgs& t, int q0, int n, hipStream_t st) {
+    TwoStage a = two_stage_launch(t, q0, n);
+    a.chunks = (t.max_cols + mfmac::PC - 1) / mfmac::PC;
+    const int64_t tiles = (int64_t)t.ns * t.ns / 128 * a.chunks;
+    const int row_steps = ksteps_of(t.max_row_beams), least = (t.n_rows * row_steps + MAX_STEPS - 1) / MAX_STEPS;
+    a.row_groups = std::min(t.n_rows, std::max(2 * least, (int)std::min<int64_t>(4096 / tiles, t.n_rows)));
+    return start_two_stage(precision == 0 ? k_sum_kx<3> : k_sum_kx<2>, a, tiles * a.row_groups, st);
+}
+
+hipError_t launch_sum_ky(const TwoStageArgs& t, int q0, int n, hipStream_t st) {
+    TwoStage a = two_stage_launch(t, q0, n);
+    const int w = std::min(t.m, 128), R = 128 / w;
+    a.chunks = (t.max_probes + mfmac::PC - 1) / mfmac::PC;
+    return start_two_stage(k_sum_ky, a, (int64_t)n * (t.ns / R) * (t.m / w) * a.chunks, st);
 }
 
 // ------------------------------------------------ deterministic bin sums --
