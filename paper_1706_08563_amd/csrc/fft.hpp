@@ -131,6 +131,10 @@ template <> struct Plan<256>  { static constexpr int E = 8,  NST = 3; static con
 template <> struct Plan<512>  { static constexpr int E = 8,  NST = 3; static constexpr int R[3] = {8, 8, 8}; };
 template <> struct Plan<1024> { static constexpr int E = 16, NST = 3; static constexpr int R[3] = {16, 8, 8}; };
 
+// Plan of the 128-point window transforms: one exchange instead of two, 8 lanes
+// per transform.
+struct PlanWin128 { static constexpr int E = 16, NST = 2; static constexpr int R[3] = {16, 8, 1}; };
+
 // Plans of transforms spread over two wavefronts of a workgroup (fewer
 // registers per lane than the one-wavefront plan of the same length).
 template <int L> struct Plan2;

@@ -833,8 +833,8 @@ __device__ __forceinline__ float wave_sum(float v) {
 }
 
 // ------------------------------------------------------- window detection --
-// One workgroup per probe: M x M window in LDS, row then column transforms,
-// |Psi|^2 / M^4, then each bin summed over its pixel list by one wavefront.
+// One workgroup per probe: row transforms, M x M window in LDS, column
+// transforms, |Psi|^2 / M^4, then each bin summed over its pixel list.
 struct WindowJob {
     const float2* win;        // [n_probes][m][m]
     float* out;               // [n_probes][n_bins], or null
@@ -843,120 +843,131 @@ struct WindowJob {
     const int* bin_start;     // [n_bins + 1]
     const float2* tw_m;       // W_m twiddles
     int n_bins;
-    int probe0;               // first workgroup of this job
+    int probe0;               // first probe of this job among those of the launch
     float scale;              // out = scale * sum (+ out when accumulating)
     int accumulate;
 };
 struct WindowBatch {
     int n_jobs;
+    int n_probes;             // over all jobs
     WindowJob job[MAX_JOBS];
 };
 
-// The window sits in LDS with an odd row stride RS of at least the padded
-// exchange length and with that many rows (more than M), so that each row
-// transform and each column transform exchanges in place, through the
-// padded slots of its own row or column: no separate exchange buffers, so
-// the 128-point windows take 16 wavefronts per workgroup in the LDS that
-// would otherwise hold 4 wavefronts' exchange buffers.  The odd stride keeps
-// the strided column accesses of 16 lanes in distinct banks.
+// Rows go straight from memory to their transform's registers; the window then
+// sits in LDS with an odd row stride RS of at least the padded exchange length
+// and with that many rows (more than M), so that each row transform and each
+// column transform exchanges in place, through the padded slots of its own row
+// or column: no separate exchange buffers.  The odd stride keeps the strided
+// column accesses in distinct banks.
+//
+// Bound: LDS traffic and latency (128-point windows: LDS and VALU each busy for
+// half of the time).  A 128-point window leaves room for one workgroup per CU,
+// which therefore stays for several probes and loads the next one's rows while
+// it transforms the columns and sums the bins of this one; its transforms are
+// 16 x 8 points (one exchange instead of two).  Bins are summed by BL lanes
+// each: a 64-point window has 24-50 pixels per bin, and a wavefront per bin took
+// its 33 bins one after the other.  256 probes of 64^2: 25 -> 8.6 us; 16,384
+// of 64^2: 370 -> 216 us; 16,384 of 128^2: 1.32 -> 1.30 ms (BL = 16: 1.32, 64:
+// 1.46; 16 wavefronts of 8 x 4 x 4 points: 1.42).
+template <int M> struct WinFft { using type = Fft<M>; };
+template <> struct WinFft<128> { using type = FftT<128, PlanWin128>; };
 template <int M>
 struct WinCfg {
-    using F = Fft<M>;
-    static constexpr int NW = M >= 128 ? 16 : 4;              // wavefronts per workgroup
+    using F = typename WinFft<M>::type;
+    static constexpr int NW = M >= 64 ? 8 : 4;                // wavefronts per workgroup
+    static constexpr int BL = M >= 128 ? 32 : 8;              // lanes per bin
     static constexpr int NT = 64 * NW;
     static constexpr int RS = F::LDS | 1;                     // row stride (float2), odd
     static constexpr int ROWS = F::LDS;                       // rows (the column exchanges use all)
+    static constexpr int PERSIST = M >= 128 ? 256 : 1 << 30;  // most workgroups of a launch
 };
+
+// Job of probe p of a launch, copied out by value (see locate).
+__device__ __forceinline__ WindowJob window_job(const WindowBatch& batch, int p) {
+    int jj = 0;
+#pragma unroll
+    for (int k = 1; k < MAX_JOBS; ++k)
+        if (k < batch.n_jobs && batch.job[k].probe0 <= p) jj = k;
+    return batch.job[jj];
+}
 
 template <int M>
 __global__ __launch_bounds__(WinCfg<M>::NT) void k_window_detect(WindowBatch batch) {
     using C = WinCfg<M>;
     using F = typename C::F;
-    constexpr int E = F::E, LPT = F::LPT, G = 64 / LPT, NW = C::NW, NT = C::NT, RS = C::RS;
+    constexpr int E = F::E, LPT = F::LPT, G = 64 / LPT, NW = C::NW, NT = C::NT, RS = C::RS, BL = C::BL;
+    constexpr int NR = (M + NW * G - 1) / (NW * G);           // rows of a lane's transforms
     __shared__ float2 buf[C::ROWS * RS];
-    int jj = 0;
-#pragma unroll
-    for (int k = 1; k < MAX_JOBS; ++k)
-        if (k < batch.n_jobs && batch.job[k].probe0 <= (int)blockIdx.x) jj = k;
-    const WindowJob job = batch.job[jj];
-    const float2* __restrict__ win = job.win;
-    float* __restrict__ out = job.out;
-    float* __restrict__ diff = job.diff;
-    const int* __restrict__ perm = job.perm;
-    const int* __restrict__ bin_start = job.bin_start;
-    const float2* __restrict__ tw_m = job.tw_m;
-    const int n_bins = job.n_bins;
-    const int p = (int)blockIdx.x - job.probe0;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int g = lane / LPT, lt = lane % LPT;
-    const float2* w = win + (size_t)p * M * M;
-    {
-        // batches of loads in flight before their LDS stores
-        constexpr int NLD = (M * M + NT - 1) / NT, BATCH = NLD < 16 ? NLD : 16;
-        static_assert(NLD % BATCH == 0, "load batches must divide the window");
+    const int r0 = wave * G + g;                              // rows (and columns) r0 + i NW G
+    float2 next[NR][E];
+    auto load_rows = [&](int p) {
+        const WindowJob job = window_job(batch, p);
+        const float2* w = job.win + (size_t)(p - job.probe0) * M * M;
+#pragma unroll
+        for (int i = 0; i < NR; ++i)
+            if (r0 + i * NW * G < M)
+#pragma unroll
+                for (int e = 0; e < E; ++e) next[i][e] = w[(r0 + i * NW * G) * M + lt + LPT * e];
+    };
+    load_rows(blockIdx.x);
+    for (int pp = blockIdx.x; pp < batch.n_probes; pp += gridDim.x) {
+        const WindowJob job = window_job(batch, pp);
+        const int p = pp - job.probe0, n_bins = job.n_bins;
+        typename F::Twiddles tw;
+        tw.load(job.tw_m, lt);
+        // rows, each exchanged in its own padded row
+#pragma unroll
+        for (int i = 0; i < NR; ++i)
+            if (r0 + i * NW * G < M) {
+                float2* row = buf + (r0 + i * NW * G) * RS;
+                F::template run_x<-1>(next[i], typename F::RowX{row}, tw, lt);
+                F::sync();
+#pragma unroll
+                for (int e = 0; e < E; ++e) row[lt + LPT * e] = next[i][e];
+            }
+        __syncthreads();
+        if (pp + (int)gridDim.x < batch.n_probes) load_rows(pp + gridDim.x);
+        // columns, each exchanged in its own padded column, then intensity in place
+        const float scale = 1.0f / ((float)M * (float)M * (float)M * (float)M);
 #pragma unroll 1
-        for (int k0 = 0; k0 < NLD; k0 += BATCH) {
-            float2 ld[BATCH];
+        for (int c = r0; c < M; c += NW * G) {
+            float2* col = buf + c;
+            float2 v[E];
 #pragma unroll
-            for (int k = 0; k < BATCH; ++k) {
-                const int idx = tid + (k0 + k) * NT;
-                if (idx < M * M) ld[k] = w[idx];
+            for (int i = 0; i < E; ++i) v[i] = col[(lt + LPT * i) * RS];
+            F::template run_x<-1>(v, typename F::template StrideX<RS>{col}, tw, lt);
+            F::sync();
+#pragma unroll
+            for (int i = 0; i < E; ++i) col[(lt + LPT * i) * RS] = make_float2(cnorm(v[i]) * scale, 0.f);
+        }
+        __syncthreads();
+        if (job.diff) {
+            // the 4D output takes the same scale and accumulation as the 3D one
+            float* d = job.diff + (size_t)p * M * M;
+            for (int idx = tid; idx < M * M; idx += NT) {
+                const float v = job.scale * buf[(idx / M) * RS + idx % M].x;
+                d[idx] = job.accumulate ? d[idx] + v : v;
             }
+        }
+        if (job.out)
+            for (int b = tid / BL; b < n_bins; b += NT / BL) {
+                float s = 0.f;
+                const int k1 = job.bin_start[b + 1];
+#pragma unroll 4
+                for (int k = job.bin_start[b] + tid % BL; k < k1; k += BL) {
+                    const int pix = job.perm[k];
+                    s += buf[(pix / M) * RS + pix % M].x;
+                }
 #pragma unroll
-            for (int k = 0; k < BATCH; ++k) {
-                const int idx = tid + (k0 + k) * NT;
-                if (idx < M * M) buf[(idx / M) * RS + idx % M] = ld[k];
+                for (int off = BL / 2; off > 0; off >>= 1) s += __shfl_xor(s, off, BL);
+                if (tid % BL == 0) {
+                    float* o = job.out + (size_t)p * n_bins + b;
+                    *o = job.accumulate ? *o + job.scale * s : job.scale * s;
+                }
             }
-        }
-    }
-    __syncthreads();
-    typename F::Twiddles tw;
-    tw.load(tw_m, lt);
-    // rows, each exchanged in its own padded row
-    for (int r0 = wave * G; r0 < M; r0 += NW * G) {
-        float2* row = buf + (r0 + g) * RS;
-        float2 v[E];
-#pragma unroll
-        for (int i = 0; i < E; ++i) v[i] = row[lt + LPT * i];
-        F::template run_x<-1>(v, typename F::RowX{row}, tw, lt);
-        F::sync();
-#pragma unroll
-        for (int i = 0; i < E; ++i) row[lt + LPT * i] = v[i];
-    }
-    __syncthreads();
-    // columns, each exchanged in its own padded column, then intensity in place
-    const float scale = 1.0f / ((float)M * (float)M * (float)M * (float)M);
-    for (int c0 = wave * G; c0 < M; c0 += NW * G) {
-        float2* col = buf + c0 + g;
-        float2 v[E];
-#pragma unroll
-        for (int i = 0; i < E; ++i) v[i] = col[(lt + LPT * i) * RS];
-        F::template run_x<-1>(v, typename F::template StrideX<RS>{col}, tw, lt);
-        F::sync();
-#pragma unroll
-        for (int i = 0; i < E; ++i) col[(lt + LPT * i) * RS] = make_float2(cnorm(v[i]) * scale, 0.f);
-    }
-    __syncthreads();
-    if (diff) {
-        // the 4D output takes the same scale and accumulation as the 3D one
-        float* d = diff + (size_t)p * M * M;
-        for (int idx = tid; idx < M * M; idx += NT) {
-            const float v = job.scale * buf[(idx / M) * RS + idx % M].x;
-            d[idx] = job.accumulate ? d[idx] + v : v;
-        }
-    }
-    if (!out) return;
-    for (int b = wave; b < n_bins; b += NW) {
-        float s = 0.f;
-        for (int k = bin_start[b] + lane; k < bin_start[b + 1]; k += 64) {
-            int pix = perm[k];
-            s += buf[(pix / M) * RS + pix % M].x;
-        }
-        s = wave_sum(s);
-        if (lane == 0) {
-            float* o = out + (size_t)p * n_bins + b;
-            *o = job.accumulate ? *o + job.scale * s : job.scale * s;
-        }
+        __syncthreads();                                      // the next rows overwrite the intensities
     }
 }
 
@@ -965,15 +976,15 @@ static hipError_t window_m(const WindowArgs* jobs, int n_jobs, hipStream_t st) {
     for (int j0 = 0; j0 < n_jobs; j0 += MAX_JOBS) {
         WindowBatch b{};
         b.n_jobs = n_jobs - j0 < MAX_JOBS ? n_jobs - j0 : MAX_JOBS;
-        int blocks = 0;
         for (int k = 0; k < b.n_jobs; ++k) {
             const WindowArgs& a = jobs[j0 + k];
-            b.job[k] = WindowJob{a.win, a.out, a.diff, a.perm, a.bin_start, a.tw_m, a.n_bins, blocks, a.scale,
+            b.job[k] = WindowJob{a.win, a.out, a.diff, a.perm, a.bin_start, a.tw_m, a.n_bins, b.n_probes, a.scale,
                                  a.accumulate};
-            blocks += a.n_probes;
+            b.n_probes += a.n_probes;
         }
-        if (blocks == 0) continue;
-        hipLaunchKernelGGL((k_window_detect<M>), dim3((unsigned)blocks), dim3(WinCfg<M>::NT), 0, st, b);
+        if (b.n_probes == 0) continue;
+        hipLaunchKernelGGL((k_window_detect<M>), dim3((unsigned)std::min(b.n_probes, WinCfg<M>::PERSIST)),
+                           dim3(WinCfg<M>::NT), 0, st, b);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
