@@ -864,17 +864,20 @@ constexpr int kMaxBuildStreams = 4;
 // as each further stream costs two launches per slice and shorter kernels, in
 // us per build on 1, 2 and 4 streams:
 //   21 beams at 256^2 (1.4 M)    339    455    765
+//   16 probes at 1024^2 (17 M)  3516   3655      -   (multislice, 4 batches)
 //   69 beams at 256^2 (4.5 M)    308    310    472
 //   69 beams at 512^2 (18 M)    1502   1374   1807
 //   305 beams at 256^2 (20 M)   1566   1408   1765
 //   1245 beams at 512^2 (326 M) 23359 22753  23269
 //   1245 beams at 1024^2 (1.3 G) 262.4, 253.9 and 249.5 ms
 std::atomic<int> g_build_streams{0};
+int streams_by_size(int n, int64_t items) {
+    const int64_t pixels = items * n * n;
+    return n > 1024 || items < 32 || pixels < (int64_t)8 << 20 ? 1 : (pixels < (int64_t)700 << 20 ? 2 : 4);
+}
 int build_streams_for(int n, int beams) {
     const int s = g_build_streams.load();
-    if (s > 0) return s;
-    const int64_t pixels = (int64_t)beams * n * n;
-    return n > 1024 || pixels < (int64_t)8 << 20 ? 1 : (pixels < (int64_t)700 << 20 ? 2 : 4);
+    return s > 0 ? s : streams_by_size(n, beams);
 }
 std::mutex g_partner_mu;
 std::map<hipStream_t, std::vector<hipStream_t>> g_partner;
@@ -915,6 +918,73 @@ int prism_set_build_streams(int32_t n) {
     return PRISM_OK;
 }
 
+// Items [first, end) in batches of NB on P streams: run(b0, i0, cnt, q, after)
+// queues items b0 + i0 .. b0 + i0 + cnt - 1 of the batch starting at b0 on
+// stream q and records `after`, when not null, where the next stream may
+// start.  Buffer slot i always holds item b0 + i of the current batch, and
+// stream k owns slots [off(k), off(k + 1)) in every batch (a short last batch
+// leaves the tail parts empty), so no two streams ever touch the same slot;
+// the forks of the first batch and the final joins are the only cross-stream
+// orderings needed.  On return all work is ordered on st, also after an error.
+}  // extern "C"
+
+template <class Run>
+static int run_overlapped(hipStream_t st, int P, int64_t first, int64_t end, int NB, Run&& run) {
+    if (end <= first) return PRISM_OK;
+    // batches of equal size: a short last one would leave the tail parts idle
+    const int64_t batches = (end - first + NB - 1) / NB;
+    NB = (int)((end - first + batches - 1) / batches);
+    P = std::min(P, NB);
+    hipStream_t q[kMaxBuildStreams] = {st};
+    if (P > 1) {
+        int got = 0;
+        int rc = partner_streams(st, P - 1, q + 1, &got);
+        if (rc) return rc;
+        if (got < P - 1) P = 1;
+    }
+    if (P <= 1) {
+        for (int64_t b0 = first; b0 < end; b0 += NB) {
+            int rc = run(b0, 0, (int)std::min<int64_t>(NB, end - b0), st, nullptr);
+            if (rc) return rc;
+        }
+        return PRISM_OK;
+    }
+    BuildEvents be;
+    for (int k = 0; k < 2 * P; ++k) HIP_TRY(hipEventCreateWithFlags(&be.ev[k], hipEventDisableTiming));
+    auto off = [&](int k) { return (int)((int64_t)k * NB / P); };
+    int forked = 1;                              // streams that may hold work of this call
+    auto enqueue = [&]() -> int {
+        for (int64_t b0 = first; b0 < end; b0 += NB) {
+            const int nb = (int)std::min<int64_t>(NB, end - b0);
+            for (int k = 0; k < P; ++k) {
+                const int i0 = off(k), cnt = std::min(off(k + 1), nb) - i0;
+                if (b0 == first && k > 0) {
+                    HIP_TRY(hipStreamWaitEvent(q[k], be.ev[k - 1], 0));
+                    forked = k + 1;
+                }
+                if (cnt > 0) {
+                    int r = run(b0, i0, cnt, q[k], b0 == first ? be.ev[k] : nullptr);
+                    if (r) return r;
+                } else if (b0 == first) {
+                    HIP_TRY(hipEventRecord(be.ev[k], q[k]));
+                }
+            }
+        }
+        return PRISM_OK;
+    };
+    int rc = enqueue();
+    // join every partner that may hold work, also after an error, so that
+    // the caller's stream orders all of this call's work
+    for (int k = 1; k < forked; ++k) {
+        hipError_t e = hipEventRecord(be.ev[P + k], q[k]);
+        if (e == hipSuccess) e = hipStreamWaitEvent(st, be.ev[P + k], 0);
+        if (e != hipSuccess && rc == PRISM_OK) rc = fail(PRISM_E_DEVICE, "stream join: %s", hipGetErrorString(e));
+    }
+    return rc;
+}
+
+extern "C" {
+
 // S-matrix layers [first, first + count): all slices of each beam batch,
 // then the real-space store.
 static int build_range(const prism_smatrix_desc* d, const float* V, void* S, int first, int count, void* ws,
@@ -952,7 +1022,7 @@ static int build_range(const prism_smatrix_desc* d, const float* V, void* S, int
     float2* Sout = static_cast<float2*>(S);
     const size_t item_w = (size_t)(n / 2) * wave_col_stride(n), layer = (size_t)(n / 2) * (n / 2);
     // items [i0, i0 + cnt) of the batch starting at beam b0, all slices then the store, on stream q
-    auto run_items = [&](int b0, int i0, int cnt, hipStream_t q, hipEvent_t after_first_a) -> int {
+    auto run_items = [&](int64_t b0, int i0, int cnt, hipStream_t q, hipEvent_t after_first_a) -> int {
         float2* Wq = W + (size_t)i0 * item_w;
         const int2* bq = d_beams + b0 + i0;
         for (int s = 0; s < nsl; ++s) {
@@ -973,58 +1043,7 @@ static int build_range(const prism_smatrix_desc* d, const float* V, void* S, int
         HIP_TRY(timed(PRISM_K_FINAL, q, [&] { return launch_smatrix_final(n, Wq, Sq, pd.tw_half, cnt, q); }));
         return PRISM_OK;
     };
-    int P = std::min(build_streams_for(n, NB), NB);
-    hipStream_t q[kMaxBuildStreams] = {st};
-    if (P > 1) {
-        int got = 0;
-        rc = partner_streams(st, P - 1, q + 1, &got);
-        if (rc) return rc;
-        if (got < P - 1) P = 1;
-    }
-    if (P <= 1) {
-        for (int b0 = first; b0 < end; b0 += NB) {
-            rc = run_items(b0, 0, std::min(NB, end - b0), st, nullptr);
-            if (rc) return rc;
-        }
-        return PRISM_OK;
-    }
-    // Wave-buffer item i always holds beam b0 + i of the current batch, and
-    // stream k owns items [off(k), off(k + 1)) in every batch (a short last
-    // batch leaves the tail parts empty), so no two streams ever touch the
-    // same item; the forks of the first batch and the final joins are the
-    // only cross-stream orderings needed.
-    BuildEvents be;
-    for (int k = 0; k < 2 * P; ++k) HIP_TRY(hipEventCreateWithFlags(&be.ev[k], hipEventDisableTiming));
-    auto off = [&](int k) { return (int)((int64_t)k * NB / P); };
-    int forked = 1;                              // streams that may hold work of this call
-    auto enqueue = [&]() -> int {
-        for (int b0 = first; b0 < end; b0 += NB) {
-            const int nb = std::min(NB, end - b0);
-            for (int k = 0; k < P; ++k) {
-                const int i0 = off(k), cnt = std::min(off(k + 1), nb) - i0;
-                if (b0 == first && k > 0) {
-                    HIP_TRY(hipStreamWaitEvent(q[k], be.ev[k - 1], 0));
-                    forked = k + 1;
-                }
-                if (cnt > 0) {
-                    int r = run_items(b0, i0, cnt, q[k], b0 == first ? be.ev[k] : nullptr);
-                    if (r) return r;
-                } else if (b0 == first) {
-                    HIP_TRY(hipEventRecord(be.ev[k], q[k]));
-                }
-            }
-        }
-        return PRISM_OK;
-    };
-    rc = enqueue();
-    // join every partner that may hold work, also after an error, so that
-    // the caller's stream orders all of this call's work
-    for (int k = 1; k < forked; ++k) {
-        hipError_t e = hipEventRecord(be.ev[P + k], q[k]);
-        if (e == hipSuccess) e = hipStreamWaitEvent(st, be.ev[P + k], 0);
-        if (e != hipSuccess && rc == PRISM_OK) rc = fail(PRISM_E_DEVICE, "build: stream join: %s", hipGetErrorString(e));
-    }
-    return rc;
+    return run_overlapped(st, build_streams_for(n, NB), first, end, NB, run_items);
 }
 
 int prism_build_smatrix(const prism_smatrix_desc* d, const float* V, void* S, void* ws, size_t ws_bytes,
@@ -1652,30 +1671,39 @@ static int multislice_run(const prism_grid* grid, double E0, double alpha_max, c
     }
     const float amp = (float)(1.0 / std::sqrt((double)h.n_ap));
     long long g = 0;
-    for (int64_t p0 = 0; p0 < n_probes; p0 += batch) {
-        const int nb = (int)std::min<int64_t>(batch, n_probes - p0);
-        HIP_TRY(timed(PRISM_K_PASS_B, st, [&] {
-            return launch_pass_b(n, PASSB_INIT, m.W, tb, h.aberr.empty() ? nullptr : m.aberr, nullptr, m.kymax,
-                                 m.xy + p0, 1.0 / L, amp, nb, st);
+    const size_t item_w = (size_t)Lh * wave_col_stride(n), item_i = (size_t)Lh * Lh;
+    // probes p0 + i0 .. of the batch at p0, in slots i0 .. of the wave buffer, on stream q
+    auto run_probes = [&](int64_t p0, int i0, int nb, hipStream_t q, hipEvent_t after_first) -> int {
+        float2* W = m.W + (size_t)i0 * item_w;
+        float* I = m.I + (size_t)i0 * item_i;
+        HIP_TRY(timed(PRISM_K_PASS_B, q, [&] {
+            return launch_pass_b(n, PASSB_INIT, W, tb, h.aberr.empty() ? nullptr : m.aberr, nullptr, m.kymax,
+                                 m.xy + p0 + i0, 1.0 / L, amp, nb, q);
         }));
         for (int s = 0; s < nsl; ++s) {
             const float2* Ts = m.T + (size_t)s * n * n;
             if (streaming) {
-                rc = feed_slice(ring, g++, V_host, s, n, m.vslot, m.T, (float)h.sig, st, h2d);
-                if (rc) return rc;
+                int r = feed_slice(ring, g++, V_host, s, n, m.vslot, m.T, (float)h.sig, q, h2d);
+                if (r) return r;
                 Ts = m.T;
             }
-            HIP_TRY(timed(PRISM_K_PASS_A, st, [&] { return launch_pass_a(n, m.W, Ts, tb, nb, st); }));
-            HIP_TRY(timed(PRISM_K_PASS_B, st, [&] {
-                return launch_pass_b(n, s == nsl - 1 ? PASSB_LAST_I : PASSB_MID, m.W, tb, nullptr, m.I, nullptr,
-                                     nullptr, 0.0, 0.f, nb, st);
+            HIP_TRY(timed(PRISM_K_PASS_A, q, [&] { return launch_pass_a(n, W, Ts, tb, nb, q); }));
+            if (s == 0 && after_first) HIP_TRY(hipEventRecord(after_first, q));
+            HIP_TRY(timed(PRISM_K_PASS_B, q, [&] {
+                return launch_pass_b(n, s == nsl - 1 ? PASSB_LAST_I : PASSB_MID, W, tb, nullptr, I, nullptr, nullptr,
+                                     0.0, 0.f, nb, q);
             }));
         }
-        HIP_TRY(timed(PRISM_K_BIN_REDUCE, st, [&] {
-            return launch_bin_reduce(m.I, (int64_t)Lh * Lh, out + p0 * n_bins, m.perm, m.bstart, nb, n_bins, st);
+        HIP_TRY(timed(PRISM_K_BIN_REDUCE, q, [&] {
+            return launch_bin_reduce(I, (int64_t)item_i, out + (p0 + i0) * n_bins, m.perm, m.bstart, nb, n_bins, q);
         }));
-    }
-    return PRISM_OK;
+        return PRISM_OK;
+    };
+    // Overlapped as the S-matrix build is: 100 probes of 50 slices at 1024^2, 64
+    // at a time, 23.6 ms on one stream, 22.5 on two.  A streamed call has one
+    // transmission slice, which one stream at a time may use.
+    const int NB = (int)std::min<int64_t>(batch, std::max<int64_t>(n_probes, 1));
+    return run_overlapped(st, streaming ? 1 : streams_by_size(n, NB), 0, n_probes, NB, run_probes);
 }
 
 int multislice_workspace(const prism_grid* grid, int32_t batch, int64_t n_probes, size_t* bytes) {

@@ -1118,30 +1118,41 @@ hipError_t launch_window_batch(int m, const WindowArgs* jobs, int n_jobs, hipStr
 }
 
 // ------------------------------------------------------------- bin reduce --
+// One wavefront per (item, bin).  Bound: latency of the gathered loads, several
+// of which are in flight at once.  64 items, 62 bins of a 512^2 band: 418 -> 30
+// us; 134 bins of a 128^2 band: 42 -> 7.5 us, against one workgroup per item
+// that took its bins in turn.
 __global__ __launch_bounds__(WG) void k_bin_reduce(const float* __restrict__ inten, int64_t pix_per_item,
                                                    float* __restrict__ out, const int* __restrict__ perm,
                                                    const int* __restrict__ bin_start, int n_bins, float scale,
                                                    int accumulate) {
-    const int item = blockIdx.x;
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const int groups = (n_bins + 3) / 4, item = blockIdx.x / groups;
+    const int b = blockIdx.x % groups * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (b >= n_bins) return;
     const float* I = inten + (size_t)item * pix_per_item;
-    for (int b = wave; b < n_bins; b += 4) {
-        float s = 0.f;
-        for (int k = bin_start[b] + lane; k < bin_start[b + 1]; k += 64) s += I[perm[k]];
-        s = wave_sum(s);
-        if (lane == 0) {
-            float* o = out + (size_t)item * n_bins + b;
-            *o = accumulate ? *o + scale * s : scale * s;
-        }
+    const int k1 = bin_start[b + 1];
+    float s = 0.f;
+#pragma unroll 8
+    for (int k = bin_start[b] + lane; k < k1; k += 64) s += I[perm[k]];
+    s = wave_sum(s);
+    if (lane == 0) {
+        float* o = out + (size_t)item * n_bins + b;
+        *o = accumulate ? *o + scale * s : scale * s;
     }
 }
 
 hipError_t launch_bin_reduce(const float* inten, int64_t pix_per_item, float* out, const int* perm,
                              const int* bin_start, int n_items, int n_bins, hipStream_t st, float scale,
                              int accumulate) {
-    hipLaunchKernelGGL(k_bin_reduce, dim3((unsigned)n_items), dim3(WG), 0, st, inten, pix_per_item, out, perm,
-                       bin_start, n_bins, scale, accumulate);
-    return hipGetLastError();
+    const int groups = (n_bins + 3) / 4, most = 0x7fffff00 / groups;   // items per launch
+    for (int i = 0; i < n_items; i += most) {
+        const int n = std::min(most, n_items - i);
+        hipLaunchKernelGGL(k_bin_reduce, dim3((unsigned)n * groups), dim3(WG), 0, st, inten + (size_t)i * pix_per_item,
+                           pix_per_item, out + (size_t)i * n_bins, perm, bin_start, n_bins, scale, accumulate);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 }  // namespace prism

@@ -35,3 +35,23 @@ def test_columns_per_group(batch):
     ref = O.build_smatrix(V.astype(np.float64), L, 2.0, one.lambda_, one.sigma, beams)
     got3 = whole[[0, 300, len(whole) - 1]].cpu().numpy()
     assert np.linalg.norm(got3 - ref) / np.linalg.norm(ref) <= 1e-5
+
+
+# batches that do not divide the probes, more and fewer streams, and a batch of
+# one: every probe's output is the one it has alone
+@pytest.mark.parametrize("n,probes,batch", [(512, 70, 64), (512, 65, 32), (256, 131, 130), (64, 5, 2), (64, 3, 1)])
+def test_multislice_batches(n, probes, batch):
+    import torch
+    import paper_1706_08563_amd as P
+    L, S, E0 = 0.1 * n, 2, 200e3
+    V = np.random.default_rng(6).uniform(0.0, 60.0, size=(S, n, n)).astype(np.float32)
+    Vd = torch.from_numpy(V).cuda()
+    g = P.prism_grid_init((L, L, 2.0 * S), 2.0, n)
+    xy = np.random.default_rng(7).uniform(0.0, L, size=(probes, 2))
+    got = P.multislice_outputs(g, E0, 0.02, Vd, xy, batch=batch)
+    alone = torch.cat([P.multislice_outputs(g, E0, 0.02, Vd, xy[p:p + 1], batch=1) for p in (0, probes // 2, probes - 1)])
+    assert torch.equal(got[[0, probes // 2, probes - 1]], alone)
+    d = P.prism_smatrix_plan(g, E0, 0.02, 1) if n <= 256 else None
+    if d is not None:
+        ref = O.multislice_outputs(V.astype(np.float64), L, 2.0, d.lambda_, d.sigma, 0.02, xy[:2])
+        assert O.rel_err(got[:2].cpu().numpy(), ref) <= 1e-5
