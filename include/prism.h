@@ -183,9 +183,9 @@ int prism_build_smatrix_range(const prism_smatrix_desc* d, const float* V, void*
                               int32_t count, void* ws, size_t ws_bytes, void* stream);
 
 /* Streams used by prism_build_smatrix (process-wide), n in 1..4, or 0 (the
- * default) for a count chosen by size: 1 for n > 1024 and for small beam
- * batches, else 2, or 4 for large batches.  Every beam batch is split into n parts, run on `stream` and on n - 1
- * partner streams that the library creates once per caller stream (default
+ * default) for a count chosen by size: 1 for small beam batches, else 2, or 4
+ * for large ones.  Every beam batch is split into n parts, run on `stream` and
+ * on n - 1 partner streams that the library creates once per caller stream (default
  * priority, kept until the process ends), each part one slice behind the
  * previous one, so that row and column passes of different beams run
  * together.  The call still returns with all work ordered on `stream`, and

@@ -858,22 +858,29 @@ constexpr int kMaxBuildStreams = 4;
 #ifndef PRISM_FORK_STAGE
 #define PRISM_FORK_STAGE 1
 #endif
-// 0: by size.  One stream above n = 1024 (1245 beams at 2048^2 on 1, 2, 3 and
-// 4: 1.419, 1.410, 1.418 and 1.426 s per build, no gain beyond the spread
-// between runs).  Up to 1024^2, by the pixels of a beam batch (beams x n^2),
-// as each further stream costs two launches per slice and shorter kernels, in
-// us per build on 1, 2 and 4 streams:
-//   21 beams at 256^2 (1.4 M)    339    455    765
-//   16 probes at 1024^2 (17 M)  3516   3655      -   (multislice, 4 batches)
-//   69 beams at 256^2 (4.5 M)    308    310    472
-//   69 beams at 512^2 (18 M)    1502   1374   1807
-//   305 beams at 256^2 (20 M)   1566   1408   1765
-//   1245 beams at 512^2 (326 M) 23359 22753  23269
-//   1245 beams at 1024^2 (1.3 G) 262.4, 253.9 and 249.5 ms
+// 0: by size, of a beam batch.  Each further stream costs two launches per
+// slice and shorter kernels; small batches stay on one.  Builds on 1, 2 and 4
+// streams:
+//   up to 1024^2, by pixels (items x n^2), us
+//     21 beams at 256^2 (1.4 M)      339    455    765
+//     69 beams at 256^2 (4.5 M)      308    310    472
+//     16 probes at 1024^2 (17 M)    3516   3655      -   (multislice, 4 batches)
+//     69 beams at 512^2 (18 M)      1502   1374   1807
+//     305 beams at 256^2 (20 M)     1566   1408   1765
+//     1245 beams at 512^2 (326 M)  23359  22753  23269
+//     1245 beams at 1024^2 (1.3 G)  262.4, 253.9 and 249.5 ms
+//   at 2048^2, by items, us per beam of 10 slices (a batch of 2^k items is the
+//   slow one on one stream, and its parts are not)
+//     40 beams                     219  231  236
+//     64                           219  216  222
+//     128                          228  213  216
+//     256                          248  224  217
+//     305, 1245                    223, 225 within 1%
 std::atomic<int> g_build_streams{0};
 int streams_by_size(int n, int64_t items) {
+    if (n > 1024) return items < 64 ? 1 : (items < 192 ? 2 : 4);
     const int64_t pixels = items * n * n;
-    return n > 1024 || items < 32 || pixels < (int64_t)8 << 20 ? 1 : (pixels < (int64_t)700 << 20 ? 2 : 4);
+    return items < 32 || pixels < (int64_t)8 << 20 ? 1 : (pixels < (int64_t)700 << 20 ? 2 : 4);
 }
 int build_streams_for(int n, int beams) {
     const int s = g_build_streams.load();

@@ -10,11 +10,10 @@ namespace prism {
 //   otherwise), y in [0, n) the real-space row.  One "item" is a beam
 //   (S-matrix) or a probe (multislice).  Columns are wave_col_stride(n) >= n
 //   elements apart so that the column starts do not all fall on the same
-//   power-of-two address stride.
-#ifndef PRISM_COL_PAD
-#define PRISM_COL_PAD 0
-#endif
-constexpr int wave_col_stride(int n) { return n + PRISM_COL_PAD; }
+//   power-of-two address stride at n = 2048 (row pass of 128 beams: 2.34 -> 2.10
+//   ms with 256 bytes of padding; 64, 192 and 512 bytes or more: 2.12-2.19).  At
+//   1024^2 the same padding gave 2% of the row pass (64 bytes: a quarter lost).
+constexpr int wave_col_stride(int n) { return n >= 2048 ? n + 32 : n; }
 struct PropTables {
     const float2* tw_half;   // W_{n/2}[m] = e^{-2 pi i m/(n/2)}, n/2 entries
     const float2* tw_full;   // W_n[m]     = e^{-2 pi i m/n},     n entries
