@@ -208,16 +208,35 @@ struct FftT {
 
     // LDS accessor of a transform's padded exchange buffer.
     struct RowX {
+        static constexpr bool PLANES = false;
         float2* p;
         __device__ __forceinline__ float2& operator()(int i) const { return p[pad(i)]; }
     };
-    // The same padded buffer with a compile-time stride between consecutive
-    // slots (a column of a row-major array, exchanged in place).
+    // The same as floats, half the size, with a compile-time stride between
+    // consecutive slots (a row or a column of an array, exchanged in place): real
+    // parts and imaginary parts pass one after the other.
     template <int STRIDE>
-    struct StrideX {
-        float2* p;
-        __device__ __forceinline__ float2& operator()(int i) const { return p[pad(i) * STRIDE]; }
+    struct PlaneX {
+        static constexpr bool PLANES = true;
+        float* p;
+        __device__ __forceinline__ float& operator()(int i) const { return p[pad(i) * STRIDE]; }
     };
+
+    template <int S, class X>
+    __device__ __forceinline__ static void exchange_plane(float2 (&v)[E], const float2 (&out)[E], float float2::*part,
+                                                          const X& lds, int lt) {
+        constexpr int R = radix(S), NS = ns(S), U = E / R;
+        sync();
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int j = lt + LPT * u, base = (j / NS) * NS * R + (j % NS);
+#pragma unroll
+            for (int r = 0; r < R; ++r) lds(base + r * NS) = out[u * R + r].*part;
+        }
+        sync();
+#pragma unroll
+        for (int i = 0; i < E; ++i) v[i].*part = lds(lt + LPT * i);
+    }
 
     template <int DIR, int S, class X>
     __device__ __forceinline__ static void stage(float2 (&v)[E], const X& lds, const Twiddles& tw, int lt) {
@@ -242,6 +261,10 @@ struct FftT {
             for (int u = 0; u < U; ++u)
 #pragma unroll
                 for (int r = 0; r < R; ++r) v[u + r * U] = out[u * R + r];
+        } else if constexpr (X::PLANES) {
+            exchange_plane<S>(v, out, &float2::x, lds, lt);
+            exchange_plane<S>(v, out, &float2::y, lds, lt);
+            stage<DIR, S + 1>(v, lds, tw, lt);
         } else {
             sync();
 #pragma unroll
@@ -332,7 +355,7 @@ struct FftT {
     __device__ __forceinline__ static void run(float2 (&v)[E], float2* lds, const Twiddles& tw, int lt) {
         stage<DIR, 0>(v, RowX{lds}, tw, lt);
     }
-    // The same through any exchange accessor (RowX, StrideX).
+    // The same through any exchange accessor (RowX, PlaneX).
     template <int DIR, class X>
     __device__ __forceinline__ static void run_x(float2 (&v)[E], const X& x, const Twiddles& tw, int lt) {
         stage<DIR, 0>(v, x, tw, lt);

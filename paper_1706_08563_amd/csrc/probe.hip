@@ -853,33 +853,29 @@ struct WindowBatch {
     WindowJob job[MAX_JOBS];
 };
 
-// Rows go straight from memory to their transform's registers; the window then
-// sits in LDS with an odd row stride RS of at least the padded exchange length
-// and with that many rows (more than M), so that each row transform and each
-// column transform exchanges in place, through the padded slots of its own row
-// or column: no separate exchange buffers.  The odd stride keeps the strided
-// column accesses in distinct banks.
+// Rows go straight from memory to their transform's registers and stay there;
+// LDS holds one plane of floats, M + M / 8 or M + M / 16 square, through which
+// real parts and then imaginary parts pass: the exchanges of the row transforms
+// (each in the padded slots of its own row), the transposition, the exchanges of
+// the column transforms (each in its own column), and last the intensities,
+// which are summed into bins by BL lanes each.
 //
-// Bound: LDS traffic and latency (128-point windows: LDS and VALU each busy for
-// half of the time).  A 128-point window leaves room for one workgroup per CU,
-// which therefore stays for several probes and loads the next one's rows while
-// it transforms the columns and sums the bins of this one; its transforms are
-// 16 x 8 points (one exchange instead of two).  Bins are summed by BL lanes
-// each: a 64-point window has 24-50 pixels per bin, and a wavefront per bin took
-// its 33 bins one after the other.  256 probes of 64^2: 25 -> 8.6 us; 16,384
-// of 64^2: 370 -> 216 us; 16,384 of 128^2: 1.32 -> 1.30 ms (BL = 16: 1.32, 64:
-// 1.46; 16 wavefronts of 8 x 4 x 4 points: 1.42).
+// Bound: LDS and latency.  Half the LDS of complex values gives a 128-point
+// window two workgroups per CU instead of one.  With the row stride 8 modulo 64
+// (M = 64 and 128) rows, columns and both exchanges touch every bank once.
+// 16,384 probes of 128^2: 1.30 (complex window, the next rows loaded beside the
+// columns) -> 0.64 ms; 16,384 of 64^2: 216 -> 160 us; 256 of 64^2: 8.6 us either
+// way.  128-point transforms are 16 x 8 points (one exchange).  Lanes per bin at
+// 128: 16 and 32 within 2%, 64 0.15 ms slower; a wavefront per bin took 16 us
+// more for 256 windows of 64^2.
 template <int M> struct WinFft { using type = Fft<M>; };
 template <> struct WinFft<128> { using type = FftT<128, PlanWin128>; };
 template <int M>
 struct WinCfg {
     using F = typename WinFft<M>::type;
     static constexpr int NW = M >= 64 ? 8 : 4;                // wavefronts per workgroup
-    static constexpr int BL = M >= 128 ? 32 : 8;              // lanes per bin
+    static constexpr int BL = M >= 128 ? 16 : 8;              // lanes per bin
     static constexpr int NT = 64 * NW;
-    static constexpr int RS = F::LDS | 1;                     // row stride (float2), odd
-    static constexpr int ROWS = F::LDS;                       // rows (the column exchanges use all)
-    static constexpr int PERSIST = M >= 128 ? 256 : 1 << 30;  // most workgroups of a launch
 };
 
 // Job of probe p of a launch, copied out by value (see locate).
@@ -892,83 +888,82 @@ __device__ __forceinline__ WindowJob window_job(const WindowBatch& batch, int p)
 }
 
 template <int M>
-__global__ __launch_bounds__(WinCfg<M>::NT) void k_window_detect(WindowBatch batch) {
+__global__ __launch_bounds__(WinCfg<M>::NT) __attribute__((amdgpu_waves_per_eu(4))) void k_window_detect(WindowBatch batch) {
     using C = WinCfg<M>;
     using F = typename C::F;
-    constexpr int E = F::E, LPT = F::LPT, G = 64 / LPT, NW = C::NW, NT = C::NT, RS = C::RS, BL = C::BL;
-    constexpr int NR = (M + NW * G - 1) / (NW * G);           // rows of a lane's transforms
-    __shared__ float2 buf[C::ROWS * RS];
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const int g = lane / LPT, lt = lane % LPT;
-    const int r0 = wave * G + g;                              // rows (and columns) r0 + i NW G
-    float2 next[NR][E];
-    auto load_rows = [&](int p) {
-        const WindowJob job = window_job(batch, p);
-        const float2* w = job.win + (size_t)(p - job.probe0) * M * M;
+    constexpr int E = F::E, LPT = F::LPT, G = 64 / LPT, NT = C::NT, RS = F::LDS, BL = C::BL;
+    constexpr int STEP = C::NW * G, NR = (M + STEP - 1) / STEP;   // rows (and columns) r0 + i STEP of a lane
+    __shared__ float buf[RS * RS];
+    const int tid = threadIdx.x, lane = tid & 63, lt = lane % LPT;
+    const int r0 = (tid >> 6) * G + lane / LPT;
+    const WindowJob job = window_job(batch, blockIdx.x);
+    const int p = (int)blockIdx.x - job.probe0, n_bins = job.n_bins;
+    float2 v[NR][E];
+    const float2* w = job.win + (size_t)p * M * M;
+#pragma unroll
+    for (int i = 0; i < NR; ++i)
+        if (r0 + i * STEP < M)
+#pragma unroll
+            for (int e = 0; e < E; ++e) v[i][e] = w[(r0 + i * STEP) * M + lt + LPT * e];
+    typename F::Twiddles tw;
+    tw.load(job.tw_m, lt);
+#pragma unroll
+    for (int i = 0; i < NR; ++i)
+        if (r0 + i * STEP < M)
+            F::template run_x<-1>(v[i], typename F::template PlaneX<1>{buf + (r0 + i * STEP) * RS}, tw, lt);
+    auto transpose = [&](float float2::*part) {
+        F::sync();
 #pragma unroll
         for (int i = 0; i < NR; ++i)
-            if (r0 + i * NW * G < M)
+            if (r0 + i * STEP < M)
 #pragma unroll
-                for (int e = 0; e < E; ++e) next[i][e] = w[(r0 + i * NW * G) * M + lt + LPT * e];
-    };
-    load_rows(blockIdx.x);
-    for (int pp = blockIdx.x; pp < batch.n_probes; pp += gridDim.x) {
-        const WindowJob job = window_job(batch, pp);
-        const int p = pp - job.probe0, n_bins = job.n_bins;
-        typename F::Twiddles tw;
-        tw.load(job.tw_m, lt);
-        // rows, each exchanged in its own padded row
-#pragma unroll
-        for (int i = 0; i < NR; ++i)
-            if (r0 + i * NW * G < M) {
-                float2* row = buf + (r0 + i * NW * G) * RS;
-                F::template run_x<-1>(next[i], typename F::RowX{row}, tw, lt);
-                F::sync();
-#pragma unroll
-                for (int e = 0; e < E; ++e) row[lt + LPT * e] = next[i][e];
-            }
+                for (int e = 0; e < E; ++e) buf[(r0 + i * STEP) * RS + lt + LPT * e] = v[i][e].*part;
         __syncthreads();
-        if (pp + (int)gridDim.x < batch.n_probes) load_rows(pp + gridDim.x);
-        // columns, each exchanged in its own padded column, then intensity in place
-        const float scale = 1.0f / ((float)M * (float)M * (float)M * (float)M);
-#pragma unroll 1
-        for (int c = r0; c < M; c += NW * G) {
-            float2* col = buf + c;
-            float2 v[E];
 #pragma unroll
-            for (int i = 0; i < E; ++i) v[i] = col[(lt + LPT * i) * RS];
-            F::template run_x<-1>(v, typename F::template StrideX<RS>{col}, tw, lt);
+        for (int i = 0; i < NR; ++i)
+            if (r0 + i * STEP < M)
+#pragma unroll
+                for (int e = 0; e < E; ++e) v[i][e].*part = buf[(lt + LPT * e) * RS + r0 + i * STEP];
+    };
+    transpose(&float2::x);
+    __syncthreads();                                          // the imaginary parts overwrite the real ones
+    transpose(&float2::y);
+    // from here a lane's transforms touch their own columns only
+    const float scale = 1.0f / ((float)M * (float)M * (float)M * (float)M);
+#pragma unroll
+    for (int i = 0; i < NR; ++i)
+        if (r0 + i * STEP < M) {
+            float* col = buf + r0 + i * STEP;
+            F::template run_x<-1>(v[i], typename F::template PlaneX<RS>{col}, tw, lt);
             F::sync();
 #pragma unroll
-            for (int i = 0; i < E; ++i) col[(lt + LPT * i) * RS] = make_float2(cnorm(v[i]) * scale, 0.f);
+            for (int e = 0; e < E; ++e) col[(lt + LPT * e) * RS] = cnorm(v[i][e]) * scale;
         }
-        __syncthreads();
-        if (job.diff) {
-            // the 4D output takes the same scale and accumulation as the 3D one
-            float* d = job.diff + (size_t)p * M * M;
-            for (int idx = tid; idx < M * M; idx += NT) {
-                const float v = job.scale * buf[(idx / M) * RS + idx % M].x;
-                d[idx] = job.accumulate ? d[idx] + v : v;
-            }
+    __syncthreads();
+    if (job.diff) {
+        // the 4D output takes the same scale and accumulation as the 3D one
+        float* d = job.diff + (size_t)p * M * M;
+        for (int idx = tid; idx < M * M; idx += NT) {
+            const float s = job.scale * buf[(idx / M) * RS + idx % M];
+            d[idx] = job.accumulate ? d[idx] + s : s;
         }
-        if (job.out)
-            for (int b = tid / BL; b < n_bins; b += NT / BL) {
-                float s = 0.f;
-                const int k1 = job.bin_start[b + 1];
-#pragma unroll 4
-                for (int k = job.bin_start[b] + tid % BL; k < k1; k += BL) {
-                    const int pix = job.perm[k];
-                    s += buf[(pix / M) * RS + pix % M].x;
-                }
-#pragma unroll
-                for (int off = BL / 2; off > 0; off >>= 1) s += __shfl_xor(s, off, BL);
-                if (tid % BL == 0) {
-                    float* o = job.out + (size_t)p * n_bins + b;
-                    *o = job.accumulate ? *o + job.scale * s : job.scale * s;
-                }
-            }
-        __syncthreads();                                      // the next rows overwrite the intensities
     }
+    if (job.out)
+        for (int b = tid / BL; b < n_bins; b += NT / BL) {
+            float s = 0.f;
+            const int k1 = job.bin_start[b + 1];
+#pragma unroll 4
+            for (int k = job.bin_start[b] + tid % BL; k < k1; k += BL) {
+                const int pix = job.perm[k];
+                s += buf[(pix / M) * RS + pix % M];
+            }
+#pragma unroll
+            for (int off = BL / 2; off > 0; off >>= 1) s += __shfl_xor(s, off, BL);
+            if (tid % BL == 0) {
+                float* o = job.out + (size_t)p * n_bins + b;
+                *o = job.accumulate ? *o + job.scale * s : job.scale * s;
+            }
+        }
 }
 
 template <int M>
@@ -983,8 +978,7 @@ static hipError_t window_m(const WindowArgs* jobs, int n_jobs, hipStream_t st) {
             b.n_probes += a.n_probes;
         }
         if (b.n_probes == 0) continue;
-        hipLaunchKernelGGL((k_window_detect<M>), dim3((unsigned)std::min(b.n_probes, WinCfg<M>::PERSIST)),
-                           dim3(WinCfg<M>::NT), 0, st, b);
+        hipLaunchKernelGGL((k_window_detect<M>), dim3((unsigned)b.n_probes), dim3(WinCfg<M>::NT), 0, st, b);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
