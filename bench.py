@@ -422,8 +422,10 @@ def multislice_leg(args):
     P.prism_timing_enable(False)
     kt = {k: P.prism_timing_read(c) for k, c in P.TIMING_CLASSES.items()}
     N2 = float(w.n) ** 2
-    a_ms = kt["pass_a"][0] / max(kt["pass_a"][1], 1)
-    b_ms = kt["pass_b"][0] / max(kt["pass_b"][1], 1)
+    # a batch's halves run on two streams; times per batch and slice, with
+    # launches of the other half beside them
+    launches = -(-len(xy) // batch) * g.n_slices
+    a_ms, b_ms = kt["pass_a"][0] / launches, kt["pass_b"][0] / launches
     return {"workload": w.name, "probes": len(xy), "slices": g.n_slices, "grid": w.n, "batch": batch,
             "seconds": dt, "probes_per_s": len(xy) / dt,
             "pass_a_avg_ms": a_ms, "pass_b_avg_ms": b_ms,
@@ -661,8 +663,8 @@ def main():
         return (wall_s, [a.elapsed_time(c) for a, b, c in ev], [a.elapsed_time(b) for a, b, c in ev],
                 [b.elapsed_time(c) for a, b, c in ev])
 
-    # headline: the library's default build streams (four overlapping beam
-    # parts up to 1024^2, one stream above)
+    # headline: the library's default build streams (overlapping beam parts, up
+    # to four by grid and batch size)
     log(f"timed {args.steps} steps")
     P.prism_set_build_streams(0)
     wall, step_ms, build_ms, synth_ms = run_steps(args.steps, False)
@@ -709,20 +711,21 @@ def main():
                              "avg_ms": tot / cnt}
     kernels["pass_a"]["GB_per_s"] = a_bytes / (kernels["pass_a"]["avg_ms"] * 1e-3) / 1e9
     kernels["pass_b"]["GB_per_s"] = b_bytes / (kernels["pass_b"]["avg_ms"] * 1e-3) / 1e9
-    kernels["contract"]["TFLOP_per_s"] = c_flops / (kernels["contract"]["avg_ms"] * 1e-3) / 1e12
-    if prec != P.PRISM_FP32:
-        # MFMA work: three BF16 products per complex product in split mode, one in plain BF16
-        mw = kernels["contract"]["TFLOP_per_s"] * (3 if prec == P.PRISM_SPLIT_BF16X3 else 1)
+    # of the direct sum over beams per probe, which a scan's sums over kx and
+    # then ky (two launches) replace by fewer operations
+    kernels["contract"]["TFLOP_per_s"] = c_flops / (kernels["contract"]["ms_total"] * 1e-3) / 1e12
+    if kernels["contract"]["launches_per_step"] == 1:
+        # MFMA work: BF16 products per product of each precision
+        mw = kernels["contract"]["TFLOP_per_s"] * {P.PRISM_FP32: 6, P.PRISM_SPLIT_BF16X3: 3}.get(prec, 1)
         kernels["contract"]["mfma_work_TFLOP_per_s"] = mw
         kernels["contract"]["mfma_frac_of_bf16_peak"] = mw / PEAK_BF16_TFLOPS
     kernels["pass_a"]["TFLOP_per_s"] = pass_flops(n, B, n) / (kernels["pass_a"]["avg_ms"] * 1e-3) / 1e12
     kernels["pass_b"]["TFLOP_per_s"] = pass_flops(n, B, n // 2) / (kernels["pass_b"]["avg_ms"] * 1e-3) / 1e12
     dom = max(["pass_a", "pass_b", "contract"], key=lambda k: kernels[k]["ms_total"])
     if dom == "contract":
-        peak = PEAK_FP32_TFLOPS if prec == P.PRISM_FP32 else PEAK_BF16_TFLOPS
         ach = kernels["contract"]["TFLOP_per_s"]
-        roof = {"kernel": "contract", "bound": "alu" if prec == P.PRISM_FP32 else "mfma", "achieved": ach,
-                "peak": peak, "unit": "TFLOP/s", "frac": ach / peak, "traffic": None}
+        roof = {"kernel": "contract", "bound": "mfma", "achieved": ach, "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
+                "frac": ach / PEAK_BF16_TFLOPS, "traffic": None}
     else:
         # the propagation passes are bounded either by HBM or by FP32 VALU
         # issue (the library is built without packed FP32, so one FMA per
@@ -763,7 +766,9 @@ def main():
         "p99_ms": float(np.percentile(step_ms, 99)),
         "build_ms": float(np.median(build_ms)),
         "build_ms_one_stream": float(np.median(build_ms_1)),
-        "build_streams": 4 if n <= 1024 else 1,     # the library's default for this grid
+        # the library's default for this grid and number of beams
+        "build_streams": (1 if B < 64 else 2 if B < 192 else 4) if n > 1024 else
+                         (1 if B < 32 or B * n * n < 8 << 20 else 2 if B * n * n < 700 << 20 else 4),
         "synthesis_ms": float(np.median(synth_ms)),
         "probe_plan_host_s": plan_s,
         # whole steps that also plan the scan (window corners, work tiles,

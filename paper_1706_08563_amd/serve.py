@@ -320,7 +320,8 @@ class GpuExecutor:
         self.precision = precision
         self.probe_chunk_bytes = probe_chunk_bytes
         self.build_ws_bytes = build_ws_bytes
-        # S-matrices whose split copy would exceed this are contracted in beam
+        # S-matrices whose synthesis scratch (as large as S itself) would exceed
+        # this are contracted in beam
         # chunks (prism_probe_outputs_chunked) instead of in the shared batch
         self.split_limit_bytes = split_limit_bytes
         self.jobs_per_request = jobs_per_request      # must match the scheduler's
@@ -368,7 +369,7 @@ class GpuExecutor:
             ws = max(_chunked_ws(d, p, beam_chunk) for p in plans)
         else:
             # a batch holds up to jobs_per_request chunks of this request, each
-            # with its own coefficients and windows, plus one split S
+            # with its own coefficients and windows, plus one S scratch
             per_chunk = max(p.ws_bytes for p in plans) - split_bytes
             ws = split_bytes + min(self.jobs_per_request, len(plans)) * per_chunk
         foot = (g.n_slices * g.n * g.n * 4 + d.smatrix_bytes + d.build_ws_bytes
