@@ -861,8 +861,9 @@ struct WindowBatch {
 // which are summed into bins by BL lanes each.
 //
 // Bound: LDS and latency.  Half the LDS of complex values gives a 128-point
-// window two workgroups per CU instead of one.  With the row stride 8 modulo 64
-// (M = 64 and 128) rows, columns and both exchanges touch every bank once.
+// window two workgroups per CU instead of one.  The row stride of 8 modulo 64
+// (M = 64 and 128) spreads rows and columns over all banks; conflicts take a
+// fifth of the active cycles at 128.
 // 16,384 probes of 128^2: 1.30 (complex window, the next rows loaded beside the
 // columns) -> 0.64 ms; 16,384 of 64^2: 216 -> 160 us; 256 of 64^2: 8.6 us either
 // way.  128-point transforms are 16 x 8 points (one exchange).  Lanes per bin at
