@@ -103,7 +103,7 @@ __device__ __forceinline__ bool locate(const ContractBatch& b, ContractJob& job,
 //   NP = 2 (split)  16 bits; hh, hl, lh (lo lo, ~2^-16 relative, left out).
 //   NP = 1 (BF16)   hh.
 //
-// A workgroup is one work tile (FP32: half of one) x PC = 64 probes: a wave
+// A workgroup is one work tile (or half of one) x PC = 64 probes: a wave
 // owns CB 32-pixel column blocks, 2 CB tile rows, and all probes (two 32-row
 // blocks).  A lane's S operand of a step of 8 beams is 4 beams of one pixel,
 // which it loads itself (no other wave needs them: nothing goes through LDS)
@@ -124,14 +124,17 @@ constexpr int NT = 256;               // threads per workgroup
 constexpr int PC = 64;                // probes per workgroup
 constexpr int RB = PC / 32;           // 32-probe row blocks
 constexpr int SUB = 8;                // beams per MFMA step, half a K step
-// 32-pixel column blocks (pairs of tile rows) per wave.  FP32 takes one, and
-// two workgroups per tile, so that the registers of the other hold the sum
-// of the last FLUSH K steps apart from the running total: an FP32 sum of
-// 1245 beams, 6 products each, is otherwise rounded 936 times at the size of
-// the total (2025 probes of 1245 beams: error against 64 bits 1.4e-7 on the
-// VALU, 1.7e-7 without the split total, 9e-8 with it).
-template <int NP> constexpr int CBS = NP == 3 ? 1 : 2;
-template <int NP> constexpr int SPLITS = 2 / CBS<NP>;   // workgroups per (tile, probe chunk)
+// A wave owns CB = 1 or 2 32-pixel column blocks (pairs of tile rows); with one,
+// two workgroups share a tile.  FP32 takes one, so that the registers of the
+// other hold the sum of the last FLUSH K steps apart from the running total: an
+// FP32 sum of 1245 beams, 6 products each, is otherwise rounded 936 times at the
+// size of the total (2025 probes of 1245 beams: error against 64 bits 1.4e-7 on
+// the VALU, 1.7e-7 without the split total, 9e-8 with it).  The other precisions
+// take two from MIN_BLOCKS workgroups on and one below, where two leave CUs with
+// little to do (same sums, same bits).  Split BF16, one and two: 256 probes of 69
+// beams at 256^2, the whole call, 36 and 44 us; 1600 of 305 beams at 512^2 109 and
+// 119; 3600 of 1245 beams at 1024^2 2.45 and 2.42 ms; 16,384 10.0 and 9.5 ms.
+constexpr int MIN_BLOCKS = 1024;
 template <int NP> constexpr int FLUSH = NP == 3 ? 2 : 1 << 30;
 }
 
@@ -444,16 +447,16 @@ __device__ __forceinline__ void sum_beams(ContractLds<NP>& lds, const float2* __
     }
 }
 
-template <int NP>
+template <int NP, int CB>
 __global__ __launch_bounds__(mfmac::NT) __attribute__((amdgpu_waves_per_eu(2))) void k_contract(ContractBatch batch) {
     using namespace mfmac;
-    constexpr int CB = CBS<NP>;
+    constexpr int SPLITS = 2 / CB;                    // workgroups per (tile, probe chunk)
     __shared__ ContractLds<NP> lds;
     int tile, chunk;
     ContractJob job;
     if (!locate(batch, job, tile, chunk)) return;
-    const int row0 = 8 * CB * (chunk % SPLITS<NP>);   // first tile row of this workgroup
-    chunk /= SPLITS<NP>;
+    const int row0 = 8 * CB * (chunk % SPLITS);   // first tile row of this workgroup
+    chunk /= SPLITS;
     float2* __restrict__ win = job.win;
     const int ns = job.ns, m = job.m;
     const int t0 = job.tile_start[tile], t1 = job.tile_start[tile + 1];
@@ -506,6 +509,10 @@ hipError_t launch_contract_batch(int precision, const ContractArgs* jobs, int n_
     for (int j0 = 0; j0 < n_jobs; j0 += MAX_JOBS) {
         ContractBatch b{};
         b.n_jobs = n_jobs - j0 < MAX_JOBS ? n_jobs - j0 : MAX_JOBS;
+        auto chunks_of = [](const ContractArgs& a) { return std::max(1, (a.max_per_tile + mfmac::PC - 1) / mfmac::PC); };
+        int64_t whole = 0;                                // workgroups with two column blocks
+        for (int k = 0; k < b.n_jobs; ++k) whole += (int64_t)chunks_of(jobs[j0 + k]) * jobs[j0 + k].n_tiles;
+        const bool two = precision != 0 && whole >= mfmac::MIN_BLOCKS;
         int blocks = 0;
         for (int k = 0; k < b.n_jobs; ++k) {
             const ContractArgs& a = jobs[j0 + k];
@@ -522,8 +529,7 @@ hipError_t launch_contract_batch(int precision, const ContractArgs* jobs, int n_
             job.m = a.m;
             job.ksteps = ksteps_of(a.n_beams);
             job.accumulate = a.accumulate;
-            job.chunks = std::max(1, (a.max_per_tile + mfmac::PC - 1) / mfmac::PC) *
-                         (precision == 0 ? mfmac::SPLITS<3> : mfmac::SPLITS<2>);
+            job.chunks = chunks_of(a) * (two ? 1 : 2);
             job.n_tiles = a.n_tiles;
             job.block0 = blocks;
             blocks += job.chunks * job.n_tiles;
@@ -534,11 +540,11 @@ hipError_t launch_contract_batch(int precision, const ContractArgs* jobs, int n_
         dim3 grid((unsigned)(8 * b.per_xcd));
         auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(mfmac::NT), 0, st, b); };
         if (precision == 0)
-            launch(k_contract<3>);
+            launch(k_contract<3, 1>);
         else if (precision == 1)
-            launch(k_contract<2>);
+            two ? launch(k_contract<2, 2>) : launch(k_contract<2, 1>);
         else
-            launch(k_contract<1>);
+            two ? launch(k_contract<1, 2>) : launch(k_contract<1, 1>);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }

@@ -71,3 +71,17 @@ def test_non_finite_pixel_stays_in_its_windows(P, prec):
     hit = torch.from_numpy(hit).cuda()
     assert torch.equal(got[~hit], clean[~hit])
     assert not torch.isfinite(got[hit]).flatten(1).all(1).any()
+
+
+@pytest.mark.parametrize("prec", sorted(TOL))
+def test_large_launch_repeats_small_ones(P, prec):
+    """Twelve jobs of about 96 workgroups in one launch (two column blocks per
+    wave) against each alone (one): the same sums in the same order."""
+    import torch
+    d, S, Sd = _setup(P, 0.024, 9)
+    rng = np.random.default_rng(10)
+    plans = [P.prism_probe_plan_upload(d, rng.uniform(0.0, L, size=(1500, 2))) for _ in range(12)]
+    alone = [P.prism_probe_outputs(d, Sd, plan, getattr(P, prec)) for plan in plans]
+    jobs = [(d, Sd, plan, torch.empty_like(a)) for plan, a in zip(plans, alone)]
+    for got, a in zip(P.prism_probe_outputs_batched(jobs, getattr(P, prec)), alone):
+        assert torch.equal(got, a)
