@@ -6,6 +6,7 @@
 // squared of the FFT of that exit wave is binned into detectors (Fig. 1i-k).
 #include "fft.hpp"
 #include "kernels.hpp"
+#include "launch_limits.hpp"
 
 #include <algorithm>
 #include <type_traits>
@@ -123,7 +124,7 @@ namespace mfmac {
 constexpr int NT = 256;               // threads per workgroup
 constexpr int PC = 64;                // probes per workgroup
 constexpr int RB = PC / 32;           // 32-probe row blocks
-constexpr int SUB = 8;                // beams per MFMA step, half a K step
+constexpr int SUB = SUM_PLANES;       // beams per MFMA step, half a K step
 // A wave owns CB = 1 or 2 32-pixel column blocks (pairs of tile rows); with one,
 // two workgroups share a tile.  FP32 takes one, so that the registers of the
 // other hold the sum of the last FLUSH K steps apart from the running total: an
@@ -278,7 +279,7 @@ struct BeamPipe {
     // for all loads in flight).
     __device__ __forceinline__ void load_s(int h, const float2* S, int64_t left) {
         const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<float2*>(S), (short)0, (int)max((int64_t)0, min(left, (int64_t)0x7fffffff)), 0x00020000);
+            const_cast<float2*>(S), (short)0, (int)max((int64_t)0, min(left, MAX_BUFFER_BYTES)), 0x00020000);
 #pragma unroll
         for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
@@ -782,8 +783,7 @@ size_t two_stage_cy_bytes(int64_t n_probes, int n_rows) { return (size_t)n_probe
 size_t two_stage_column_bytes(int n_rows, int ns, int m) { return (size_t)n_rows * ns * m * sizeof(float2); }
 
 int two_stage_columns(const TwoStageArgs& t) {
-    const size_t fit = t.T_bytes / two_stage_column_bytes(t.n_rows, t.ns, t.m);
-    return (int)std::max<size_t>(1, std::min<size_t>(fit, t.n_cols));
+    return two_stage_columns_per_launch(t.n_cols, t.n_rows, t.ns, t.m, t.T_bytes);
 }
 
 static TwoStage two_stage_launch(const TwoStageArgs& t, int q0, int n) {
@@ -825,6 +825,7 @@ hipError_t launch_sum_kx(int precision, const TwoStageArgs& t, int q0, int n, hi
 }
 
 hipError_t launch_sum_ky(const TwoStageArgs& t, int q0, int n, hipStream_t st) {
+    if (n > two_stage_columns(t)) return hipErrorInvalidValue;
     TwoStage a = two_stage_launch(t, q0, n);
     const int w = std::min(t.m, 128), R = 128 / w;
     a.chunks = (t.max_probes + mfmac::PC - 1) / mfmac::PC;

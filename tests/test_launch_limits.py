@@ -1,0 +1,66 @@
+"""Host arithmetic of the launch sizes (launch_limits.hpp, compiled here by the
+host compiler), over every grid, interpolation factor and aperture."""
+import ctypes
+import itertools
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_1706_08563_amd", "csrc")
+
+SHIM = """
+#include "launch_limits.hpp"
+extern "C" int columns(int n_cols, int n_rows, int ns, int m, size_t T_bytes) {
+    return prism::two_stage_columns_per_launch(n_cols, n_rows, ns, m, T_bytes);
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def limits(tmp_path_factory):
+    d = tmp_path_factory.mktemp("limits")
+    src, so = d / "shim.cpp", d / "shim.so"
+    src.write_text(SHIM)
+    subprocess.run(["g++", "-std=c++17", "-shared", "-fPIC", "-I" + CSRC, str(src), "-o", str(so)], check=True)
+    lib = ctypes.CDLL(str(so))
+    lib.columns.argtypes = [ctypes.c_int] * 4 + [ctypes.c_size_t]
+    return lib
+
+
+def _last_offset(n_cols, ns, m):
+    """Largest byte offset + 8 of a load of the second sum: value (row of the
+    tile, window column) of the eighth ky from a base at its first."""
+    w = min(m, 128)
+    return 8 * (7 * ns * n_cols * m + (128 // w - 1) * n_cols * m + (m - 1)) + 8
+
+
+def test_offsets_of_the_second_sum_stay_in_32_bits(limits):
+    grids = [(n, f) for n, f in itertools.product((64, 128, 256, 512, 1024, 2048), (1, 2, 4, 8, 16, 32))
+             if 16 <= n // 2 // f <= 512]
+    for (n, f), n_rows, cols in itertools.product(grids, (1, 9, 40, 64, 257), (1, 2, 64, 147, 255, 256, 293, 320, 4096,
+                                                                              (1 << 28) - 1)):
+        ns, m = n // 2, n // 2 // f
+        for T in (n_rows * ns * m * 8, 1 << 30, 105 << 30):
+            if T < n_rows * ns * m * 8:
+                continue                                  # a column of T fits, or the call takes the direct sum
+            got = limits.columns(cols, n_rows, ns, m, T)
+            assert 1 <= got <= cols
+            assert got * n_rows * ns * m * 8 <= T
+            assert _last_offset(got, ns, m) <= 0x7fffffff
+            # and no more launches than these bounds ask for
+            assert (got == cols or (got + 1) * n_rows * ns * m * 8 > T
+                    or _last_offset(got + 1, ns, m) + 8 * m * (got + 1) > 0x7fffffff)
+
+
+# 2048^2 at 200 A: (beams, ky rows, f, scan columns) of apertures and
+# scans whose T fits the scratch in one launch, and whose offsets do not
+@pytest.mark.parametrize("beams,n_rows,f,cols", [(1789, 47, 8, 305), (2925, 61, 8, 320), (4997, 79, 4, 160),
+                                                 (4997, 79, 2, 80)])
+def test_large_scans_take_more_launches(limits, beams, n_rows, f, cols):
+    ns, m = 1024, 1024 // f
+    T = (beams + 15) // 16 * 16 * ns * ns * 8
+    assert cols * n_rows * ns * m * 8 <= T and _last_offset(cols, ns, m) > 0x7fffffff
+    got = limits.columns(cols, n_rows, ns, m, T)
+    assert got < cols and _last_offset(got, ns, m) <= 0x7fffffff
