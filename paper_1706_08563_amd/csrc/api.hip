@@ -1306,7 +1306,7 @@ static bool two_stage_args(const prism_smatrix_desc* d, const prism_probe_plan* 
     t.T_bytes = s.off;
     if (align256(two_stage_cx_bytes(t.n_cols, t.col_steps)) + two_stage_cy_bytes(t.n_probes, t.n_rows) >
             c_operand_bytes(t.n_probes, d->n_beams) ||
-        two_stage_column_bytes(t.n_rows, t.ns, t.m) > t.T_bytes)
+        two_stage_column_bytes(t.n_rows, t.ns, t.m) > t.T_bytes || !two_stage_launchable(t))
         return false;
     // Time of the one-stage sum by its products, at what it reaches, against
     // that of the two stages by their memory traffic (S read, T written and

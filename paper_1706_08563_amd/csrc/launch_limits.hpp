@@ -26,4 +26,30 @@ inline int two_stage_columns_per_launch(int n_cols, int n_rows, int ns, int m, s
     return (int)std::max<int64_t>(1, std::min<int64_t>({(int64_t)n_cols, fit, reach}));
 }
 
+// A launch holds fewer than 2^32 threads.
+constexpr int64_t MAX_THREADS = 0xffffffff;
+inline int64_t most_blocks(int threads) { return MAX_THREADS / threads; }
+
+// Bin sums, one wavefront per (item, bin): workgroups of 4 bins per item (each
+// takes further bins in turn when they are more than 2^22), and items per launch.
+inline int bin_groups(int n_bins) { return (int)std::min<int64_t>(((int64_t)n_bins + 3) / 4, 1 << 20); }
+inline int bin_items(int n_bins) { return (int)std::min<int64_t>(most_blocks(256) / std::max(1, bin_groups(n_bins)), 1 << 24); }
+
+// Workgroups of the two-stage sum's launches.  First sum: 128-pixel tiles by 64
+// scan columns (max_cols over a tile) by row groups, enough for 4096 workgroups
+// and at least two per max_steps K steps.  Second sum: 128 window pixels by scan
+// columns by 64 probes (max_probes of a column over those pixels).
+constexpr int SUM_ROWS = 64;
+inline int64_t sum_kx_tiles(int ns, int max_cols) { return (int64_t)ns * ns / 128 * ((max_cols + SUM_ROWS - 1) / SUM_ROWS); }
+inline int sum_kx_row_groups(int64_t tiles, int n_rows, int row_steps, int max_steps) {
+    const int64_t least = ((int64_t)n_rows * row_steps + max_steps - 1) / max_steps;
+    return (int)std::min<int64_t>(n_rows, std::max<int64_t>(2 * least, std::min<int64_t>(4096 / tiles, n_rows)));
+}
+inline int64_t sum_ky_blocks(int n_cols, int ns, int m, int max_probes) {
+    const int w = std::min(m, 128), R = 128 / w;
+    return (int64_t)n_cols * (ns / R) * (m / w) * ((max_probes + SUM_ROWS - 1) / SUM_ROWS);
+}
+// Whether a launch may hold that many workgroups of 256, in 8 equal parts.
+inline bool launchable(int64_t blocks) { return (blocks + 7) / 8 * 8 <= most_blocks(256); }
+
 }  // namespace prism

@@ -122,7 +122,7 @@ __device__ __forceinline__ bool locate(const ContractBatch& b, ContractJob& job,
 // VALU: 2025 probes x 1245 beams x 128^2, 7.1 -> 2.0 ms with six BF16 products.
 namespace mfmac {
 constexpr int NT = 256;               // threads per workgroup
-constexpr int PC = 64;                // probes per workgroup
+constexpr int PC = SUM_ROWS;          // probes per workgroup
 constexpr int RB = PC / 32;           // 32-probe row blocks
 constexpr int SUB = SUM_PLANES;       // beams per MFMA step, half a K step
 // A wave owns CB = 1 or 2 32-pixel column blocks (pairs of tile rows); with one,
@@ -808,28 +808,32 @@ static TwoStage two_stage_launch(const TwoStageArgs& t, int q0, int n) {
     return a;
 }
 static hipError_t start_two_stage(void (*kernel)(TwoStage), TwoStage& a, int64_t blocks, hipStream_t st) {
-    if (blocks > 0x7ffffff0) return hipErrorInvalidValue;
+    if (!launchable(blocks)) return hipErrorInvalidValue;
     a.n_blocks = (int)blocks;
     a.per_xcd = (a.n_blocks + 7) / 8;
     hipLaunchKernelGGL(kernel, dim3((unsigned)(8 * a.per_xcd)), dim3(mfmac::NT), 0, st, a);
     return hipGetLastError();
 }
 
+bool two_stage_launchable(const TwoStageArgs& t) {
+    const int64_t tiles = sum_kx_tiles(t.ns, t.max_cols);
+    return launchable(tiles * sum_kx_row_groups(tiles, t.n_rows, ksteps_of(t.max_row_beams), MAX_STEPS)) &&
+           launchable(sum_ky_blocks(two_stage_columns(t), t.ns, t.m, t.max_probes));
+}
+
 hipError_t launch_sum_kx(int precision, const TwoStageArgs& t, int q0, int n, hipStream_t st) {
     TwoStage a = two_stage_launch(t, q0, n);
     a.chunks = (t.max_cols + mfmac::PC - 1) / mfmac::PC;
-    const int64_t tiles = (int64_t)t.ns * t.ns / 128 * a.chunks;
-    const int row_steps = ksteps_of(t.max_row_beams), least = (t.n_rows * row_steps + MAX_STEPS - 1) / MAX_STEPS;
-    a.row_groups = std::min(t.n_rows, std::max(2 * least, (int)std::min<int64_t>(4096 / tiles, t.n_rows)));
+    const int64_t tiles = sum_kx_tiles(t.ns, t.max_cols);
+    a.row_groups = sum_kx_row_groups(tiles, t.n_rows, ksteps_of(t.max_row_beams), MAX_STEPS);
     return start_two_stage(precision == 0 ? k_sum_kx<3> : k_sum_kx<2>, a, tiles * a.row_groups, st);
 }
 
 hipError_t launch_sum_ky(const TwoStageArgs& t, int q0, int n, hipStream_t st) {
     if (n > two_stage_columns(t)) return hipErrorInvalidValue;
     TwoStage a = two_stage_launch(t, q0, n);
-    const int w = std::min(t.m, 128), R = 128 / w;
     a.chunks = (t.max_probes + mfmac::PC - 1) / mfmac::PC;
-    return start_two_stage(k_sum_ky, a, (int64_t)n * (t.ns / R) * (t.m / w) * a.chunks, st);
+    return start_two_stage(k_sum_ky, a, sum_ky_blocks(n, t.ns, t.m, t.max_probes), st);
 }
 
 // ------------------------------------------------ deterministic bin sums --
@@ -1126,31 +1130,31 @@ hipError_t launch_window_batch(int m, const WindowArgs* jobs, int n_jobs, hipStr
 // that took its bins in turn.
 __global__ __launch_bounds__(WG) void k_bin_reduce(const float* __restrict__ inten, int64_t pix_per_item,
                                                    float* __restrict__ out, const int* __restrict__ perm,
-                                                   const int* __restrict__ bin_start, int n_bins, float scale,
-                                                   int accumulate) {
-    const int groups = (n_bins + 3) / 4, item = blockIdx.x / groups;
-    const int b = blockIdx.x % groups * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-    if (b >= n_bins) return;
+                                                   const int* __restrict__ bin_start, int n_bins, int groups,
+                                                   float scale, int accumulate) {
+    const int item = blockIdx.x / groups, lane = threadIdx.x & 63;
     const float* I = inten + (size_t)item * pix_per_item;
-    const int k1 = bin_start[b + 1];
-    float s = 0.f;
+    for (int64_t b = blockIdx.x % groups * 4 + (threadIdx.x >> 6); b < n_bins; b += 4 * groups) {
+        const int k1 = bin_start[b + 1];
+        float s = 0.f;
 #pragma unroll 8
-    for (int k = bin_start[b] + lane; k < k1; k += 64) s += I[perm[k]];
-    s = wave_sum(s);
-    if (lane == 0) {
-        float* o = out + (size_t)item * n_bins + b;
-        *o = accumulate ? *o + scale * s : scale * s;
+        for (int k = bin_start[b] + lane; k < k1; k += 64) s += I[perm[k]];
+        s = wave_sum(s);
+        if (lane == 0) {
+            float* o = out + (size_t)item * n_bins + b;
+            *o = accumulate ? *o + scale * s : scale * s;
+        }
     }
 }
 
 hipError_t launch_bin_reduce(const float* inten, int64_t pix_per_item, float* out, const int* perm,
                              const int* bin_start, int n_items, int n_bins, hipStream_t st, float scale,
                              int accumulate) {
-    const int groups = (n_bins + 3) / 4, most = 0x7fffff00 / groups;   // items per launch
-    for (int i = 0; i < n_items; i += most) {
-        const int n = std::min(most, n_items - i);
+    const int groups = bin_groups(n_bins), most = bin_items(n_bins);
+    for (int64_t i = 0; i < n_items; i += most) {
+        const int n = (int)std::min<int64_t>(most, n_items - i);
         hipLaunchKernelGGL(k_bin_reduce, dim3((unsigned)n * groups), dim3(WG), 0, st, inten + (size_t)i * pix_per_item,
-                           pix_per_item, out + (size_t)i * n_bins, perm, bin_start, n_bins, scale, accumulate);
+                           pix_per_item, out + (size_t)i * n_bins, perm, bin_start, n_bins, groups, scale, accumulate);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }

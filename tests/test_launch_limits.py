@@ -15,6 +15,14 @@ SHIM = """
 extern "C" int columns(int n_cols, int n_rows, int ns, int m, size_t T_bytes) {
     return prism::two_stage_columns_per_launch(n_cols, n_rows, ns, m, T_bytes);
 }
+extern "C" int groups(int n_bins) { return prism::bin_groups(n_bins); }
+extern "C" int items(int n_bins) { return prism::bin_items(n_bins); }
+extern "C" long kx(int ns, int max_cols, int n_rows, int row_steps, int max_steps) {
+    const long tiles = prism::sum_kx_tiles(ns, max_cols);
+    return tiles * prism::sum_kx_row_groups(tiles, n_rows, row_steps, max_steps);
+}
+extern "C" long ky(int n_cols, int ns, int m, int max_probes) { return prism::sum_ky_blocks(n_cols, ns, m, max_probes); }
+extern "C" int launchable(long blocks) { return prism::launchable(blocks); }
 """
 
 
@@ -26,6 +34,8 @@ def limits(tmp_path_factory):
     subprocess.run(["g++", "-std=c++17", "-shared", "-fPIC", "-I" + CSRC, str(src), "-o", str(so)], check=True)
     lib = ctypes.CDLL(str(so))
     lib.columns.argtypes = [ctypes.c_int] * 4 + [ctypes.c_size_t]
+    lib.kx.restype = lib.ky.restype = ctypes.c_long
+    lib.launchable.argtypes = [ctypes.c_long]
     return lib
 
 
@@ -64,3 +74,31 @@ def test_large_scans_take_more_launches(limits, beams, n_rows, f, cols):
     assert cols * n_rows * ns * m * 8 <= T and _last_offset(cols, ns, m) > 0x7fffffff
     got = limits.columns(cols, n_rows, ns, m, T)
     assert got < cols and _last_offset(got, ns, m) <= 0x7fffffff
+
+
+def test_bin_sums_hold_fewer_than_2_32_threads(limits):
+    for n_bins in (1, 4, 62, 4095, 4096, 4097, 1 << 20, (1 << 22) - 1, 1 << 22, (1 << 22) + 5, 1 << 26, 0x7fffffff):
+        g, most = limits.groups(n_bins), limits.items(n_bins)
+        assert g >= 1 and most >= 1 and g * most * 256 < 1 << 32
+        assert 4 * g >= n_bins or g == 1 << 20              # all bins at once, or 2^22 at a time
+    assert limits.items(4096) < 16384                       # 16,384 windows of 4096 bins: two launches
+
+
+def test_two_stage_launches_hold_fewer_than_2_32_threads(limits):
+    assert limits.launchable((1 << 24) - 8) and not limits.launchable((1 << 24) - 7)
+    # the benchmark scans, and one column of very many probes beside 256 others
+    assert limits.launchable(limits.ky(256, 1024, 128, 256)) and limits.launchable(limits.kx(1024, 256, 39, 3, 256))
+    assert not limits.launchable(limits.ky(257, 512, 128, 20000))
+    assert not limits.launchable(limits.kx(1024, 65535, 39, 3, 256))
+    # a row group's K steps fit its table
+    for n_rows in (1, 2, 9, 39, 79, 257):
+        for row_steps in (1, 3, 17, 128):
+            for tiles in (2, 32, 8192):
+                got = _row_groups(limits, tiles, n_rows, row_steps)
+                assert 1 <= got <= n_rows
+                assert -(-n_rows // got) * row_steps <= 256
+
+
+def _row_groups(limits, tiles, n_rows, row_steps):
+    ns = {2: 16, 32: 64, 8192: 1024}[tiles]
+    return limits.kx(ns, 1, n_rows, row_steps, 256) // tiles
