@@ -387,13 +387,16 @@ constexpr int MIN_PER_COLUMN = 8;
 static void scan_columns(const double* xy, int64_t n_probes, int ns, int M, ProbeHost& h) {
     const int64_t most = n_probes / MIN_PER_COLUMN;
     if (most < 1) return;
-    size_t size = 64;
-    while ((int64_t)size < 4 * most) size *= 2;
+    int lg = 6;
+    while (((int64_t)1 << lg) < 4 * most) ++lg;
+    const size_t size = (size_t)1 << lg;
     std::vector<int> slot(size, -1), column(n_probes), head;   // open addressing on the bits of x
     for (int64_t p = 0; p < n_probes; ++p) {
         uint64_t bits;
         std::memcpy(&bits, &xy[2 * p], sizeof bits);
-        size_t at = (size_t)((bits * 0x9E3779B97F4A7C15ull) >> 20) & (size - 1);
+        // the top bits of the product: positions on a lattice of binary fractions
+        // have zeros in their low bits, and so have the product's middle ones
+        size_t at = (size_t)(((bits ^ bits >> 32) * 0x9E3779B97F4A7C15ull) >> (64 - lg));
         while (slot[at] >= 0 && std::memcmp(&xy[2 * head[slot[at]]], &bits, sizeof bits) != 0) at = (at + 1) & (size - 1);
         if (slot[at] < 0) {
             if ((int64_t)head.size() == most) return;
