@@ -1309,12 +1309,16 @@ static bool two_stage_args(const prism_smatrix_desc* d, const prism_probe_plan* 
     t.T_bytes = s.off;
     if (align256(two_stage_cx_bytes(t.n_cols, t.col_steps)) + two_stage_cy_bytes(t.n_probes, t.n_rows) >
             c_operand_bytes(t.n_probes, d->n_beams) ||
-        two_stage_column_bytes(t.n_rows, t.ns, t.m) > t.T_bytes || !two_stage_launchable(t))
+        two_stage_column_bytes(t.n_rows, t.ns, t.m) > t.T_bytes)
         return false;
+    const int64_t blocks = two_stage_blocks(t);
+    if (blocks < 0) return false;
     // Time of the one-stage sum by its products, at what it reaches, against
     // that of the two stages by their memory traffic (S read, T written and
-    // read) and two more launches.  Measured calls, one and two stages (FP32;
-    // split BF16), in us:
+    // read) and two more launches, but no less than 3 ns for each workgroup, most
+    // of which are empty when one column has many more probes than the others (256
+    // columns of 8 probes and one of 20,000: 41 million, 128 ms; one stage 18 ms in
+    // split BF16).  Measured calls, one and two stages (FP32; split BF16), in us:
     //   256 probes, 69 beams, 64^2 windows at 256^2      47, 61
     //   400 probes, 305 beams, 64^2 windows at 512^2     84, 130;   62, 122
     //   144 probes, 1245 beams, 128^2 windows at 512^2   253, 274;  161, 255
@@ -1323,7 +1327,7 @@ static bool two_stage_args(const prism_smatrix_desc* d, const prism_probe_plan* 
     //   16,384 probes, 1245 beams, 128^2 at 1024^2       (split) 8100, 3650
     const double s_bytes = (double)d->smatrix_bytes, t_bytes = (double)t.n_cols * two_stage_column_bytes(t.n_rows, t.ns, t.m);
     const double one = (double)plan->n_entries * 256 * 8 * d->n_beams / (precision == PRISM_FP32 ? 130e12 : 230e12);
-    const double two = 20e-6 + (s_bytes + 2 * t_bytes) / 4e12;
+    const double two = 20e-6 + std::max((s_bytes + 2 * t_bytes) / 4e12, 3e-9 * (double)blocks);
     if (one < 1.15 * two) return false;
     t.col_xy = reinterpret_cast<const double2*>(pb + c.col_xy);
     t.col_corner = reinterpret_cast<const int*>(pb + c.col_corner);

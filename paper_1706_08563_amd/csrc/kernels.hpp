@@ -121,9 +121,9 @@ hipError_t launch_two_stage_operands(const TwoStageArgs& t, hipStream_t st);
 // Scan columns per pair of launches (whose T fits), and the two sums for
 // columns q0 .. q0 + n - 1.
 int two_stage_columns(const TwoStageArgs& t);
-// Whether launches hold the workgroups of both sums (columns or tiles with very
-// many of the probes can ask for more).
-bool two_stage_launchable(const TwoStageArgs& t);
+// Workgroups of both sums' launches over the first columns, or -1 when a launch
+// does not hold them (every column gets as many as the one with most probes).
+int64_t two_stage_blocks(const TwoStageArgs& t);
 hipError_t launch_sum_kx(int precision, const TwoStageArgs& t, int q0, int n, hipStream_t st);
 hipError_t launch_sum_ky(const TwoStageArgs& t, int q0, int n, hipStream_t st);
 
