@@ -24,6 +24,7 @@
 #include <vector>
 
 #include "kernels.hpp"
+#include "synth_route.hpp"
 #include "prism.h"
 
 using namespace prism;
@@ -1313,22 +1314,11 @@ static bool two_stage_args(const prism_smatrix_desc* d, const prism_probe_plan* 
         return false;
     const int64_t blocks = two_stage_blocks(t);
     if (blocks < 0) return false;
-    // Time of the one-stage sum by its products, at what it reaches, against
-    // that of the two stages by their memory traffic (S read, T written and
-    // read) and two more launches, but no less than 3 ns for each workgroup, most
-    // of which are empty when one column has many more probes than the others (256
-    // columns of 8 probes and one of 20,000: 41 million, 128 ms; one stage 18 ms in
-    // split BF16).  Measured calls, one and two stages (FP32; split BF16), in us:
-    //   256 probes, 69 beams, 64^2 windows at 256^2      47, 61
-    //   400 probes, 305 beams, 64^2 windows at 512^2     84, 130;   62, 122
-    //   144 probes, 1245 beams, 128^2 windows at 512^2   253, 274;  161, 255
-    //   900 probes, 1245 beams, 128^2 windows at 1024^2  1502, 1067;  917, 1005
-    //   16,384 probes, 305 beams, 64^2 windows at 256^2  1669, 778;  1050, 770
-    //   16,384 probes, 1245 beams, 128^2 at 1024^2       (split) 8100, 3650
-    const double s_bytes = (double)d->smatrix_bytes, t_bytes = (double)t.n_cols * two_stage_column_bytes(t.n_rows, t.ns, t.m);
-    const double one = (double)plan->n_entries * 256 * 8 * d->n_beams / (precision == PRISM_FP32 ? 130e12 : 230e12);
-    const double two = 20e-6 + std::max((s_bytes + 2 * t_bytes) / 4e12, 3e-9 * (double)blocks);
-    if (one < 1.15 * two) return false;
+    const int step = two_stage_columns(t);
+    const SynthSizes z{precision == PRISM_FP32, plan->n_probes, d->n_beams, plan->n_entries, plan->n_tiles,
+                       plan->max_per_tile, t.n_cols, (t.n_cols + step - 1) / step, t.n_rows, t.ns, t.m, t.max_probes,
+                       blocks, (double)d->smatrix_bytes};
+    if (!two_stage_route(z)) return false;
     t.col_xy = reinterpret_cast<const double2*>(pb + c.col_xy);
     t.col_corner = reinterpret_cast<const int*>(pb + c.col_corner);
     t.col_start = reinterpret_cast<const int*>(pb + c.col_start);
