@@ -447,7 +447,7 @@ int prism_detector_default_bins(const prism_grid* grid, double E0, double dalpha
 #define PRISM_K_WINDOW         6   /* window FFT, |Psi|^2, detector sums */
 #define PRISM_K_POTENTIAL      7   /* projected potential */
 #define PRISM_K_BIN_REDUCE     8   /* multislice detector sums */
-#define PRISM_K_SPLIT          9   /* none: the contraction splits the S-matrix itself */
+#define PRISM_K_SPLIT          9   /* S-matrix to BF16 records (large calls in plain BF16) */
 #define PRISM_K_FIRST         10   /* first slice of an S-matrix build (plane waves from the row spectrum) */
 #define PRISM_TIMING_CLASSES  11
 

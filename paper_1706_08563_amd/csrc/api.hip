@@ -1329,11 +1329,17 @@ static bool two_stage_args(const prism_smatrix_desc* d, const prism_probe_plan* 
     return true;
 }
 
+// (work tile, probe) pairs of windows that fill their tiles.
+static int64_t exact_entries(const prism_probe_plan* plan, const prism_smatrix_desc* d) {
+    return plan->n_probes * (d->m_win / 16) * (d->m_win / 16);
+}
+
 // Probe synthesis for several (S-matrix, probe plan) jobs on one stream:
-// coefficients per job, one contraction launch for all jobs, one window launch
-// per window side.
+// coefficients per job, one contraction launch for all jobs (in plain BF16 a
+// second one for the jobs whose S-matrix is converted first, once for all of
+// them), one window launch per window side.
 static int synth_run(const prism_probe_job* jobs, int n_jobs, int precision, void* ws, hipStream_t st) {
-    std::vector<ContractArgs> ca;
+    std::vector<ContractArgs> ca[2];               // from S, from its BF16 records
     std::vector<std::vector<WindowArgs>> wa(10);   // by log2(m)
     Carve c(ws);
     std::vector<SynthJobDev> jd(n_jobs);
@@ -1343,6 +1349,27 @@ static int synth_run(const prism_probe_job* jobs, int n_jobs, int precision, voi
         const int j = first_with_same_s(jobs, k);
         scratch[k] = j < k ? scratch[j]
                            : reinterpret_cast<float2*>(s_scratch_carve(jobs[k].desc, jobs[k].desc->n_beams, c));
+    }
+    std::vector<char> records(n_jobs, 0);
+    for (int k = 0; k < n_jobs && precision == PRISM_BF16; ++k) {
+        const int j = first_with_same_s(jobs, k);
+        const prism_smatrix_desc* d = jobs[k].desc;
+        if (j == k) {
+            int64_t entries = 0, exact = 0, tiles = 0;
+            for (int i = k; i < n_jobs; ++i)
+                if (first_with_same_s(jobs, i) == k) {
+                    entries += jobs[i].plan->n_entries;
+                    exact += exact_entries(jobs[i].plan, jobs[i].desc);
+                    tiles += jobs[i].plan->n_tiles;
+                }
+            records[k] = bf16_records_route(entries, exact, tiles, d->n_beams, d->ns);
+            if (records[k])
+                HIP_TRY(timed(PRISM_K_SPLIT, st, [&] {
+                    return launch_bf16_records(static_cast<const float2*>(jobs[k].S), scratch[k], d->n_beams, d->ns, st);
+                }));
+        } else {
+            records[k] = records[j];
+        }
     }
     for (int k = 0; k < n_jobs; ++k) {
         const prism_probe_job& jb = jobs[k];
@@ -1391,11 +1418,14 @@ static int synth_run(const prism_probe_job* jobs, int n_jobs, int precision, voi
         HIP_TRY(timed(PRISM_K_COEFFICIENTS, st, [&] {
             return launch_coefficients(precision, jd[k].C, xy, beams, aberr, P, B, inv_L, amp, st);
         }));
-        ca.push_back(ContractArgs{jd[k].C, static_cast<const float2*>(jb.S), jd[k].win, tstart, tprobes, torigin, corner, plan->n_tiles,
-                                  plan->max_per_tile, B, d->ns, M});
+        ca[records[k]].push_back(ContractArgs{jd[k].C, records[k] ? scratch[k] : jb.S, jd[k].win, tstart, tprobes, torigin,
+                                              corner, plan->n_tiles, plan->max_per_tile, B, d->ns, M});
     }
-    if (!ca.empty())
-        HIP_TRY(timed(PRISM_K_CONTRACT, st, [&] { return launch_contract_batch(precision, ca.data(), (int)ca.size(), st); }));
+    for (int r = 0; r < 2; ++r)
+        if (!ca[r].empty())
+            HIP_TRY(timed(PRISM_K_CONTRACT, st, [&] {
+                return launch_contract_batch(precision, ca[r].data(), (int)ca[r].size(), st, r == 1);
+            }));
     for (int lg = 0; lg < 10; ++lg)
         if (!wa[lg].empty())
             HIP_TRY(timed(PRISM_K_WINDOW, st, [&] { return launch_window_batch(1 << lg, wa[lg].data(), (int)wa[lg].size(), st); }));
@@ -1846,21 +1876,21 @@ int prism_build_smatrix_streaming(const prism_smatrix_desc* d, const float* V_ho
 // --------------------------------------------------- streaming synthesis --
 struct StreamSynthDev {
     float2* Sst[2];
-    void* C;
+    void *C, *records;
     float2* win;
     float* inten;
 };
 
 // Beam-chunked synthesis layout: two chunk slots when S is streamed from
-// host memory (none when S is device-resident), the coefficients of one
-// chunk, the windows of all probes.
+// host memory (none when S is device-resident), the coefficients and BF16
+// records of one chunk, the windows of all probes.
 static void stream_synth_carve(Carve& c, const prism_smatrix_desc* d, const prism_probe_plan* plan, int chunk,
                                bool slots, StreamSynthDev& m) {
     const size_t P = (size_t)std::max<int64_t>(plan->n_probes, 1), M = d->m_win;
     m.Sst[0] = slots ? c.take<float2>((size_t)chunk * d->ns * d->ns) : nullptr;
     m.Sst[1] = slots ? c.take<float2>((size_t)chunk * d->ns * d->ns) : nullptr;
     m.C = c.take<char>(c_operand_bytes((int64_t)P, chunk));
-    s_scratch_carve(d, chunk, c);
+    m.records = s_scratch_carve(d, chunk, c);
     m.win = c.take<float2>(P * M * M);
     m.inten = M > 128 ? c.take<float>(P * M * M) : nullptr;
 }
@@ -1936,9 +1966,13 @@ static int synth_chunked(const prism_smatrix_desc* d, const void* S, const prism
         HIP_TRY(timed(PRISM_K_COEFFICIENTS, st, [&] {
             return launch_coefficients(precision, m.C, xy, beams + c0, ab, P, nb, inv_L, amp, st);
         }));
-        ContractArgs ca{m.C, chunk, m.win, tstart, tprobes, torigin, corner, plan->n_tiles, plan->max_per_tile, nb,
-                        d->ns, M, ci > 0 ? 1 : 0};
-        HIP_TRY(timed(PRISM_K_CONTRACT, st, [&] { return launch_contract_batch(precision, &ca, 1, st); }));
+        const bool records = precision == PRISM_BF16 &&
+                             bf16_records_route(plan->n_entries, exact_entries(plan, d), plan->n_tiles, nb, d->ns);
+        if (records)
+            HIP_TRY(timed(PRISM_K_SPLIT, st, [&] { return launch_bf16_records(chunk, m.records, nb, d->ns, st); }));
+        ContractArgs ca{m.C, records ? m.records : chunk, m.win, tstart, tprobes, torigin, corner, plan->n_tiles,
+                        plan->max_per_tile, nb, d->ns, M, ci > 0 ? 1 : 0};
+        HIP_TRY(timed(PRISM_K_CONTRACT, st, [&] { return launch_contract_batch(precision, &ca, 1, st, records); }));
         // a streamed slot is free again once its chunk has been read
         if (streamed) HIP_TRY(hipEventRecord(r.freed[k], st));
         if (streamed) r.used[k] = true;

@@ -75,10 +75,10 @@ hipError_t launch_coefficients(int precision, void* C, const double2* xy, const 
 // Windowed contraction of one probe set: win[p][v][u] = sum_b C[p][b] S[b][pix]
 // over the plan's work tiles (16 x 16 pixels from tile_origin, periodic).
 // C is the precision's operand (launch_coefficients), S complex64
-// [n_beams][ns][ns].
+// [n_beams][ns][ns], or with `records` its BF16 records (PRISM_BF16, same sums).
 struct ContractArgs {
     const void* C;
-    const float2* S;
+    const void* S;
     float2* win;
     const int* tile_start;
     const int* tile_probes;
@@ -90,7 +90,9 @@ struct ContractArgs {
 // Probes per workgroup of the contraction (the plan's work-tile cost unit).
 int contract_probe_chunk();
 // All jobs in as few launches as possible (one per 24 jobs).
-hipError_t launch_contract_batch(int precision, const ContractArgs* jobs, int n_jobs, hipStream_t st);
+hipError_t launch_contract_batch(int precision, const ContractArgs* jobs, int n_jobs, hipStream_t st, bool records = false);
+size_t bf16_record_bytes(int n_beams, int ns);
+hipError_t launch_bf16_records(const float2* S, void* records, int n_beams, int ns, hipStream_t st);
 
 // The same windows by sums over kx, per distinct x of the probes ("scan
 // column"), then over ky (PRISM_FP32 and PRISM_SPLIT_BF16X3).

@@ -47,7 +47,7 @@ constexpr int TILE = 16;
 // Work of one (request's) probe synthesis inside a batched contraction launch.
 struct ContractJob {
     const void* C;            // coefficients (k_coefficients)
-    const float2* S;          // S-matrix: complex64 [n_beams][ns][ns]
+    const void* S;            // S-matrix: complex64 [n_beams][ns][ns], or its BF16 records
     float2* win;              // [n_probes][m][m]
     const int* tile_start;    // [n_tiles + 1]
     const int* tile_probes;
@@ -228,6 +228,37 @@ hipError_t launch_coefficients(int precision, void* C, const double2* xy, const 
     return hipGetLastError();
 }
 
+// S as BF16 records, 32 bytes per (step of 8 beams, pixel): the words (re | im <<
+// 16) of its beams, zero past the last.  A thread makes one record, a wave 2 KB.
+// For large sums in plain BF16 (bf16_records_route): a lane's operand of a step is
+// then one load of 16 bytes in runs of 512, where S takes four of 8 in runs of
+// 128, most of which lie across two lines.  Bound: HBM traffic, S read and half as
+// much written (1245 beams at 1024^2 0.66 ms, 5.9 TB/s).  16,384 probes of 128^2:
+// contraction 4.9 -> 3.1 ms, the call 5.8 -> 4.4.
+__global__ __launch_bounds__(WG) void k_bf16_records(const float2* __restrict__ S, u32x4* __restrict__ rec, int n_beams,
+                                                     int plane) {
+    const int pix = blockIdx.x * WG + threadIdx.x, step = blockIdx.y;
+    if (pix >= plane) return;
+    u32x4 w[2];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        const int b = step * 8 + j;
+        const float2 v = b < n_beams ? S[(size_t)b * plane + pix] : make_float2(0.f, 0.f);
+        w[j / 4][j % 4] = pack_bf16(v.x, v.y);
+    }
+    u32x4* out = rec + ((size_t)step * plane + pix) * 2;
+    out[0] = w[0];
+    out[1] = w[1];
+}
+
+size_t bf16_record_bytes(int n_beams, int ns) { return (size_t)ksteps_of(n_beams) * KSTEP * ns * ns * 4; }
+hipError_t launch_bf16_records(const float2* S, void* records, int n_beams, int ns, hipStream_t st) {
+    const int plane = ns * ns;
+    hipLaunchKernelGGL(k_bf16_records, dim3((unsigned)((plane + WG - 1) / WG), 2u * ksteps_of(n_beams)), dim3(WG), 0, st, S,
+                       static_cast<u32x4*>(records), n_beams, plane);
+    return hipGetLastError();
+}
+
 // LDS of a contraction workgroup, C operand in NA parts.
 template <int NA>
 struct ContractLds {
@@ -243,13 +274,17 @@ struct ContractLds {
 __device__ __forceinline__ int sum_row(int rb, int r, int half) { return 32 * rb + (r & 3) + 8 * (r >> 2) + 4 * half; }
 
 // Registers and steps of the pipelined product of C (NA parts, through LDS)
-// and S (NB parts, CB 32-pixel column blocks of the wave).
-template <int NA, int NB, int CB>
+// and S (NB parts, CB 32-pixel column blocks of the wave).  RECS: S comes as the
+// BF16 records of k_bf16_records instead of complex64 planes.
+template <int NA, int NB, int CB, bool RECS = false>
 struct BeamPipe {
+    static_assert(!RECS || NB == 1, "records hold one part");
     static constexpr int NCH = NA * 4, LP = ContractLds<NA>::LP, NT = mfmac::NT;
     static constexpr int CW = NA == 3 ? 2 : NA, NCP = NA == 3 ? 1 : NA;
-    int voff[CB][4];
-    float2 raw[2][CB][4];                         // S of the two halves of a K step, in flight
+    static constexpr int NL = RECS ? 1 : 4;       // loads of a lane's 4 beams
+    using Raw = std::conditional_t<RECS, u32x4, float2>;
+    int voff[CB][NL];
+    Raw raw[2][CB][NL];                           // S of the two halves of a K step, in flight
     u32x4 B[2][NB][CB];                           // the same converted
     u32x4 creg[CW];
     const u32x4* cptr[NCP];
@@ -265,7 +300,9 @@ struct BeamPipe {
 #pragma unroll
         for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) voff[cb][j] = pix[cb] * (int)sizeof(float2) + (4 * half + j) * plane_bytes;
+            for (int j = 0; j < NL; ++j)
+                voff[cb][j] = RECS ? (2 * pix[cb] + half) * (int)sizeof(u32x4)
+                                   : pix[cb] * (int)sizeof(float2) + (4 * half + j) * plane_bytes;
 #pragma unroll
         for (int j = 0; j < NCP; ++j) {
             const int q = max(lds.idx[NA == 3 ? tid / 4 : (tid + j * NT) / NCH], 0);
@@ -277,25 +314,34 @@ struct BeamPipe {
     // bytes from the start of the step), so that beams past it read as zero
     // and the loop holds no branch around a load (each would end in a wait
     // for all loads in flight).
-    __device__ __forceinline__ void load_s(int h, const float2* S, int64_t left) {
+    __device__ __forceinline__ void load_s(int h, const void* S, int64_t left) {
         const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<float2*>(S), (short)0, (int)max((int64_t)0, min(left, MAX_BUFFER_BYTES)), 0x00020000);
+            const_cast<void*>(S), (short)0, (int)max((int64_t)0, min(left, MAX_BUFFER_BYTES)), 0x00020000);
 #pragma unroll
         for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
-                raw[h][cb][j] = __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(rs, voff[cb][j], 0, 0));
+            for (int j = 0; j < NL; ++j) {
+                if constexpr (RECS)
+                    raw[h][cb][j] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, voff[cb][j], 0, 0));
+                else
+                    raw[h][cb][j] = __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(rs, voff[cb][j], 0, 0));
+            }
     }
     __device__ __forceinline__ void convert_s(int h) {
 #pragma unroll
-        for (int cb = 0; cb < CB; ++cb)
+        for (int cb = 0; cb < CB; ++cb) {
+            if constexpr (RECS) {
+                B[h][0][cb] = raw[h][cb][0];
+            } else {
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                unsigned int w[NB];
-                split_parts<NB>(raw[h][cb][j].x, raw[h][cb][j].y, w);
+                for (int j = 0; j < 4; ++j) {
+                    unsigned int w[NB];
+                    split_parts<NB>(raw[h][cb][j].x, raw[h][cb][j].y, w);
 #pragma unroll
-                for (int part = 0; part < NB; ++part) B[h][part][cb][j] = w[part];
+                    for (int part = 0; part < NB; ++part) B[h][part][cb][j] = w[part];
+                }
             }
+        }
     }
     // Ends the conversion of half h here (not sunk to where its results are
     // used): the loads that follow reuse its registers and are not moved down.
@@ -379,9 +425,9 @@ struct Sums {
 // of C[lds.idx[row]][beam] S[beam][pix]: one lane's pixels are pix[cb]; C rows
 // are `stride` records apart; `two`: the second row block holds rows; every
 // FLUSH K steps are summed by themselves.  Called by all threads of the
-// workgroup, lds.idx written and synchronised.
-template <int NP, int CB, int FLUSH>
-__device__ __forceinline__ void sum_beams(ContractLds<NP>& lds, const float2* __restrict__ S, size_t plane, int n_beams,
+// workgroup, lds.idx written and synchronised.  RECS: S as BF16 records.
+template <int NP, int CB, int FLUSH, bool RECS = false>
+__device__ __forceinline__ void sum_beams(ContractLds<NP>& lds, const void* __restrict__ S, size_t plane, int n_beams,
                                           const int (&pix)[CB], const u32x4* __restrict__ C, int stride, bool two,
                                           Sums<CB>& sum) {
     using namespace mfmac;
@@ -394,11 +440,16 @@ __device__ __forceinline__ void sum_beams(ContractLds<NP>& lds, const float2* __
         clear(sum.r);
         clear(sum.i);
     }
-    BeamPipe<NP, NP, CB> pipe;
+    BeamPipe<NP, NP, CB, RECS> pipe;
     pipe.init(lds, pix, plane_bytes, C, stride);
     auto load_s = [&](int k, int h) {
-        const int b0 = min(k * KSTEP + h * SUB, n_beams);
-        pipe.load_s(h, S + (size_t)b0 * plane, (int64_t)(n_beams - b0) * plane_bytes);
+        if constexpr (RECS) {
+            const int step = min(2 * k + h, 2 * K - 1);
+            pipe.load_s(h, static_cast<const u32x4*>(S) + (size_t)step * plane * 2, (int64_t)plane * 32);
+        } else {
+            const int b0 = min(k * KSTEP + h * SUB, n_beams);
+            pipe.load_s(h, static_cast<const float2*>(S) + (size_t)b0 * plane, (int64_t)(n_beams - b0) * plane_bytes);
+        }
     };
     pipe.load_c(0);
     load_s(0, 0);
@@ -448,7 +499,7 @@ __device__ __forceinline__ void sum_beams(ContractLds<NP>& lds, const float2* __
     }
 }
 
-template <int NP, int CB>
+template <int NP, int CB, bool RECS = false>
 __global__ __launch_bounds__(mfmac::NT) __attribute__((amdgpu_waves_per_eu(2))) void k_contract(ContractBatch batch) {
     using namespace mfmac;
     constexpr int SPLITS = 2 / CB;                    // workgroups per (tile, probe chunk)
@@ -480,7 +531,7 @@ __global__ __launch_bounds__(mfmac::NT) __attribute__((amdgpu_waves_per_eu(2))) 
         pix[cb] = py[cb] * ns + px;
     }
     Sums<CB> sum;
-    sum_beams<NP, CB, FLUSH<NP>>(lds, job.S, (size_t)ns * ns, job.n_beams, pix, static_cast<const u32x4*>(job.C),
+    sum_beams<NP, CB, FLUSH<NP>, RECS>(lds, job.S, (size_t)ns * ns, job.n_beams, pix, static_cast<const u32x4*>(job.C),
                                  job.ksteps, np > 32, sum);
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb)
@@ -506,7 +557,7 @@ __global__ __launch_bounds__(mfmac::NT) __attribute__((amdgpu_waves_per_eu(2))) 
 
 int contract_probe_chunk() { return mfmac::PC; }
 
-hipError_t launch_contract_batch(int precision, const ContractArgs* jobs, int n_jobs, hipStream_t st) {
+hipError_t launch_contract_batch(int precision, const ContractArgs* jobs, int n_jobs, hipStream_t st, bool records) {
     for (int j0 = 0; j0 < n_jobs; j0 += MAX_JOBS) {
         ContractBatch b{};
         b.n_jobs = n_jobs - j0 < MAX_JOBS ? n_jobs - j0 : MAX_JOBS;
@@ -544,6 +595,8 @@ hipError_t launch_contract_batch(int precision, const ContractArgs* jobs, int n_
             launch(k_contract<3, 1>);
         else if (precision == 1)
             two ? launch(k_contract<2, 2>) : launch(k_contract<2, 1>);
+        else if (records)
+            two ? launch(k_contract<1, 2, true>) : launch(k_contract<1, 1, true>);
         else
             two ? launch(k_contract<1, 2>) : launch(k_contract<1, 1>);
         hipError_t e = hipGetLastError();

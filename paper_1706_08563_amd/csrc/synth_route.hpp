@@ -1,4 +1,5 @@
-// synth_route.hpp -- which calls take the two-stage probe sum (plain host C++).
+// synth_route.hpp -- which calls take the two-stage probe sum, and which plain BF16
+// calls convert S first (plain host C++).
 #pragma once
 #include <algorithm>
 #include <cstdint>
@@ -59,6 +60,32 @@ inline bool two_stage_route(const SynthSizes& z) {
     if (products < 1.15 * traffic) return false;
     const double one = one_stage_seconds(z), part = z.t_bytes() > 3 * z.window_bytes() ? 0.1 : 0.35;
     return two_stage_seconds(z) <= one + std::max(std::min(one / 2, 100e-6), part * one);
+}
+
+// Whether plain BF16 converts S to records first (1.5 times S in traffic, then a
+// quarter of the load instructions and 3/5 of the cache lines per product): by how
+// often each S value is used, and whether the windows fill their work tiles exactly
+// (n_entries = exact_entries), as for scans on whole pixels, whose direct sum is
+// slowed more by rows of 128 bytes that lie across two lines.  Measured, from S and
+// with records, us:
+//   uses (products per pixel of S) with full tiles
+//       64   1024 probes, 1245 beams at 1024^2        733, 1026
+//      256   4096 at 1024^2                          1806, 1648
+//     1024   16,384 at 1024^2                        5813, 4435;   65,536 at 2048^2  24693, 17863
+//     4096   16,384 at 512^2                         5073, 3743
+//   with part-filled tiles
+//      281   3600 anywhere at 1024^2                 1545, 1752
+//      632   2025 on a 45 x 45 scan at 512^2          761, 806
+//     1278   16,384 anywhere at 1024^2               5749, 5377
+//   small sums do not pay for the launch: 4096 probes, 69 beams at 64^2 (2e9
+//   operations) 31, 34; at 256^2 (6e10) 158, 152.
+//   and full tiles of a part of S (n_tiles below those of the grid) count as the
+//   others do: 8192 probes at one place, 1245 beams at 1024^2 (512) 2099, 2359;
+//   16,384 within 5 of 100 A (1274) 7856, 6607.
+inline bool bf16_records_route(int64_t n_entries, int64_t exact_entries, int64_t n_tiles, int64_t n_beams, int64_t ns) {
+    const double products = (double)n_entries * 256, uses = products / ((double)ns * ns);
+    const bool full = n_entries == exact_entries && n_tiles * 256 >= ns * ns;
+    return uses >= (full ? 200 : 900) && products * 8 * n_beams >= 3e10;
 }
 
 }  // namespace prism

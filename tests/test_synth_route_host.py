@@ -23,6 +23,9 @@ extern "C" int two_stages(int fp32, long probes, long beams, long entries, long 
     return prism::two_stage_route({(bool)fp32, probes, beams, entries, tiles, per_tile, cols, (cols + step - 1) / step, rows,
                                    ns, m, max_probes, blocks, s_bytes});
 }
+extern "C" int records(long entries, long exact, long tiles, long beams, long ns) {
+    return prism::bf16_records_route(entries, exact, tiles, beams, ns);
+}
 """
 
 
@@ -32,7 +35,9 @@ def rule(tmp_path_factory):
     src, so = d / "shim.cpp", d / "shim.so"
     src.write_text(SHIM)
     subprocess.run(["g++", "-std=c++17", "-shared", "-fPIC", "-I" + CSRC, str(src), "-o", str(so)], check=True)
-    f = ctypes.CDLL(str(so)).two_stages
+    lib = ctypes.CDLL(str(so))
+    f, lib.records.argtypes = lib.two_stages, [ctypes.c_long] * 5
+    f.records = lib.records
     f.argtypes = [ctypes.c_int] + [ctypes.c_long] * 12 + [ctypes.c_double]
     return f
 
@@ -94,3 +99,26 @@ def test_one_crowded_column_takes_one_stage(rule):
     """256 columns of 8 probes and one of 20,000 (n = 1024, f = 4, 1245 beams)."""
     common = (1245, 1430000, 70000, 20008)
     assert not rule(0, 22048, *common, 257, 39, 512, 128, 80, 20008, 1248 * 512 * 512 * 8, 1245 * 512 * 512 * 8.0)
+
+
+# (n, L, alpha, f, probes along each axis), microseconds in plain BF16 from S and with its records
+BF16 = [
+    ((1024, 100.0, 0.020, 4, 256), (21822, 15528)), ((1024, 100.0, 0.020, 4, 128), (5813, 4435)),
+    ((1024, 100.0, 0.020, 4, 64), (1806, 1648)), ((1024, 100.0, 0.020, 4, 32), (733, 1026)),
+    ((2048, 200.0, 0.020, 8, 256), (24693, 17863)), ((2048, 200.0, 0.020, 8, 64), (3084, 4112)),
+    ((512, 50.0, 0.020, 2, 64), (1457, 1098)), ((512, 50.0, 0.020, 2, 20), (278, 377)),
+    ((1024, 100.0, 0.010, 2, 64), (7235, 5981)), ((256, 25.0, 0.020, 2, 16), (35, 46)),
+    ((64, 10.0, 0.024, 2, 64), (31, 34)),
+]
+
+
+@pytest.mark.parametrize("call,times", BF16)
+def test_bf16_records_where_they_pay(rule, call, times):
+    import paper_1706_08563_amd as P
+    n, L, alpha, f, k = call
+    d = P.prism_smatrix_plan(P.prism_grid_init((L, L, 20.0), 2.0, n), 200e3, alpha, f)
+    x = np.arange(k) * (L / k)
+    yy, xx = np.meshgrid(x + 0.11, x + 0.37, indexing="ij")
+    p = P.prism_probe_plan_init(d, np.stack([xx.ravel(), yy.ravel()], axis=1))
+    got = rule.records(p.n_entries, k * k * (d.m_win // 16) ** 2, p.n_tiles, d.n_beams, d.ns)
+    assert bool(got) == (times[1] < times[0])
