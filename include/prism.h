@@ -182,17 +182,18 @@ int prism_build_smatrix(const prism_smatrix_desc* d, const float* V, void* S,
 int prism_build_smatrix_range(const prism_smatrix_desc* d, const float* V, void* S, int32_t first,
                               int32_t count, void* ws, size_t ws_bytes, void* stream);
 
-/* Streams used by prism_build_smatrix (process-wide), n in 1..4, or 0 (the
- * default) for a count chosen by size: 1 for small beam batches, else 2, or 4
- * for large ones.  Every beam batch is split into n parts, run on `stream` and
+/* Streams used by prism_build_smatrix and multislice_outputs (process-wide), n in
+ * 1..4, or 0 (the default) for a count chosen by size: 1 for small batches of
+ * beams (probes), else 2, or 4 for large ones.  Every batch is split into n parts,
+ * run on `stream` and
  * on n - 1 partner streams that the library creates once per caller stream (default
  * priority, kept until the process ends), each part one slice behind the
- * previous one, so that row and column passes of different beams run
+ * previous one, so that row and column passes of different beams (probes) run
  * together.  The call still returns with all work ordered on `stream`, and
- * the S-matrix is identical to the one-stream build (n = 1).  Batches of
- * fewer than n beams use as many streams as beams.  At most 32 caller
- * streams get partners; builds on any further caller stream run on that
- * stream alone.
+ * the S-matrix (the outputs) is identical to that of one stream (n = 1).  Batches
+ * of fewer than n items use as many streams as items.  At most 32 caller
+ * streams get partners; calls on any further caller stream run on that
+ * stream alone, as do the streaming forms of multislice.
  * Errors: PRISM_E_INVAL (n outside 0..4). */
 int prism_set_build_streams(int32_t n);
 
@@ -317,7 +318,8 @@ int multislice_workspace(const prism_grid* grid, int32_t batch, int64_t n_probes
  * transmitted and propagated through every slice (Eqs. 1-2), then
  * |Psi(q)|^2 / n^4 summed over annular bins of width dalpha up to alpha_aa.
  * probe_xy: host float64 [n_probes][2].  V: device float32 [n_slices][n][n].
- * The probes are processed `batch` at a time inside ws.  Uploads host tables.
+ * The probes are processed `batch` at a time inside ws, parts of a batch on
+ * partner streams by prism_set_build_streams.  Uploads host tables.
  * Errors: PRISM_E_INVAL, PRISM_E_UNSUPPORTED, PRISM_E_WORKSPACE, PRISM_E_DEVICE. */
 int multislice_outputs(const prism_grid* grid, double E0, double alpha_max, const prism_aberrations* ab,
                        const float* V, const double* probe_xy, int64_t n_probes, double dalpha,

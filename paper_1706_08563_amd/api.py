@@ -398,8 +398,8 @@ def multislice_outputs_streaming(grid: prism_grid, E0: float, alpha_max: float, 
 
 
 def prism_set_build_streams(n: int):
-    """Streams of the S-matrix build, 1-4, or 0 (the default) for a count by
-    grid and batch size: each beam batch is split into that many parts
+    """Streams of the S-matrix build and of multislice, 1-4, or 0 (the default)
+    for a count by grid and batch size: each batch is split into that many parts
     that overlap on the current stream and partner streams; 1 runs everything
     on the current stream."""
     check(lib.prism_set_build_streams(int(n)))

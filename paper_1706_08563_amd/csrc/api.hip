@@ -886,9 +886,9 @@ int streams_by_size(int n, int64_t items) {
     const int64_t pixels = items * n * n;
     return items < 32 || pixels < (int64_t)8 << 20 ? 1 : (pixels < (int64_t)700 << 20 ? 2 : 4);
 }
-int build_streams_for(int n, int beams) {
+int build_streams_for(int n, int items) {
     const int s = g_build_streams.load();
-    return s > 0 ? s : streams_by_size(n, beams);
+    return s > 0 ? s : streams_by_size(n, items);
 }
 std::mutex g_partner_mu;
 std::map<hipStream_t, std::vector<hipStream_t>> g_partner;
@@ -1737,7 +1737,7 @@ static int multislice_run(const prism_grid* grid, double E0, double alpha_max, c
     // at a time, 23.6 ms on one stream, 22.5 on two.  A streamed call has one
     // transmission slice, which one stream at a time may use.
     const int NB = (int)std::min<int64_t>(batch, std::max<int64_t>(n_probes, 1));
-    return run_overlapped(st, streaming ? 1 : streams_by_size(n, NB), 0, n_probes, NB, run_probes);
+    return run_overlapped(st, streaming ? 1 : build_streams_for(n, NB), 0, n_probes, NB, run_probes);
 }
 
 int multislice_workspace(const prism_grid* grid, int32_t batch, int64_t n_probes, size_t* bytes) {
