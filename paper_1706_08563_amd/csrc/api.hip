@@ -24,6 +24,7 @@
 #include <vector>
 
 #include "kernels.hpp"
+#include "launch_limits.hpp"
 #include "synth_route.hpp"
 #include "prism.h"
 
@@ -862,33 +863,11 @@ constexpr int kMaxBuildStreams = 4;
 #ifndef PRISM_FORK_STAGE
 #define PRISM_FORK_STAGE 1
 #endif
-// 0: by size, of a beam batch.  Each further stream costs two launches per
-// slice and shorter kernels; small batches stay on one.  Builds on 1, 2 and 4
-// streams:
-//   up to 1024^2, by pixels (items x n^2), us
-//     21 beams at 256^2 (1.4 M)      339    455    765
-//     69 beams at 256^2 (4.5 M)      308    310    472
-//     16 probes at 1024^2 (17 M)    3516   3655      -   (multislice, 4 batches)
-//     69 beams at 512^2 (18 M)      1502   1374   1807
-//     305 beams at 256^2 (20 M)     1566   1408   1765
-//     1245 beams at 512^2 (326 M)  23359  22753  23269
-//     1245 beams at 1024^2 (1.3 G)  262.4, 253.9 and 249.5 ms
-//   at 2048^2, by items, us per beam of 10 slices (a batch of 2^k items is the
-//   slow one on one stream, and its parts are not)
-//     40 beams                     219  231  236
-//     64                           219  216  222
-//     128                          228  213  216
-//     256                          248  224  217
-//     305, 1245                    223, 225 within 1%
-std::atomic<int> g_build_streams{0};
-int streams_by_size(int n, int64_t items) {
-    if (n > 1024) return items < 64 ? 1 : (items < 192 ? 2 : 4);
-    const int64_t pixels = items * n * n;
-    return items < 32 || pixels < (int64_t)8 << 20 ? 1 : (pixels < (int64_t)700 << 20 ? 2 : 4);
-}
-int build_streams_for(int n, int items) {
+std::atomic<int> g_build_streams{0};               // 0: by size (streams_by_size)
+// Streams of a call over `count` items, `batch` at a time.
+int build_streams_for(int n, int64_t count, int batch) {
     const int s = g_build_streams.load();
-    return s > 0 ? s : streams_by_size(n, items);
+    return s > 0 ? s : streams_by_size(n, batch, (count + batch - 1) / batch);
 }
 std::mutex g_partner_mu;
 std::map<hipStream_t, std::vector<hipStream_t>> g_partner;
@@ -929,10 +908,10 @@ int prism_set_build_streams(int32_t n) {
     return PRISM_OK;
 }
 
-// Items [first, end) in batches of NB on P streams: run(b0, i0, cnt, q, after)
-// queues items b0 + i0 .. b0 + i0 + cnt - 1 of the batch starting at b0 on
+// Items [first, end) in batches of NB on P streams: run(b0, i0, cnt, beside, q,
+// after) queues items b0 + i0 .. b0 + i0 + cnt - 1 of the batch starting at b0 on
 // stream q and records `after`, when not null, where the next stream may
-// start.  Buffer slot i always holds item b0 + i of the current batch, and
+// start; `beside` such parts run at the same time.  Buffer slot i always holds item b0 + i of the current batch, and
 // stream k owns slots [off(k), off(k + 1)) in every batch (a short last batch
 // leaves the tail parts empty), so no two streams ever touch the same slot;
 // the forks of the first batch and the final joins are the only cross-stream
@@ -954,7 +933,7 @@ static int run_overlapped(hipStream_t st, int P, int64_t first, int64_t end, int
     }
     if (P <= 1) {
         for (int64_t b0 = first; b0 < end; b0 += NB) {
-            int rc = run(b0, 0, (int)std::min<int64_t>(NB, end - b0), st, nullptr);
+            int rc = run(b0, 0, (int)std::min<int64_t>(NB, end - b0), 1, st, nullptr);
             if (rc) return rc;
         }
         return PRISM_OK;
@@ -963,6 +942,8 @@ static int run_overlapped(hipStream_t st, int P, int64_t first, int64_t end, int
     // the tail parts idle.  On one they are full: 300 probes of 128^2, 128 at a
     // time, 371 us, in equal batches of 100 384 us.
     NB = equal;
+    // over many batches the parts drift apart and their launches fill the GPU together
+    const int beside = batches >= MANY_BATCHES ? P : 1;
     BuildEvents be;
     for (int k = 0; k < 2 * P; ++k) HIP_TRY(hipEventCreateWithFlags(&be.ev[k], hipEventDisableTiming));
     auto off = [&](int k) { return (int)((int64_t)k * NB / P); };
@@ -977,7 +958,7 @@ static int run_overlapped(hipStream_t st, int P, int64_t first, int64_t end, int
                     forked = k + 1;
                 }
                 if (cnt > 0) {
-                    int r = run(b0, i0, cnt, q[k], b0 == first ? be.ev[k] : nullptr);
+                    int r = run(b0, i0, cnt, beside, q[k], b0 == first ? be.ev[k] : nullptr);
                     if (r) return r;
                 } else if (b0 == first) {
                     HIP_TRY(hipEventRecord(be.ev[k], q[k]));
@@ -1036,7 +1017,7 @@ static int build_range(const prism_smatrix_desc* d, const float* V, void* S, int
     float2* Sout = static_cast<float2*>(S);
     const size_t item_w = (size_t)(n / 2) * wave_col_stride(n), layer = (size_t)(n / 2) * (n / 2);
     // items [i0, i0 + cnt) of the batch starting at beam b0, all slices then the store, on stream q
-    auto run_items = [&](int64_t b0, int i0, int cnt, hipStream_t q, hipEvent_t after_first_a) -> int {
+    auto run_items = [&](int64_t b0, int i0, int cnt, int beside, hipStream_t q, hipEvent_t after_first_a) -> int {
         float2* Wq = W + (size_t)i0 * item_w;
         const int2* bq = d_beams + b0 + i0;
         for (int s = 0; s < nsl; ++s) {
@@ -1049,7 +1030,7 @@ static int build_range(const prism_smatrix_desc* d, const float* V, void* S, int
                 HIP_TRY(hipEventRecord(after_first_a, q));
             HIP_TRY(timed(PRISM_K_PASS_B, q, [&] {
                 return launch_pass_b(n, s == nsl - 1 ? PASSB_LAST_S : PASSB_MID, Wq, tb, nullptr, nullptr, nullptr,
-                                     nullptr, 0.0, 0.f, cnt, q);
+                                     nullptr, 0.0, 0.f, cnt, q, beside);
             }));
             if (PRISM_FORK_STAGE == 1 && s == 0 && after_first_a) HIP_TRY(hipEventRecord(after_first_a, q));
         }
@@ -1057,7 +1038,7 @@ static int build_range(const prism_smatrix_desc* d, const float* V, void* S, int
         HIP_TRY(timed(PRISM_K_FINAL, q, [&] { return launch_smatrix_final(n, Wq, Sq, pd.tw_half, cnt, q); }));
         return PRISM_OK;
     };
-    return run_overlapped(st, build_streams_for(n, NB), first, end, NB, run_items);
+    return run_overlapped(st, build_streams_for(n, count, NB), first, end, NB, run_items);
 }
 
 int prism_build_smatrix(const prism_smatrix_desc* d, const float* V, void* S, void* ws, size_t ws_bytes,
@@ -1710,12 +1691,12 @@ static int multislice_run(const prism_grid* grid, double E0, double alpha_max, c
     long long g = 0;
     const size_t item_w = (size_t)Lh * wave_col_stride(n), item_i = (size_t)Lh * Lh;
     // probes p0 + i0 .. of the batch at p0, in slots i0 .. of the wave buffer, on stream q
-    auto run_probes = [&](int64_t p0, int i0, int nb, hipStream_t q, hipEvent_t after_first) -> int {
+    auto run_probes = [&](int64_t p0, int i0, int nb, int beside, hipStream_t q, hipEvent_t after_first) -> int {
         float2* W = m.W + (size_t)i0 * item_w;
         float* I = m.I + (size_t)i0 * item_i;
         HIP_TRY(timed(PRISM_K_PASS_B, q, [&] {
             return launch_pass_b(n, PASSB_INIT, W, tb, h.aberr.empty() ? nullptr : m.aberr, nullptr, m.kymax,
-                                 m.xy + p0 + i0, 1.0 / L, amp, nb, q);
+                                 m.xy + p0 + i0, 1.0 / L, amp, nb, q, beside);
         }));
         for (int s = 0; s < nsl; ++s) {
             const float2* Ts = m.T + (size_t)s * n * n;
@@ -1728,7 +1709,7 @@ static int multislice_run(const prism_grid* grid, double E0, double alpha_max, c
             if (s == 0 && after_first) HIP_TRY(hipEventRecord(after_first, q));
             HIP_TRY(timed(PRISM_K_PASS_B, q, [&] {
                 return launch_pass_b(n, s == nsl - 1 ? PASSB_LAST_I : PASSB_MID, W, tb, nullptr, I, nullptr, nullptr,
-                                     0.0, 0.f, nb, q);
+                                     0.0, 0.f, nb, q, beside);
             }));
         }
         HIP_TRY(timed(PRISM_K_BIN_REDUCE, q, [&] {
@@ -1740,7 +1721,7 @@ static int multislice_run(const prism_grid* grid, double E0, double alpha_max, c
     // at a time, 23.6 ms on one stream, 22.5 on two.  A streamed call has one
     // transmission slice, which one stream at a time may use.
     const int NB = (int)std::min<int64_t>(batch, std::max<int64_t>(n_probes, 1));
-    return run_overlapped(st, streaming ? 1 : build_streams_for(n, NB), 0, n_probes, NB, run_probes);
+    return run_overlapped(st, streaming ? 1 : build_streams_for(n, n_probes, NB), 0, n_probes, NB, run_probes);
 }
 
 int multislice_workspace(const prism_grid* grid, int32_t batch, int64_t n_probes, size_t* bytes) {

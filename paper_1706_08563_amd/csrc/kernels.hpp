@@ -42,10 +42,11 @@ hipError_t launch_first_from_spectrum(int n, float2* W, const float2* R, const P
 // Column pass (see PassBMode).  inten: band intensities [item][j][j'] for
 // PASSB_LAST_I.  For PASSB_INIT the spectrum is the aperture: |ky| <= ky_max[j],
 // coefficient amp e^{-2 pi i (kx x + ky y)/L} times aberr[j][j'] when `aux`
-// (the aberration table, complex [n/2][n/2]) is not null.
+// (the aberration table, complex [n/2][n/2]) is not null.  `beside`: such launches
+// at the same time (on other streams).
 hipError_t launch_pass_b(int n, int mode, float2* W, const PropTables& tb, const float2* aux, float* inten,
                          const int* ky_max, const double2* probe_xy, double inv_L, float amp, int n_items,
-                         hipStream_t st);
+                         hipStream_t st, int beside = 1);
 
 // Final S-matrix pass: S[b][my][mx] = inverse row transform of half[b][j][my].
 hipError_t launch_smatrix_final(int n, const float2* half, float2* S, const float2* tw_half, int n_items,

@@ -1,4 +1,5 @@
-// launch_limits.hpp -- how much one launch may hold (plain host C++, no HIP).
+// launch_limits.hpp -- how much one launch may hold, and how many streams a call
+// takes (plain host C++, no HIP).
 #pragma once
 #include <algorithm>
 #include <cstddef>
@@ -51,5 +52,40 @@ inline int64_t sum_ky_blocks(int n_cols, int ns, int m, int max_probes) {
 }
 // Whether a launch may hold that many workgroups of 256, in 8 equal parts.
 inline bool launchable(int64_t blocks) { return (blocks + 7) / 8 * 8 <= most_blocks(256); }
+
+// Streams of a build (or multislice) in batches of `items`.  Each further stream
+// costs two launches per slice and shorter kernels; small batches stay on one.
+// Builds on 1, 2 and 4 streams:
+//   up to 1024^2, by pixels (items x n^2), us
+//     21 beams at 256^2 (1.4 M)      339    455    765
+//     69 beams at 256^2 (4.5 M)      308    310    472
+//     16 probes at 1024^2 (17 M)    3516   3655      -   (multislice, 4 batches)
+//     69 beams at 512^2 (18 M)      1502   1374   1807
+//     305 beams at 256^2 (20 M)     1566   1408   1765
+//     1245 beams at 512^2 (326 M)  23359  22753  23269
+//     1245 beams at 1024^2 (1.3 G)  262.4, 253.9 and 249.5 ms
+//   many small batches at 1024^2, whose parts run on without waiting for each
+//   other: 1245 beams in batches of, ms of 6 slices
+//     8     40.3  41.5  37.8
+//     12    39.7  37.8  34.4
+//     16    35.4  34.9  32.0
+//     20    37.7  34.3  31.5
+//     24    34.4  31.8  32.5
+//     31    32.6  30.8  31.3
+//   at 2048^2, by items, us per beam of 10 slices (a batch of 2^k items is the
+//   slow one on one stream, and its parts are not)
+//     40 beams                     219  231  236
+//     64                           219  216  222
+//     128                          228  213  216
+//     256                          248  224  217
+//     305, 1245                    223, 225 within 1%
+constexpr int MANY_BATCHES = 8;
+inline int streams_by_size(int n, int64_t items, int64_t batches) {
+    if (n > 1024) return items < 64 ? 1 : (items < 192 ? 2 : 4);
+    const int64_t M = 1 << 20, pixels = items * n * n;
+    if (pixels < 8 * M || (items < 32 && batches < MANY_BATCHES)) return 1;
+    if (items < 32) return pixels < 24 * M ? 4 : 2;
+    return pixels < 700 * M ? 2 : 4;
+}
 
 }  // namespace prism

@@ -684,7 +684,7 @@ __global__ __launch_bounds__(WG) void k_pass_b_tile(float2* __restrict__ W, Prop
 
 template <int N, int MODE>
 static hipError_t pass_b_nm(float2* W, const PropTables& tb, const float2* aux, float* inten, const int* ky_max,
-                            const double2* xy, double inv_L, float amp, int n_items, hipStream_t st) {
+                            const double2* xy, double inv_L, float amp, int n_items, hipStream_t st, int beside) {
     constexpr int L = N / 2, LPT = Fft<L>::LPT, GROUPS = 4 * (64 / LPT), NC = PassBCols<N, MODE>::value;
     if constexpr (MODE != PASSB_INIT && PassBTile<N>::ok) {
         constexpr int TC = PassBTile<N>::TC;
@@ -703,9 +703,12 @@ static hipError_t pass_b_nm(float2* W, const PropTables& tb, const float2* aux, 
     // works its columns off one after the other, so in a small launch fewer
     // CUs each take longer.  One slice of 69 beams at 256^2: 26 us with 8
     // columns (17-69 workgroups), 6 us with 1; 152 beams at 512^2 (608
-    // workgroups) 5.64 ms per 20-slice build with 8, 5.78 ms with 4.
+    // workgroups) 5.64 ms per 20-slice build with 8, 5.78 ms with 4.  Launches on
+    // other streams count where they keep running beside this one: 1245 beams at
+    // 1024^2, 16 at a time on 4 streams, 34.6 -> 32.0 ms; in a single batch they
+    // follow each other closely (305 beams at 256^2 0.74 ms, counted 0.78).
     if constexpr (NC > 1) {
-        const int64_t one = (int64_t)n_items * (L / GROUPS);   // workgroups at one column per group
+        const int64_t one = (int64_t)n_items * beside * (L / GROUPS);   // at one column per group
         if (one >= 512 * NC) launch(std::integral_constant<int, NC>{});
         else if (NC > 4 && one >= 512 * 4) launch(std::integral_constant<int, 4>{});
         else if (NC > 2 && one >= 512 * 2) launch(std::integral_constant<int, 2>{});
@@ -719,28 +722,28 @@ static hipError_t pass_b_nm(float2* W, const PropTables& tb, const float2* aux, 
 template <int N>
 static hipError_t pass_b_n(int mode, float2* W, const PropTables& tb, const float2* aux, float* inten,
                            const int* ky_max, const double2* xy, double inv_L, float amp, int n_items,
-                           hipStream_t st) {
+                           hipStream_t st, int beside) {
     switch (mode) {
-        case PASSB_MID: return pass_b_nm<N, PASSB_MID>(W, tb, aux, inten, ky_max, xy, inv_L, amp, n_items, st);
+        case PASSB_MID: return pass_b_nm<N, PASSB_MID>(W, tb, aux, inten, ky_max, xy, inv_L, amp, n_items, st, beside);
         case PASSB_LAST_S:
-            return pass_b_nm<N, PASSB_LAST_S>(W, tb, aux, inten, ky_max, xy, inv_L, amp, n_items, st);
+            return pass_b_nm<N, PASSB_LAST_S>(W, tb, aux, inten, ky_max, xy, inv_L, amp, n_items, st, beside);
         case PASSB_LAST_I:
-            return pass_b_nm<N, PASSB_LAST_I>(W, tb, aux, inten, ky_max, xy, inv_L, amp, n_items, st);
-        case PASSB_INIT: return pass_b_nm<N, PASSB_INIT>(W, tb, aux, inten, ky_max, xy, inv_L, amp, n_items, st);
+            return pass_b_nm<N, PASSB_LAST_I>(W, tb, aux, inten, ky_max, xy, inv_L, amp, n_items, st, beside);
+        case PASSB_INIT: return pass_b_nm<N, PASSB_INIT>(W, tb, aux, inten, ky_max, xy, inv_L, amp, n_items, st, beside);
     }
     return hipErrorInvalidValue;
 }
 
 hipError_t launch_pass_b(int n, int mode, float2* W, const PropTables& tb, const float2* aux, float* inten,
                          const int* ky_max, const double2* probe_xy, double inv_L, float amp, int n_items,
-                         hipStream_t st) {
+                         hipStream_t st, int beside) {
     switch (n) {
-        case 64: return pass_b_n<64>(mode, W, tb, aux, inten, ky_max, probe_xy, inv_L, amp, n_items, st);
-        case 128: return pass_b_n<128>(mode, W, tb, aux, inten, ky_max, probe_xy, inv_L, amp, n_items, st);
-        case 256: return pass_b_n<256>(mode, W, tb, aux, inten, ky_max, probe_xy, inv_L, amp, n_items, st);
-        case 512: return pass_b_n<512>(mode, W, tb, aux, inten, ky_max, probe_xy, inv_L, amp, n_items, st);
-        case 1024: return pass_b_n<1024>(mode, W, tb, aux, inten, ky_max, probe_xy, inv_L, amp, n_items, st);
-        case 2048: return pass_b_n<2048>(mode, W, tb, aux, inten, ky_max, probe_xy, inv_L, amp, n_items, st);
+        case 64: return pass_b_n<64>(mode, W, tb, aux, inten, ky_max, probe_xy, inv_L, amp, n_items, st, beside);
+        case 128: return pass_b_n<128>(mode, W, tb, aux, inten, ky_max, probe_xy, inv_L, amp, n_items, st, beside);
+        case 256: return pass_b_n<256>(mode, W, tb, aux, inten, ky_max, probe_xy, inv_L, amp, n_items, st, beside);
+        case 512: return pass_b_n<512>(mode, W, tb, aux, inten, ky_max, probe_xy, inv_L, amp, n_items, st, beside);
+        case 1024: return pass_b_n<1024>(mode, W, tb, aux, inten, ky_max, probe_xy, inv_L, amp, n_items, st, beside);
+        case 2048: return pass_b_n<2048>(mode, W, tb, aux, inten, ky_max, probe_xy, inv_L, amp, n_items, st, beside);
     }
     return hipErrorInvalidValue;
 }

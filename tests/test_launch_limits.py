@@ -22,6 +22,7 @@ extern "C" long kx(int ns, int max_cols, int n_rows, int row_steps, int max_step
     return tiles * prism::sum_kx_row_groups(tiles, n_rows, row_steps, max_steps);
 }
 extern "C" long ky(int n_cols, int ns, int m, int max_probes) { return prism::sum_ky_blocks(n_cols, ns, m, max_probes); }
+extern "C" int streams(int n, long items, long batches) { return prism::streams_by_size(n, items, batches); }
 extern "C" int launchable(long blocks) { return prism::launchable(blocks); }
 """
 
@@ -36,6 +37,7 @@ def limits(tmp_path_factory):
     lib.columns.argtypes = [ctypes.c_int] * 4 + [ctypes.c_size_t]
     lib.kx.restype = lib.ky.restype = ctypes.c_long
     lib.launchable.argtypes = [ctypes.c_long]
+    lib.streams.argtypes = [ctypes.c_int, ctypes.c_long, ctypes.c_long]
     return lib
 
 
@@ -102,3 +104,16 @@ def test_two_stage_launches_hold_fewer_than_2_32_threads(limits):
 def _row_groups(limits, tiles, n_rows, row_steps):
     ns = {2: 16, 32: 64, 8192: 1024}[tiles]
     return limits.kx(ns, 1, n_rows, row_steps, 256) // tiles
+
+
+# n, items of a batch, batches, times on 1, 2 and 4 streams
+@pytest.mark.parametrize("n,items,batches,times", [
+    (256, 21, 1, (339, 455, 765)), (256, 69, 1, (308, 310, 472)), (512, 69, 1, (1502, 1374, 1807)),
+    (256, 305, 1, (1566, 1408, 1765)), (1024, 1245, 1, (262400, 253900, 249500)),
+    (1024, 12, 104, (39700, 37800, 34400)), (1024, 16, 78, (35400, 34900, 32000)), (1024, 20, 63, (37700, 34300, 31500)), (1024, 24, 52, (34400, 31800, 32500)),
+    (1024, 31, 41, (32600, 30800, 31300)), (1024, 33, 38, (36970, 30660, 30970)), (1024, 8, 1, (501, 557, 623)),
+    (512, 24, 1, (336, 411, 481)), (2048, 40, 1, (219, 231, 236)), (2048, 128, 1, (228, 213, 216)),
+    (2048, 256, 1, (248, 224, 217))])
+def test_streams_by_size(limits, n, items, batches, times):
+    got = limits.streams(n, items, batches)
+    assert times[{1: 0, 2: 1, 4: 2}[got]] <= 1.02 * min(times)
