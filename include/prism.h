@@ -390,14 +390,15 @@ int prism_probe_outputs_streaming(const prism_smatrix_desc* d, const void* S_hos
                                   void* ws, size_t ws_bytes, void* stream, void* h2d_stream);
 
 /* Device workspace of prism_probe_outputs_chunked with beam_chunk beams per
- * chunk (coefficients and scratch of one chunk, the windows of all probes). */
+ * chunk (coefficients of one chunk, where plain BF16 converts it also its
+ * records, the windows of all probes). */
 int prism_probe_chunked_workspace(const prism_smatrix_desc* d, const prism_probe_plan* plan,
                                   int32_t beam_chunk, size_t* bytes);
 
 /* prism_probe_outputs (out, or the 4D output out4d when out is NULL) with S in
- * device memory, contracted beam_chunk beams at a time into FP32 windows:
- * the workspace then holds scratch for one chunk of S instead of all of it
- * (for S-matrices too large to have it beside them).  The result
+ * device memory, contracted beam_chunk beams at a time into FP32 windows: the
+ * workspace then holds no scratch beside S but the records of one chunk, in
+ * large calls (for S-matrices that leave no room beside them).  The result
  * equals prism_probe_outputs_streaming's for the same chunk size.  Fully
  * asynchronous.  Errors: PRISM_E_INVAL, PRISM_E_WORKSPACE, PRISM_E_DEVICE. */
 int prism_probe_outputs_chunked(const prism_smatrix_desc* d, const void* S,

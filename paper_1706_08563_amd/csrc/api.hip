@@ -586,12 +586,6 @@ SynthJobDev synth_job_carve(const prism_smatrix_desc* d, const prism_probe_plan*
     j.inten = d->m_win > 128 ? c.take<float>(P * d->m_win * d->m_win) : nullptr;
     return j;
 }
-// Part of every workspace per distinct S-matrix of a call: the size of the
-// S-matrix with its beams padded to whole K steps.
-char* s_scratch_carve(const prism_smatrix_desc* d, int n_beams, Carve& c) {
-    return c.take<char>((size_t)d->ns * d->ns * ksteps_of(n_beams) * KSTEP * sizeof(float2));
-}
-
 // Tables of the two-stage sum inside the plan buffer, after the others.  The
 // plan's off[0] (the positions start the buffer) holds the counts the launches
 // need: scan columns (0: none), log2 of the tile width, max_cols and max_probes
@@ -625,6 +619,33 @@ ColumnTables column_tables(const prism_probe_plan* plan, size_t n_rows, size_t n
     t.end = c.off;
     return t;
 }
+
+inline size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
+
+// ky of the beams.
+int beam_row_count(const prism_smatrix_desc* d) {
+    int k = 0;
+    while (angle_of(d->lambda, 0, (k + 1) * d->f, d->grid.cell[0]) <= d->alpha_max) ++k;
+    return 2 * k + 1;
+}
+
+// Scratch of a call beside a distinct S-matrix: T of the two-stage sum, as many
+// scan columns as fit the size of the S-matrix with its beams padded to whole K
+// steps (0 without scan columns) ...
+size_t t_scratch_bytes(const prism_smatrix_desc* d, const prism_probe_plan* plan, int n_rows) {
+    const size_t full = (size_t)d->ns * d->ns * ksteps_of(d->n_beams) * KSTEP * sizeof(float2);
+    return std::min(full, (size_t)(plan->off[0] & 0xfffffffu) * two_stage_column_bytes(n_rows, d->ns, d->m_win));
+}
+// ... or the BF16 records of S, when its probes' sums are large enough.
+struct BeamUses {
+    int64_t entries = 0, exact = 0, tiles = 0;
+    void add(const prism_smatrix_desc* d, const prism_probe_plan* plan) {
+        entries += plan->n_entries;
+        exact += plan->n_probes * (d->m_win / 16) * (d->m_win / 16);   // of windows that fill their tiles
+        tiles += plan->n_tiles;
+    }
+    bool records(int n_beams, int ns) const { return bf16_records_route(entries, exact, tiles, n_beams, ns); }
+};
 
 // Consistency of a descriptor filled by prism_smatrix_plan (without recounting
 // the beams, which costs O(n^2) host work per call).
@@ -1150,7 +1171,10 @@ static int probe_plan_make(const prism_smatrix_desc* d, const double* probe_xy, 
     p.plan_bytes = c.off + 256;
     Carve w(nullptr);
     synth_job_carve(d, &p, w);
-    s_scratch_carve(d, d->n_beams, w);
+    BeamUses uses;
+    uses.add(d, &p);
+    w.take<char>(std::max(t_scratch_bytes(d, &p, beam_row_count(d)),
+                          uses.records(d->n_beams, d->ns) ? bf16_record_bytes(d->n_beams, d->ns) : 0));
     p.ws_bytes = w.off + 256;
     *plan = p;
     memo_store(d, dalpha, n_bins, C1, C3, dmap, std::move(h), maxpt);
@@ -1237,13 +1261,38 @@ int prism_probe_plan_upload_map(const prism_smatrix_desc* d, const double* probe
     return probe_plan_put(d, probe_xy, detector_map, plan, plan_dev, stream);
 }
 
-// Index of the first job that reads the same S-matrix (same pointer and shape).
-static int first_with_same_s(const prism_probe_job* jobs, int k) {
-    for (int j = 0; j < k; ++j)
-        if (jobs[j].S == jobs[k].S && jobs[j].desc->n_beams == jobs[k].desc->n_beams &&
-            jobs[j].desc->ns == jobs[k].desc->ns)
-            return j;
-    return k;
+// Index of the first job that reads the same S-matrix (same pointer and shape),
+// for every job.
+static std::vector<int> first_with_same_s(const prism_probe_job* jobs, int n_jobs) {
+    std::vector<int> first(n_jobs);
+    for (int k = 0; k < n_jobs; ++k) {
+        first[k] = k;
+        for (int j = 0; j < k && first[k] == k; ++j)
+            if (jobs[j].S == jobs[k].S && jobs[j].desc->n_beams == jobs[k].desc->n_beams &&
+                jobs[j].desc->ns == jobs[k].desc->ns)
+                first[k] = j;
+    }
+    return first;
+}
+
+// Per job that is the first on its S-matrix: the uses of it, and the scratch beside it.
+struct SUse {
+    BeamUses uses;
+    size_t scratch = 0;
+};
+static std::vector<SUse> s_uses(const prism_probe_job* jobs, const std::vector<int>& first) {
+    std::vector<SUse> u(first.size());
+    for (size_t k = 0; k < first.size(); ++k) {
+        const prism_smatrix_desc* d = jobs[k].desc;
+        u[first[k]].uses.add(d, jobs[k].plan);
+        u[first[k]].scratch = std::max(u[first[k]].scratch, t_scratch_bytes(d, jobs[k].plan, beam_row_count(d)));
+    }
+    for (size_t k = 0; k < first.size(); ++k) {
+        const prism_smatrix_desc* d = jobs[k].desc;
+        if (first[k] == (int)k && u[k].uses.records(d->n_beams, d->ns))
+            u[k].scratch = std::max(u[k].scratch, bf16_record_bytes(d->n_beams, d->ns));
+    }
+    return u;
 }
 
 static int synth_validate(const prism_probe_job* jobs, int n_jobs, int precision, size_t* need) {
@@ -1261,20 +1310,20 @@ static int synth_validate(const prism_probe_job* jobs, int n_jobs, int precision
             return fail(PRISM_E_INVAL, "probe outputs: job %d: bad out_scale or accumulate", k);
         synth_job_carve(jb.desc, jb.plan, c);
     }
+    const std::vector<int> first = first_with_same_s(jobs, n_jobs);
+    const std::vector<SUse> uses = s_uses(jobs, first);
     for (int k = 0; k < n_jobs; ++k)
-        if (first_with_same_s(jobs, k) == k) s_scratch_carve(jobs[k].desc, jobs[k].desc->n_beams, c);
+        if (first[k] == k) c.take<char>(uses[k].scratch);
     *need = c.off + 256;
     return PRISM_OK;
 }
-
-inline size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
 
 // The two-stage sum's arguments for a job, when it takes that route.
 static bool two_stage_args(const prism_smatrix_desc* d, const prism_probe_plan* plan, const char* pb, int precision,
                            TwoStageArgs& t) {
     if (!plan->off[0] || precision == PRISM_BF16) return false;
     const BeamRows br = beam_rows(d->grid.cell[0], d->lambda, d->alpha_max, d->f);
-    if (br.rows.back().x + br.rows.back().y != d->n_beams) return false;
+    if (br.rows.back().x + br.rows.back().y != d->n_beams || (int)br.rows.size() != beam_row_count(d)) return false;
     const ColumnTables c = column_tables(plan, br.rows.size(), br.steps.size());
     t = TwoStageArgs{};
     t.n_cols = c.n_cols;
@@ -1288,10 +1337,8 @@ static bool two_stage_args(const prism_smatrix_desc* d, const prism_probe_plan* 
     t.ns = d->ns;
     t.m = d->m_win;
     // both operands within the C operand's part of the workspace, a column
-    // of T within the S-matrix's
-    Carve s(nullptr);
-    s_scratch_carve(d, d->n_beams, s);
-    t.T_bytes = s.off;
+    // of T within the scratch
+    t.T_bytes = t_scratch_bytes(d, plan, t.n_rows);
     if (align256(two_stage_cx_bytes(t.n_cols, t.col_steps)) + two_stage_cy_bytes(t.n_probes, t.n_rows) >
             c_operand_bytes(t.n_probes, d->n_beams) ||
         two_stage_column_bytes(t.n_rows, t.ns, t.m) > t.T_bytes)
@@ -1313,11 +1360,6 @@ static bool two_stage_args(const prism_smatrix_desc* d, const prism_probe_plan* 
     return true;
 }
 
-// (work tile, probe) pairs of windows that fill their tiles.
-static int64_t exact_entries(const prism_probe_plan* plan, const prism_smatrix_desc* d) {
-    return plan->n_probes * (d->m_win / 16) * (d->m_win / 16);
-}
-
 // Probe synthesis for several (S-matrix, probe plan) jobs on one stream:
 // coefficients per job, one contraction launch for all jobs (in plain BF16 a
 // second one for the jobs whose S-matrix is converted first, once for all of
@@ -1328,31 +1370,22 @@ static int synth_run(const prism_probe_job* jobs, int n_jobs, int precision, voi
     Carve c(ws);
     std::vector<SynthJobDev> jd(n_jobs);
     for (int k = 0; k < n_jobs; ++k) jd[k] = synth_job_carve(jobs[k].desc, jobs[k].plan, c);
+    const std::vector<int> first = first_with_same_s(jobs, n_jobs);
+    const std::vector<SUse> uses = s_uses(jobs, first);
     std::vector<float2*> scratch(n_jobs);
-    for (int k = 0; k < n_jobs; ++k) {
-        const int j = first_with_same_s(jobs, k);
-        scratch[k] = j < k ? scratch[j]
-                           : reinterpret_cast<float2*>(s_scratch_carve(jobs[k].desc, jobs[k].desc->n_beams, c));
-    }
+    for (int k = 0; k < n_jobs; ++k)
+        scratch[k] = first[k] < k ? scratch[first[k]] : reinterpret_cast<float2*>(c.take<char>(uses[k].scratch));
     std::vector<char> records(n_jobs, 0);
     for (int k = 0; k < n_jobs && precision == PRISM_BF16; ++k) {
-        const int j = first_with_same_s(jobs, k);
         const prism_smatrix_desc* d = jobs[k].desc;
-        if (j == k) {
-            int64_t entries = 0, exact = 0, tiles = 0;
-            for (int i = k; i < n_jobs; ++i)
-                if (first_with_same_s(jobs, i) == k) {
-                    entries += jobs[i].plan->n_entries;
-                    exact += exact_entries(jobs[i].plan, jobs[i].desc);
-                    tiles += jobs[i].plan->n_tiles;
-                }
-            records[k] = bf16_records_route(entries, exact, tiles, d->n_beams, d->ns);
+        if (first[k] == k) {
+            records[k] = uses[k].uses.records(d->n_beams, d->ns);
             if (records[k])
                 HIP_TRY(timed(PRISM_K_SPLIT, st, [&] {
                     return launch_bf16_records(static_cast<const float2*>(jobs[k].S), scratch[k], d->n_beams, d->ns, st);
                 }));
         } else {
-            records[k] = records[j];
+            records[k] = records[first[k]];
         }
     }
     for (int k = 0; k < n_jobs; ++k) {
@@ -1874,7 +1907,9 @@ static void stream_synth_carve(Carve& c, const prism_smatrix_desc* d, const pris
     m.Sst[0] = slots ? c.take<float2>((size_t)chunk * d->ns * d->ns) : nullptr;
     m.Sst[1] = slots ? c.take<float2>((size_t)chunk * d->ns * d->ns) : nullptr;
     m.C = c.take<char>(c_operand_bytes((int64_t)P, chunk));
-    m.records = s_scratch_carve(d, chunk, c);
+    BeamUses uses;
+    uses.add(d, plan);
+    m.records = c.take<char>(uses.records(chunk, d->ns) ? bf16_record_bytes(chunk, d->ns) : 0);
     m.win = c.take<float2>(P * M * M);
     m.inten = M > 128 ? c.take<float>(P * M * M) : nullptr;
 }
@@ -1927,6 +1962,8 @@ static int synth_chunked(const prism_smatrix_desc* d, const void* S, const prism
     auto torigin = reinterpret_cast<const int2*>(pb + plan->off[9]);
     const float amp = (float)(1.0 / std::sqrt((double)B));
     const double inv_L = 1.0 / d->grid.cell[0];
+    BeamUses uses;
+    uses.add(d, plan);
     const float2* Sb = static_cast<const float2*>(S);
     Ring2 r;
     if (streamed) {
@@ -1950,8 +1987,7 @@ static int synth_chunked(const prism_smatrix_desc* d, const void* S, const prism
         HIP_TRY(timed(PRISM_K_COEFFICIENTS, st, [&] {
             return launch_coefficients(precision, m.C, xy, beams + c0, ab, P, nb, inv_L, amp, st);
         }));
-        const bool records = precision == PRISM_BF16 &&
-                             bf16_records_route(plan->n_entries, exact_entries(plan, d), plan->n_tiles, nb, d->ns);
+        const bool records = precision == PRISM_BF16 && uses.records(nb, d->ns);
         if (records)
             HIP_TRY(timed(PRISM_K_SPLIT, st, [&] { return launch_bf16_records(chunk, m.records, nb, d->ns, st); }));
         ContractArgs ca{m.C, records ? m.records : chunk, m.win, tstart, tprobes, torigin, corner, plan->n_tiles,

@@ -320,9 +320,9 @@ class GpuExecutor:
         self.precision = precision
         self.probe_chunk_bytes = probe_chunk_bytes
         self.build_ws_bytes = build_ws_bytes
-        # S-matrices whose synthesis scratch (as large as S itself) would exceed
-        # this are contracted in beam
-        # chunks (prism_probe_outputs_chunked) instead of in the shared batch
+        # S-matrices above this, whose synthesis may take scratch as large as S
+        # itself, are contracted in beam chunks (prism_probe_outputs_chunked)
+        # instead of in the shared batch
         self.split_limit_bytes = split_limit_bytes
         self.jobs_per_request = jobs_per_request      # must match the scheduler's
         # beams of one build range: about range_pixels beam-pixels (n^2 each)
@@ -370,8 +370,8 @@ class GpuExecutor:
         else:
             # a batch holds up to jobs_per_request chunks of this request, each
             # with its own coefficients and windows, plus one S scratch
-            per_chunk = max(p.ws_bytes for p in plans) - split_bytes
-            ws = split_bytes + min(self.jobs_per_request, len(plans)) * per_chunk
+            largest = sorted(plans, key=lambda p: p.ws_bytes, reverse=True)[:self.jobs_per_request]
+            ws = _batch_ws(d, largest)
         foot = (g.n_slices * g.n * g.n * 4 + d.smatrix_bytes + d.build_ws_bytes
                 + sum(p.plan_bytes for p in plans) + ws + len(xy) * n_bins * 4)
         req.info.update(grid=g, desc=d, chunks=chunks, n_bins=n_bins, n_beams=d.n_beams, m_win=d.m_win,
@@ -569,6 +569,22 @@ class GpuExecutor:
 
     def chunks_left(self, req: Request):
         return range(req.chunks_issued, req.chunks_total)
+
+
+def _batch_ws(d, plans):
+    """Workspace of a batch of plans on one S-matrix (host sizes only: the
+    buffers' addresses, which do not exist yet, are not read)."""
+    import ctypes
+
+    from ._lib import check, lib, prism_probe_job
+    jobs = (prism_probe_job * len(plans))()
+    for job, plan in zip(jobs, plans):
+        job.desc, job.plan = ctypes.pointer(d), ctypes.pointer(plan)
+        job.S = job.plan_dev = job.out = 256
+        job.out_scale = 1.0
+    need = ctypes.c_size_t()
+    check(lib.prism_probe_batch_workspace(jobs, len(plans), ctypes.byref(need)))
+    return need.value
 
 
 def _chunked_ws(d, plan, beam_chunk):
