@@ -78,19 +78,27 @@ def prism_detector_default_bins(grid: prism_grid, E0: float, dalpha: float = 1e-
     return nb.value, a.value
 
 
+def _atom_records(pos, species_idx):
+    """prism_atom records of atoms at pos[i][0..2]: float64 [max(n, 1)][4], x, y,
+    z, and the species (modulo 2^32, as ctypes stores it) beside a zero pad in the
+    last 8 bytes."""
+    pos = np.ascontiguousarray(pos, dtype=np.float64)
+    n = len(pos)
+    rec = np.zeros((max(n, 1), 4), dtype=np.float64)
+    if n:
+        for k in range(3):
+            rec[:, k] = pos[:, k].reshape(n)              # an IndexError without 3 coordinates
+        if not (isinstance(species_idx, np.ndarray) and species_idx.dtype.kind in "iu" and species_idx.ndim == 1
+                and len(species_idx) >= n):
+            species_idx = np.array([int(species_idx[i]) & 0xffffffff for i in range(n)], dtype=np.uint32)
+        rec.view(np.int32)[:, 6] = species_idx[:n].astype(np.int32)
+    return rec, n
+
+
 def prism_project_potential(pos, species_idx, species, grid: prism_grid, device=None):
     """V [n_slices, n, n] float32 on the device from host atoms."""
     torch = _torch()
-    pos = np.ascontiguousarray(pos, dtype=np.float64)
-    n_atoms = len(pos)
-    # prism_atom records: x, y, z, and species beside a zero pad in the last 8 bytes
-    rec = np.zeros((max(n_atoms, 1), 4), dtype=np.float64)
-    if n_atoms:
-        rec[:, :3] = pos[:, :3]
-        if not (isinstance(species_idx, np.ndarray) and species_idx.dtype.kind in "iu" and species_idx.ndim == 1
-                and len(species_idx) >= n_atoms):
-            species_idx = np.array([int(species_idx[i]) for i in range(n_atoms)])
-        rec.view(np.int32)[:, 6] = species_idx[:n_atoms]
+    rec, n_atoms = _atom_records(pos, species_idx)
     atoms = rec.ctypes.data_as(ctypes.POINTER(prism_atom))
     sp = (prism_species * len(species))()
     for i, s in enumerate(species):
