@@ -478,10 +478,13 @@ def precision_study(args):
         torch.cuda.synchronize()
         dt = time.perf_counter() - t0
         P.prism_timing_enable(False)
-        cms, _ = P.prism_timing_read(P.TIMING_CLASSES["contract"])
+        cms, launches = P.prism_timing_read(P.TIMING_CLASSES["contract"])
         flops = 8.0 * d.n_beams * d.m_win ** 2 * len(xy)
+        # two launches: the sums over kx and ky, which do fewer operations
+        rate = "contract_useful_TFLOP_per_s" if launches == 1 else "direct_sum_equivalent_TFLOP_per_s"
         res[name] = {"synthesis_s": dt, "probes_per_s": len(xy) / dt, "contract_ms": cms,
-                     "contract_useful_TFLOP_per_s": flops / (cms * 1e-3) / 1e12}
+                     "convert_ms": P.prism_timing_read(P.TIMING_CLASSES["split"])[0],
+                     rate: flops / (cms * 1e-3) / 1e12}
         if fx is not None:
             got = P.prism_probe_outputs(d, S, plan_s, prec).cpu().numpy()
             res[name]["vs_fp64"] = detector_errors(got, fx["prism"])
@@ -710,19 +713,31 @@ def main():
                              "avg_ms": tot / cnt}
     kernels["pass_a"]["GB_per_s"] = a_bytes / (kernels["pass_a"]["avg_ms"] * 1e-3) / 1e9
     kernels["pass_b"]["GB_per_s"] = b_bytes / (kernels["pass_b"]["avg_ms"] * 1e-3) / 1e9
-    # of the direct sum over beams per probe, which a scan's sums over kx and
-    # then ky (two launches) replace by fewer operations
-    kernels["contract"]["TFLOP_per_s"] = c_flops / (kernels["contract"]["ms_total"] * 1e-3) / 1e12
-    if kernels["contract"]["launches_per_step"] == 1:
+    kc = kernels["contract"]
+    c_rate = c_flops / (kc["ms_total"] * 1e-3) / 1e12
+    if kc["launches_per_step"] == 1:
         # MFMA work: BF16 products per product of each precision
-        mw = kernels["contract"]["TFLOP_per_s"] * {P.PRISM_FP32: 6, P.PRISM_SPLIT_BF16X3: 3}.get(prec, 1)
-        kernels["contract"]["mfma_work_TFLOP_per_s"] = mw
-        kernels["contract"]["mfma_frac_of_bf16_peak"] = mw / PEAK_BF16_TFLOPS
+        kc["TFLOP_per_s"] = c_rate
+        mw = c_rate * {P.PRISM_FP32: 6, P.PRISM_SPLIT_BF16X3: 3}.get(prec, 1)
+        kc["mfma_work_TFLOP_per_s"] = mw
+        kc["mfma_frac_of_bf16_peak"] = mw / PEAK_BF16_TFLOPS
+    else:
+        # a scan's sums over kx and then ky do a fraction of the direct sum's
+        # operations and are bound by traffic: S in every pass over the scan
+        # columns, T written and read, the windows written
+        kc["direct_sum_equivalent_TFLOP_per_s"] = c_rate
+        ky = len(np.unique(P.prism_beam_list(d)[:, 1]))
+        s_bytes = kc["launches_per_step"] // 2 * d.smatrix_bytes
+        t_bytes = 16.0 * len(np.unique(xy[:, 0])) * ky * d.ns * M
+        kc["GB_per_s"] = (s_bytes + t_bytes + 8.0 * n_probes * M * M) / (kc["ms_total"] * 1e-3) / 1e9
     kernels["pass_a"]["TFLOP_per_s"] = pass_flops(n, B, n) / (kernels["pass_a"]["avg_ms"] * 1e-3) / 1e12
     kernels["pass_b"]["TFLOP_per_s"] = pass_flops(n, B, n // 2) / (kernels["pass_b"]["avg_ms"] * 1e-3) / 1e12
     dom = max(["pass_a", "pass_b", "contract"], key=lambda k: kernels[k]["ms_total"])
-    if dom == "contract":
-        ach = kernels["contract"]["TFLOP_per_s"]
+    if dom == "contract" and "GB_per_s" in kc:
+        roof = {"kernel": "contract", "bound": "hbm", "achieved": kc["GB_per_s"], "peak": PEAK_HBM_GBS, "unit": "GB/s",
+                "frac": kc["GB_per_s"] / PEAK_HBM_GBS, "traffic": None}
+    elif dom == "contract":
+        ach = kc["TFLOP_per_s"]
         roof = {"kernel": "contract", "bound": "mfma", "achieved": ach, "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
                 "frac": ach / PEAK_BF16_TFLOPS, "traffic": None}
     else:
@@ -765,9 +780,7 @@ def main():
         "p99_ms": float(np.percentile(step_ms, 99)),
         "build_ms": float(np.median(build_ms)),
         "build_ms_one_stream": float(np.median(build_ms_1)),
-        # the library's default for this grid and number of beams
-        "build_streams": (1 if B < 64 else 2 if B < 192 else 4) if n > 1024 else
-                         (1 if B < 32 or B * n * n < 8 << 20 else 2 if B * n * n < 700 << 20 else 4),
+        "build_streams": "by size",                 # the library's default
         "synthesis_ms": float(np.median(synth_ms)),
         "probe_plan_host_s": plan_s,
         # whole steps that also plan the scan (window corners, work tiles,
