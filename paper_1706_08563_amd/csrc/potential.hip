@@ -14,8 +14,9 @@
 // Bound: VALU and LDS (a table read and 6 operations per pixel and atom).
 // 51,000 atoms, 50 slices at 1024^2: 1.13 -> 0.38 ms against the form that
 // tested every atom of the slice per tile and took two exponentials per pixel
-// and atom (the 210 MB of V alone are 0.04 ms).  Tables of 8 atoms keep 16
-// wavefronts per SIMD within the LDS (16 atoms the same, 32 atoms 0.5 ms).
+// and atom (the 210 MB of V alone are 0.04 ms).  Tables of 8 atoms take 4.8 KB of
+// LDS with two Gaussians, 33 wavefronts (8 per SIMD) of a CU's 160 KB; 16 atoms
+// take the same time, 32 atoms 0.5 ms.
 #include "kernels.hpp"
 
 namespace prism {

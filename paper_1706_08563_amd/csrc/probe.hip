@@ -99,8 +99,8 @@ __device__ __forceinline__ bool locate(const ContractBatch& b, ContractJob& job,
 // An FP32 operand is a sum of NP BF16 parts, each the rounding of what the
 // parts before it leave (the differences are exact):
 //   NP = 3 (FP32)   all 24 bits; products hh, hm, mh, mm, hl, lh.  What is
-//                   left out (ml, lm, ll) is at most 2^-25 of the product,
-//                   below the rounding of an FP32 product.
+//                   left out (ml, lm, ll) is at most 2^-24 of the product in
+//                   all, as much as the rounding of an FP32 product.
 //   NP = 2 (split)  16 bits; hh, hl, lh (lo lo, ~2^-16 relative, left out).
 //   NP = 1 (BF16)   hh.
 //
@@ -118,7 +118,8 @@ __device__ __forceinline__ bool locate(const ContractBatch& b, ContractJob& job,
 // Before: S converted to BF16 records by a pass of its own (1.06 ms, and as
 // much memory again as S) and both operands staged through LDS, 6.8 + 1.06
 // ms; with few probes per pixel the pass was as long as the contraction (441
-// probes of 256^2 windows: 1.16 + 1.07 -> 1.02 ms).  FP32 products on the
+// probes of 256^2 windows: 1.16 + 1.07 -> 1.02 ms).  Plain BF16 reads such records
+// where sums are large (k_bf16_records).  FP32 products on the
 // VALU: 2025 probes x 1245 beams x 128^2, 7.1 -> 2.0 ms with six BF16 products.
 namespace mfmac {
 constexpr int NT = 256;               // threads per workgroup
@@ -618,7 +619,7 @@ hipError_t launch_contract_batch(int precision, const ContractArgs* jobs, int n_
 //
 // Bound: HBM traffic (S read, T written and read, windows written) and the
 // latency of its short sums.  16,384 probes of 1245 beams, 128^2 windows at
-// 1024^2, split BF16: 7.0 ms in one stage, 1.2 + 1.1 ms in two (9.9 GB, 4.3
+// 1024^2, split BF16: 7.0 ms in one stage, 1.2 + 1.1 ms in two (10.4 GB, 4.5
 // TB/s), with the products of the second stage in FP32 accuracy: the error
 // against 64 bits falls from 7e-7 to 2.4e-7.  With T by [x][ky][row][column]
 // and 16-pixel tiles the first stage took 1.9 ms.
