@@ -932,11 +932,12 @@ int prism_set_build_streams(int32_t n) {
 // Items [first, end) in batches of NB on P streams: run(b0, i0, cnt, beside, q,
 // after) queues items b0 + i0 .. b0 + i0 + cnt - 1 of the batch starting at b0 on
 // stream q and records `after`, when not null, where the next stream may
-// start; `beside` such parts run at the same time.  Buffer slot i always holds item b0 + i of the current batch, and
-// stream k owns slots [off(k), off(k + 1)) in every batch (a short last batch
-// leaves the tail parts empty), so no two streams ever touch the same slot;
-// the forks of the first batch and the final joins are the only cross-stream
-// orderings needed.  On return all work is ordered on st, also after an error.
+// start; `beside` such parts run at the same time.  Buffer slot i always holds
+// item b0 + i of the current batch, and stream k owns slots [off(k), off(k + 1))
+// in every batch (a short last batch leaves the tail parts empty), so no two
+// streams ever touch the same slot; the forks of the first batch and the final
+// joins are the only cross-stream orderings needed.  On return all work is
+// ordered on st, also after an error.
 }  // extern "C"
 
 template <class Run>
